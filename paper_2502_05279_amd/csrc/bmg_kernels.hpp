@@ -19,6 +19,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace bmg {
 
 template <typename T>
@@ -538,24 +540,43 @@ static __global__ __launch_bounds__(BAND_FACTOR_THREADS) void k_band_factor(Lev<
 }
 
 // The factor as the one-wave solve reads it.  Unknowns are padded to M, a
-// multiple of 64; lane l keeps the pending values of unknowns 64q + l (block
-// q, "current") and 64(q+1) + l (block q+1, "next"), since w <= 64 means an
-// unknown only couples to its own block and the neighbouring one.  A step
-// subtracts multiples of one final unknown from at most w <= 64 pending ones,
-// one per lane, so every step has one row of 64 doubles (CF for the forward
-// substitution, CG for the backward one):
-//   forward step j = 64q + r:  CF[j][l] = L(64q + l, j)       for l > r (current block),
-//                                         L(64q + 64 + l, j)  for l <= r (next block);
-//   backward step k = 64q + r: CG[k][l] = L(k, 64q + l)       for l < r (current block),
-//                                         L(k, 64q - 64 + l)  for l >= r (previous block);
-// zero wherever the entry lies outside the band or the matrix; Dp = D padded
-// with ones.  The 64 rows of a block are contiguous (32 KB).
+// multiple of 64, and taken in blocks of 16 (block p: unknowns 16p .. 16p+15).
+// While block p is being finished, every 16-lane row of the wave holds the
+// block's pending values (`cur`, unknown 16p + i in lane i of each row), and
+// `pend` holds the pending values of the four blocks that come next, block b in
+// row b mod 4: w <= 64, so a step touches nothing further away.  A step then
+// takes its final value from lane t of each row by the row broadcast of the
+// multiply-add itself (DPP), without a trip through scalar registers.
+// Row of step s = 16p + t (CF forward, CG backward), 64 doubles, lane l = 16r + i:
+//   CF: r == p mod 4:  i > t:  -L(16p + i, s)          (cur)
+//                      i <= t: -L(16(p + 4) + i, s)    (pend)
+//       else, b the block of p+1 .. p+3 with b mod 4 == r: -L(16b + i, s);
+//   CG: r == p mod 4:  i < t:  -L(s, 16p + i)          (cur)
+//                      i >= t: -L(s, 16(p - 4) + i)    (pend)
+//       else, b the block of p-1 .. p-3 with b mod 4 == r: -L(s, 16b + i);
+// (-)zero wherever the entry lies outside the band or the matrix; Dp = D
+// padded with ones.  Two consecutive steps in the order they run (CG: t
+// descending) lie side by side per lane, so one 16-byte access per lane reads
+// both; the 64 rows of 4 blocks are contiguous (32 KB).
 struct BandSolve {
     const double *CF, *CG, *Dp;
     int m, M, nc;
 };
 
 __host__ __device__ inline int band_padded(int m) { return (m + 63) & ~63; }
+
+// Step s of a factor given by its entries Lf(i, k) of the forward and
+// Ub(k, i) of the backward substitution (the multiple of the final value of
+// unknown s that the pending value of unknown i loses), written by lane l.
+template <typename Fwd, typename Bwd>
+__device__ __forceinline__ void band_expand_step(int s, int l, double *CF, double *CG, Fwd &&fwd, Bwd &&bwd)
+{
+    const int p = s >> 4, t = s & 15, r = l >> 4, i = l & 15, e = 15 - t;
+    const int f = r == (p & 3) ? (i > t ? p : p + 4) : p + ((r - p) & 3);
+    const int g = r == (p & 3) ? (i < t ? p : p - 4) : p - ((p - r) & 3);
+    CF[((size_t)(p * 8 + (t >> 1)) * 64 + l) * 2 + (t & 1)] = -fwd(16 * f + i, s);
+    CG[((size_t)(p * 8 + (e >> 1)) * 64 + l) * 2 + (e & 1)] = -bwd(16 * g + i, s);
+}
 
 static __global__ void k_band_expand(int nc, const double *__restrict__ Lb, const double *__restrict__ D,
                                      double *__restrict__ CF, double *__restrict__ CG, double *__restrict__ Dp)
@@ -564,139 +585,255 @@ static __global__ void k_band_expand(int nc, const double *__restrict__ Lb, cons
     const int l = threadIdx.x & 63;
     const int s = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);   // step
     if (s >= M) return;
-    const int q = s >> 6, r = s & 63;
-    // L(i, k) for i - w <= k < i < m, else 0
+    // L(i, k) for 0 <= i - w <= k < i < m, else 0
     auto Lik = [&](int i, int k) -> double {
         return (i < m && k >= 0 && k < i && i - k <= w) ? Lb[(size_t)i * w + (k - i + w)] : 0.0;
     };
-    const size_t o = (size_t)s * 64 + l;
-    CF[o] = l > r ? Lik(64 * q + l, s) : Lik(64 * q + 64 + l, s);
-    CG[o] = l < r ? Lik(s, 64 * q + l) : (q >= 1 ? Lik(s, 64 * q - 64 + l) : 0.0);
+    band_expand_step(s, l, CF, CG, [&](int i, int k) { return Lik(i, k); }, [&](int i, int k) { return Lik(k, i); });
     if (l == 0) Dp[s] = s < m ? D[s] : 1.0;
 }
 
-// One step: the final value y of lane r is broadcast and y L is removed from
-// the pending values, each update one fused multiply-add (p - L y rounded
-// once); f0 applies to a0 (current block), f1 to a1.  A lane whose entry is
-// zero keeps its value (up to the sign of a zero).
-__device__ __forceinline__ void band_step(double &a0, double &a1, double f0, double f1, int r)
+typedef double band_v2d __attribute__((ext_vector_type(2)));
+
+// Eight steps of a block, H = 0 the first half: the final value y of lane t of
+// each row is broadcast within the row and y L is removed from the pending
+// values, each update one fused multiply-add rounded once (c, p hold -L for cur
+// and pend, two steps each; t ascending for DIR > 0, else descending).  A lane
+// whose entry is zero keeps its value (up to the sign of a zero).  A DPP operand
+// must not be read within two wait states of the vector instruction that
+// wrote it, and the compiler does not look into the block (it may even copy
+// cur just before it, hence the first wait): `cur` takes its own update first,
+// and `pend` reads its broadcast from a copy of cur as the previous step left
+// it (%2 and %3 in turn), so a step's copy and its update of pend are the two
+// instructions between a write of cur and its next use; waiting in their
+// place costs a slot more per step.
+template <int DIR, int H>
+__device__ __forceinline__ void band_steps(double &cur, double &pend, const band_v2d *c, const band_v2d *p)
 {
-    const double y = readlane_d(a0, r);
-    a0 = fma(-f0, y, a0);
-    a1 = fma(-f1, y, a1);
+    double copy = cur, mid;
+    constexpr int T0 = DIR > 0 ? 8 * H : 15 - 8 * H;
+    asm volatile("s_nop 1\n\t"
+                 "v_fmac_f64_dpp %0, %0, %4 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_mov_b64 %3, %0\n\t"
+                 "v_fmac_f64_dpp %1, %2, %12 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %0, %0, %5 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_mov_b64 %2, %0\n\t"
+                 "v_fmac_f64_dpp %1, %3, %13 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %0, %0, %6 row_newbcast:%22 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_mov_b64 %3, %0\n\t"
+                 "v_fmac_f64_dpp %1, %2, %14 row_newbcast:%22 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %0, %0, %7 row_newbcast:%23 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_mov_b64 %2, %0\n\t"
+                 "v_fmac_f64_dpp %1, %3, %15 row_newbcast:%23 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %0, %0, %8 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_mov_b64 %3, %0\n\t"
+                 "v_fmac_f64_dpp %1, %2, %16 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %0, %0, %9 row_newbcast:%25 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_mov_b64 %2, %0\n\t"
+                 "v_fmac_f64_dpp %1, %3, %17 row_newbcast:%25 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %0, %0, %10 row_newbcast:%26 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_mov_b64 %3, %0\n\t"
+                 "v_fmac_f64_dpp %1, %2, %18 row_newbcast:%26 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %0, %0, %11 row_newbcast:%27 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_mov_b64 %2, %0\n\t"
+                 "v_fmac_f64_dpp %1, %3, %19 row_newbcast:%27 row_mask:0xf bank_mask:0xf"
+                 : "+v"(cur), "+v"(pend), "+v"(copy), "=&v"(mid)
+                 : "v"(c[0].x), "v"(c[0].y), "v"(c[1].x), "v"(c[1].y), "v"(c[2].x), "v"(c[2].y), "v"(c[3].x),
+                   "v"(c[3].y), "v"(p[0].x), "v"(p[0].y), "v"(p[1].x), "v"(p[1].y), "v"(p[2].x), "v"(p[2].y),
+                   "v"(p[3].x), "v"(p[3].y), "n"(T0), "n"(T0 + DIR), "n"(T0 + 2 * DIR), "n"(T0 + 3 * DIR),
+                   "n"(T0 + 4 * DIR), "n"(T0 + 5 * DIR), "n"(T0 + 6 * DIR), "n"(T0 + 7 * DIR));
+}
+
+// Row R of v in every row of the wave: two copies swap their rows 16 lanes
+// apart, (0, 0, 2, 2) and (1, 1, 3, 3), then two copies of the one that holds
+// row R their halves.  v may come straight from band_steps, and a swap must not
+// read a register within two wait states of its write: the compiler, which
+// does not look into that block and would wait for each half in turn, is kept
+// out of it.
+template <int R>
+__device__ __forceinline__ double row_to_all(double v)
+{
+    double a, b;
+    asm volatile("v_mov_b64 %0, %2\n\t"
+                 "v_mov_b64 %1, %2\n\t"
+                 "s_nop 1" : "=&v"(a), "=&v"(b) : "v"(v));
+    auto swap = [](double &x, double &y, bool half) {
+        const long long p = __double_as_longlong(x), q = __double_as_longlong(y);
+        unsigned h[2][2] = {{(unsigned)p, (unsigned)(p >> 32)}, {(unsigned)q, (unsigned)(q >> 32)}};
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const auto t = half ? __builtin_amdgcn_permlane32_swap(h[0][k], h[1][k], false, false)
+                                : __builtin_amdgcn_permlane16_swap(h[0][k], h[1][k], false, false);
+            h[0][k] = t[0];
+            h[1][k] = t[1];
+        }
+        x = __longlong_as_double(((long long)h[0][1] << 32) | h[0][0]);
+        y = __longlong_as_double(((long long)h[1][1] << 32) | h[1][0]);
+    };
+    swap(a, b, false);
+    double c = (R & 1) ? b : a, d;
+    asm volatile("v_mov_b64 %0, %1\n\t"
+                 "s_nop 1" : "=&v"(d), "+v"(c));
+    swap(c, d, true);
+    return (R >> 1) ? d : c;
 }
 
 // The coarsest solve x = L^-T D^-1 L^-1 b, in the order of the oracle's
 // column form: y_i takes its terms over increasing j, z_i = y_i / D_i, x_i
 // takes its terms over decreasing k.  Run by one wave (lanes l = 0..63),
 // reading the step rows from global memory (the persistent small-level
-// kernel, whose coarsest level is small).  Steps of padding unknowns (index
+// kernel, whose coarsest level is small).  Blocks of padding unknowns (index
 // >= m) change nothing and are skipped.  get(k): right-hand side of unknown
 // k < m as FP64; put(k, x): the result; z: M doubles of scratch.
 template <typename Get, typename Put>
 __device__ void band_solve_direct(const BandSolve &B, Get get, Put put, double *z)
 {
-    const int l = threadIdx.x & 63, m = B.m, nb = B.M >> 6;
-    double a0 = l < m ? get(l) : 0.0;
-    double a1 = 64 + l < m ? get(64 + l) : 0.0;
-    constexpr int G = 16;   // steps whose rows are requested together
-    for (int q = 0; q < nb; ++q) {
-        const double *rows = B.CF + (size_t)q * 4096;
-        const int nr = min(64, m - 64 * q);
-        for (int r0 = 0; r0 < nr; r0 += G) {
-            double f[G];
+    const int l = threadIdx.x & 63, i = l & 15, r = l >> 4, m = B.m, nb = (m + 15) >> 4;
+    auto rhs = [&](int k) -> double { return k < m ? get(k) : 0.0; };
+    // the factors of a block: each half's registers take the next block's half
+    // once they are used, so its loads run behind the rest of the block
+    band_v2d fc[8], fp[8];
+    auto load = [&](const double *rows, int p, int k) {
+        const band_v2d *g = reinterpret_cast<const band_v2d *>(rows) + (size_t)(p * 8 + k) * 64;
+        fp[k] = g[l];
+        fc[k] = g[(p & 3) * 16 + i];
+    };
+    auto start = [&](const double *rows, int p) {
 #pragma unroll
-            for (int i = 0; i < G; ++i) f[i] = r0 + i < nr ? rows[(r0 + i) * 64 + l] : 0.0;
+        for (int k = 0; k < 8; ++k) load(rows, p, k);
+    };
+    // half h of the block, each entry zero where it belongs to the other of
+    // cur and pend; then the same half of block pn is requested
+    auto half = [&](auto dir, auto h, bool own, const double *rows, int pn, double &cur, double &pend) {
+        constexpr bool fwd = dir.value > 0;
+        band_v2d c[4], f[4];
 #pragma unroll
-            for (int i = 0; i < G; ++i) {
-                const int r = r0 + i;
-                if (r < nr) band_step(a0, a1, l > r ? f[i] : 0.0, l > r ? 0.0 : f[i], r);
-            }
+        for (int u = 0; u < 4; ++u) {
+            const int k = 4 * h.value + u, ta = fwd ? 2 * k : 15 - 2 * k, tb = fwd ? 2 * k + 1 : 14 - 2 * k;
+            const bool ca = fwd ? i > ta : i < ta, cb = fwd ? i > tb : i < tb;
+            c[u].x = ca ? fc[k].x : -0.0;
+            c[u].y = cb ? fc[k].y : -0.0;
+            f[u].x = own && ca ? -0.0 : fp[k].x;
+            f[u].y = own && cb ? -0.0 : fp[k].y;
         }
-        z[64 * q + l] = a0 / B.Dp[64 * q + l];
-        a0 = a1;
-        a1 = 64 * (q + 2) + l < m ? get(64 * (q + 2) + l) : 0.0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) load(rows, pn, 4 * h.value + u);
+        band_steps<dir.value, h.value>(cur, pend, c, f);
+    };
+    using Up = std::integral_constant<int, 1>;
+    using Down = std::integral_constant<int, -1>;
+    using First = std::integral_constant<int, 0>;
+    using Second = std::integral_constant<int, 1>;
+    auto next_cur = [](int rr, double pend) {
+        return rr == 0 ? row_to_all<0>(pend) : rr == 1 ? row_to_all<1>(pend)
+             : rr == 2 ? row_to_all<2>(pend) : row_to_all<3>(pend);
+    };
+    // rows 1..3 hold blocks 1..3, row 0 block 4
+    start(B.CF, 0);
+    double cur = rhs(i), pend = rhs(r == 0 ? 64 + i : l);
+    for (int p = 0; p < nb; ++p) {
+        const double nx = rhs(16 * (p + 5) + i);
+        const bool own = r == (p & 3);
+        const int pn = p + 1 < nb ? p + 1 : p;
+        half(Up{}, First{}, own, B.CF, pn, cur, pend);
+        half(Up{}, Second{}, own, B.CF, pn, cur, pend);
+        if (r == 0) z[16 * p + i] = cur / B.Dp[16 * p + i];
+        const int rr = (p + 1) & 3;
+        cur = next_cur(rr, pend);
+        pend = r == rr ? nx : pend;
     }
-    a0 = z[64 * (nb - 1) + l];
-    a1 = nb >= 2 ? z[64 * (nb - 2) + l] : 0.0;
-    for (int q = nb - 1; q >= 0; --q) {
-        const double *rows = B.CG + (size_t)q * 4096;
-        for (int r0 = min(63, m - 1 - 64 * q); r0 >= 0; r0 -= G) {
-            double g[G];
-#pragma unroll
-            for (int i = 0; i < G; ++i) g[i] = r0 - i >= 0 ? rows[(r0 - i) * 64 + l] : 0.0;
-#pragma unroll
-            for (int i = 0; i < G; ++i) {
-                const int r = r0 - i;
-                if (r >= 0) band_step(a0, a1, l < r ? g[i] : 0.0, l < r ? 0.0 : g[i], r);
-            }
-        }
-        if (64 * q + l < m) put(64 * q + l, a0);
-        a0 = a1;
-        a1 = q >= 2 ? z[64 * q - 128 + l] : 0.0;
+    auto zed = [&](int k) -> double { return k >= 0 ? z[k] : 0.0; };
+    start(B.CG, nb - 1);
+    // block b of nb-2 .. nb-5 in row b mod 4
+    cur = zed(16 * (nb - 1) + i);
+    pend = zed(16 * (nb - 2 - ((nb - 2 - r) & 3)) + i);
+    for (int p = nb - 1; p >= 0; --p) {
+        const double nx = zed(16 * (p - 5) + i);
+        const bool own = r == (p & 3);
+        const int pn = p > 0 ? p - 1 : p;
+        half(Down{}, First{}, own, B.CG, pn, cur, pend);
+        half(Down{}, Second{}, own, B.CG, pn, cur, pend);
+        if (r == 0 && 16 * p + i < m) put(16 * p + i, cur);
+        const int rr = (p - 1) & 3;
+        cur = next_cur(rr, pend);
+        pend = r == rr ? nx : pend;
     }
 }
 
 // The coarsest solve as a kernel of its own (the coarsest level is larger
 // than the persistent small-level kernel handles, or the basic path runs).
-// Wave 0 runs the chain of steps, BAND_CH per phase, reading each step's
-// pair of rows (current block, neighbouring block) from LDS, so a step is a
-// broadcast and two fused multiply-adds.  The loader waves expand the
-// compressed rows of phase c + 1 into the other of two LDS slots meanwhile,
-// the global loads of the phases after it already in flight in their
+// Wave 0 runs the chain of steps, 64 (four blocks) per phase, reading the
+// factors from LDS, so a step is two fused multiply-adds, a copy and half a
+// pair of 16-byte reads.  The loader waves split the rows of a phase into the
+// entries of `cur` and of `pend` (8 KB + 32 KB) in one of three LDS slots, two
+// phases ahead, so the chain's reads run ahead across the end of a phase; the
+// global loads of the phases after that are already in flight in the loaders'
 // registers (BAND_INFLIGHT sets), so memory latency stays behind the chain.
-// The right-hand side and the pivots are staged in LDS first (z, dpl), so
-// the chain itself waits on no global load.  Phases run forward through the blocks (two per block), then backward:
-// nch = 4 M / 64 phases, band_phases(nch) barriers on every wave.  Workgroup
-// k solves right-hand side k (its arrays ks elements, its stop flag kstop
-// ints after the first's).
+// The right-hand side is staged in LDS first (z).  Phases run forward through
+// the blocks, then backward: nch = M / 32 phases.  Workgroup k solves
+// right-hand side k (its arrays ks elements, its stop flag kstop ints after
+// the first's).
 constexpr int BAND_LOADERS = 8;
 constexpr int BAND_SOLVE_THREADS = 64 * (1 + BAND_LOADERS);
-constexpr int BAND_CH = 32;
 constexpr int BAND_INFLIGHT = 4;
-constexpr int BAND_PER_LANE = BAND_CH * 64 / 2 / (64 * BAND_LOADERS);   // double pairs per loader lane per phase
+constexpr int BAND_PER_LANE = 64 * 64 / 2 / (64 * BAND_LOADERS);   // double pairs per loader lane per phase
+constexpr int BAND_SLOT = 64 * 64 + 64 * 16;                       // doubles of a phase in LDS
 
-// Barriers of k_coarse_solve on every wave: one before the first phase and
-// one after each, rounded up to whole rounds of the loaders' register sets.
+// Phases the loaders write: one past the last (its slot is read ahead), in
+// whole rounds of the loaders' register sets; every wave passes one barrier
+// after each of them but the first.
 __host__ __device__ inline int band_phases(int nch) { return (nch + BAND_INFLIGHT) / BAND_INFLIGHT * BAND_INFLIGHT; }
 
-__host__ __device__ inline size_t band_solve_lds(int M) { return (2 * (size_t)M + 2 * BAND_CH * 128) * sizeof(double); }
+__host__ __device__ inline size_t band_solve_lds(int M) { return ((size_t)M + 3 * BAND_SLOT) * sizeof(double); }
 
-// Steps R0 + BAND_CH - 1 .. R0 (DIR < 0) or R0 .. R0 + BAND_CH - 1 of a block;
-// row t of the slot holds step R0 + t (current block at [0, 64), the
-// neighbouring one at [64, 128)).  Each step's pair of rows is read
-// BAND_AHEAD steps before it runs, and the steps keep their order (a
-// scheduling barrier after each), so the chain waits on no LDS read: left
-// to itself the scheduler reads a row just before its step to save
-// registers, and the read's latency joins the chain.  (Forming two steps'
-// broadcasts at once, the second from the first by one fused multiply-add
-// on the broadcast values, was measured slower: 21 ns per step against 19.6,
-// the extra operations costing more issue time than the broadcast saved.)
-#ifndef BMG_BAND_AHEAD
-#define BMG_BAND_AHEAD 8
-#endif
-constexpr int BAND_AHEAD = BMG_BAND_AHEAD;
-template <int R0, int DIR>
-__device__ __forceinline__ void band_phase(double &a0, double &a1, const double *rows, int l)
+// The factors of a block's eight pairs of steps, in running order.
+struct BandFactors {
+    band_v2d c[8], p[8];
+};
+
+// Pair k of a phase from its slot: `pend` entries per lane, then `cur` entries
+// per lane of a row.
+__device__ __forceinline__ void band_read(const double *slot, int l, int k, band_v2d &c, band_v2d &p)
 {
-    double f0[BAND_CH], f1[BAND_CH];
-    auto row = [&](int i) {
-        const int t = DIR > 0 ? i : BAND_CH - 1 - i;
-        f0[i] = rows[t * 128 + l];
-        f1[i] = rows[t * 128 + 64 + l];
-    };
+    p = reinterpret_cast<const band_v2d *>(slot)[k * 64 + l];
+    c = reinterpret_cast<const band_v2d *>(slot + 64 * 64)[k * 16 + (l & 15)];
+}
+
+// The four blocks of a phase.  The next block's factors are requested at the
+// start of a block (the scheduling barriers keep them there: left to itself
+// the scheduler reads a row just before its step to save registers, and the
+// read's latency joins the chain) and waited for at its end: an instruction
+// of any kind costs the lone wave about 5 clocks, a wait per pair as much as a
+// step's multiply-add.  nx, nx2: the pending values that enter as
+// blocks finish.  Returns the final values of the phase, lane l = unknown l of
+// the 64.
+template <int DIR>
+__device__ __forceinline__ double band_phase(double &cur, double &pend, BandFactors &A, const double *slot,
+                                             const double *next, int l, double nx, const double &nx2)
+{
+    const int r = l >> 4;
+    double fin = 0.0;
 #pragma unroll
-    for (int i = 0; i < BAND_AHEAD; ++i) row(i);
+    for (int b = 0; b < 4; ++b) {
+        BandFactors N;
 #pragma unroll
-    for (int i = 0; i < BAND_CH; ++i) {
-        if (i + BAND_AHEAD < BAND_CH) row(i + BAND_AHEAD);
-        band_step(a0, a1, f0[i], f1[i], R0 + (DIR > 0 ? i : BAND_CH - 1 - i));
+        for (int u = 0; u < 8; ++u)
+            band_read(b < 3 ? slot : next, l, b < 3 ? 8 * (b + 1) + u : u, N.c[u], N.p[u]);
         __builtin_amdgcn_sched_barrier(0);
+        band_steps<DIR, 0>(cur, pend, A.c, A.p);
+        band_steps<DIR, 1>(cur, pend, A.c + 4, A.p + 4);
+        __builtin_amdgcn_sched_barrier(0);
+        const int s = DIR > 0 ? b : 3 - b, rr = DIR > 0 ? (s + 1) & 3 : (s + 3) & 3;
+        fin = r == s ? cur : fin;
+        cur = rr == 0 ? row_to_all<0>(pend) : rr == 1 ? row_to_all<1>(pend)
+            : rr == 2 ? row_to_all<2>(pend) : row_to_all<3>(pend);
+        pend = r == rr ? (b < 3 ? nx : nx2) : pend;
+        __builtin_amdgcn_s_waitcnt(0xc07f);   // LDS reads only
+#pragma unroll
+        for (int k = 0; k < 8; ++k) asm volatile("" : "+v"(N.c[k]), "+v"(N.p[k]));
+        A = N;
     }
-    // both values complete here: the updates of a1 (off the chain) are not
-    // deferred past the barrier that follows, which would keep the phase's
-    // rows and broadcasts live across it
-    asm volatile("" : "+v"(a0), "+v"(a1));
+    return fin;
 }
 
 template <typename T>
@@ -704,106 +841,148 @@ static __global__ __launch_bounds__(BAND_SOLVE_THREADS) void k_coarse_solve(Lev<
                                                                                const int *stop, int kstop)
 {
     const int rk = blockIdx.x;
-    if (stopped(stop ? stop + rk * kstop : stop)) return;
     extern __shared__ double band_sm[];
-    double *z = band_sm, *dpl = band_sm + B.M, *slot = band_sm + 2 * B.M;
-    const int nb = B.M >> 6, nch = 4 * nb;
+    double *z = band_sm, *slots = band_sm + B.M;
+    const int nb = B.M >> 6, nch = 2 * nb;
     const int l = threadIdx.x & 63;
     const int nc = B.nc, m = B.m;
-    auto pos = [&](int k) { return (size_t)(k / nc + 1) * Cl.ld + (k % nc + 1); };
-    // every wave: the right-hand side as FP64 (zero past m) into z, the padded
-    // pivots into dpl, so that the chain reads no global memory
-    {
-        const T *bv = Cl.b + (size_t)rk * ks;
-        for (int k = threadIdx.x; k < B.M; k += BAND_SOLVE_THREADS) {
-            z[k] = k < m ? (double)bv[pos(k)] : 0.0;
-            dpl[k] = B.Dp[k];
-        }
-    }
     if (threadIdx.x >= 64) {
-        // loaders.  Phase c: block q, half h (steps 32h .. 32h + 31), forward
-        // for c < 2 nb, backward after; its rows are the contiguous rows
-        // 64q + 32h .. of CF or CG.
+        // loaders.  Phase c: the 64 unknowns q, forward for c < nb, backward
+        // after; its rows are contiguous in CF or CG.
         const int t0 = threadIdx.x - 64;
-        typedef double v2d __attribute__((ext_vector_type(2)));
-        auto where = [&](int c, int &q, int &h, bool &fwd) {
-            fwd = c < 2 * nb;
-            const int c2 = fwd ? c : c - 2 * nb;
-            q = fwd ? c2 >> 1 : nb - 1 - (c2 >> 1);
-            h = fwd ? (c2 & 1) : 1 - (c2 & 1);
-        };
         // the loads are unconditional (a phase past the last reads the last)
-        // and so are the phases, so that the compiler's wait for a set covers
-        // that set's loads only and the other sets stay in flight
-        v2d buf[BAND_INFLIGHT][BAND_PER_LANE];
-        auto request = [&](v2d(&r)[BAND_PER_LANE], int c) {
-            int q, h;
-            bool fwd;
-            where(min(c, nch - 1), q, h, fwd);
-            const v2d *g = reinterpret_cast<const v2d *>((fwd ? B.CF : B.CG) + ((size_t)q * 64 + 32 * h) * 64);
+        // and so are the phases, and the requests keep their order, so that
+        // the wait for a set covers that set's loads only and the other sets
+        // stay in flight
+        band_v2d buf[BAND_INFLIGHT][BAND_PER_LANE];
+        auto request = [&](band_v2d(&v)[BAND_PER_LANE], int c) {
+            const int cc = min(c, nch - 1);
+            const bool fwd = cc < nb;
+            const int q = fwd ? cc : nch - 1 - cc;
+            const band_v2d *g = reinterpret_cast<const band_v2d *>((fwd ? B.CF : B.CG) + (size_t)q * 4096);
 #pragma unroll
-            for (int e = 0; e < BAND_PER_LANE; ++e) r[e] = g[t0 + e * 64 * BAND_LOADERS];
+            for (int e = 0; e < BAND_PER_LANE; ++e) v[e] = g[t0 + e * 64 * BAND_LOADERS];
+            __builtin_amdgcn_sched_barrier(0);
         };
-        // phase c: the rows of phase c, expanded into pairs (current block,
-        // neighbouring block), go into slot c & 1 (a slot no longer read once
-        // c >= nch); the set then requests phase c + BAND_INFLIGHT
-        auto phase = [&](v2d(&r)[BAND_PER_LANE], int c) {
-            int q, h;
-            bool fwd;
-            where(min(c, nch - 1), q, h, fwd);
-            double *dst = slot + (size_t)(c & 1) * BAND_CH * 128;
+        // the right-hand side and the first rows are requested before the stop
+        // flag is known, so that their latencies overlap.  Unknown k sits at
+        // point (k mod nc, k div nc).
+        constexpr int NZ = BAND_MAX_NC * BAND_MAX_NC / (64 * BAND_LOADERS) + 1;
+        double zv[NZ];
+        {
+            const T *bv = Cl.b + (size_t)rk * ks;
+            int j = t0 / nc, i = t0 - j * nc;
+            const int dj = 64 * BAND_LOADERS / nc, di = 64 * BAND_LOADERS - dj * nc;
 #pragma unroll
-            for (int e = 0; e < BAND_PER_LANE; ++e) {
-                const int x = t0 + e * 64 * BAND_LOADERS;   // pair x of the phase's 32 x 32 pairs
-                const int t = x >> 5, lp = (x & 31) * 2, rr = 32 * h + t;
-                v2d c0, c1;
-                const bool k0 = fwd ? lp > rr : lp < rr, k1 = fwd ? lp + 1 > rr : lp + 1 < rr;
-                c0.x = k0 ? r[e].x : 0.0;
-                c1.x = k0 ? 0.0 : r[e].x;
-                c0.y = k1 ? r[e].y : 0.0;
-                c1.y = k1 ? 0.0 : r[e].y;
-                *reinterpret_cast<v2d *>(dst + t * 128 + lp) = c0;
-                *reinterpret_cast<v2d *>(dst + t * 128 + 64 + lp) = c1;
+            for (int e = 0; e < NZ; ++e) {
+                const bool in = t0 + e * 64 * BAND_LOADERS < m;
+                const double v = (double)bv[in ? (size_t)(j + 1) * Cl.ld + i + 1 : 0];
+                zv[e] = in ? v : 0.0;
+                i += di;
+                j += dj;
+                if (i >= nc) {
+                    i -= nc;
+                    ++j;
+                }
             }
-            request(r, c + BAND_INFLIGHT);
-            lds_barrier();
-        };
+        }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < BAND_INFLIGHT; ++u) request(buf[u], u);
+        if (stopped(stop ? stop + rk * kstop : stop)) return;
+#pragma unroll
+        for (int e = 0; e < NZ; ++e)
+            if (t0 + e * 64 * BAND_LOADERS < B.M) z[t0 + e * 64 * BAND_LOADERS] = zv[e];
+        // phase c: its rows go into slot c mod 3 (one that is no longer read),
+        // block by block in the order they run; the set then requests phase
+        // c + BAND_INFLIGHT.  Wave k holds pair k of each block, e = 0 .. 3:
+        // the `cur` entries of block e are in its row e, so the four blocks'
+        // are gathered into one write (an instruction costs a wave about 5
+        // clocks here, and the loaders have to keep up with the chain)
+        static_assert(BAND_LOADERS == 8 && BAND_PER_LANE == 4, "a loader wave holds one pair of each block");
+        const int k = __builtin_amdgcn_readfirstlane(t0 >> 6), i = l & 15, r = l >> 4;
+        const bool upx = i > 2 * k, upy = i > 2 * k + 1, dnx = i < 15 - 2 * k, dny = i < 14 - 2 * k;
+        double *dst = slots;
+        auto phase = [&](band_v2d(&v)[BAND_PER_LANE], int c) {
+            const bool fwd = c < nb;
+            const bool cx = fwd ? upx : dnx, cy = fwd ? upy : dny;   // an entry of cur, in the own row
+            band_v2d g = v[0];
+            band_v2d *pd = reinterpret_cast<band_v2d *>(dst) + k * 64 + l;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                band_v2d f = v[e];
+                const bool own = r == e;
+                if (e > 0) g = own ? f : g;
+                f.x = own && cx ? -0.0 : f.x;
+                f.y = own && cy ? -0.0 : f.y;
+                pd[(fwd ? e : 3 - e) * 8 * 64] = f;
+            }
+            g.x = cx ? g.x : -0.0;
+            g.y = cy ? g.y : -0.0;
+            reinterpret_cast<band_v2d *>(dst + 64 * 64)[((fwd ? r : 3 - r) * 8 + k) * 16 + i] = g;
+            dst = dst == slots + 2 * BAND_SLOT ? slots : dst + BAND_SLOT;
+            request(v, c + BAND_INFLIGHT);
+            if (c > 0) lds_barrier();
+        };
         for (int c0 = 0; c0 < band_phases(nch); c0 += BAND_INFLIGHT) {
 #pragma unroll
             for (int u = 0; u < BAND_INFLIGHT; ++u) phase(buf[u], c0 + u);
         }
         return;
     }
-    // wave 0: forward through the blocks, two phases each, then backward
+    // wave 0: forward through the blocks, then backward.  Unknown 64q + l of
+    // the next and the next but one 64 enter as blocks finish (zero outside).
+    // At barrier c the slots of phases c and c + 1 are filled.  The barrier
+    // between phases orders the loaders' later writes after this wave's reads
+    // of a slot, whose values have all been used by then, so the reads ahead
+    // stay in flight across it.
     T *uv = Cl.u + (size_t)rk * ks;
-    lds_barrier();                                  // phase 0, b and the pivots are in LDS
-    double a0 = z[l], a1 = nb >= 2 ? z[64 + l] : 0.0, bn = nb >= 3 ? z[128 + l] : 0.0;
+    const double *cs = slots, *ns = slots + BAND_SLOT;
+    auto turn = [&]() {
+        cs = ns;
+        ns = ns == slots + 2 * BAND_SLOT ? slots : ns + BAND_SLOT;
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    double d = B.Dp[l];
+    if (stopped(stop ? stop + rk * kstop : stop)) return;
+    __builtin_amdgcn_s_setprio(3);                  // before the loaders on the same SIMD
+    lds_barrier();                                  // phases 0 and 1 and b are in LDS
+    BandFactors A;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) band_read(cs, l, k, A.c[k], A.p[k]);
+    auto zq = [&](int q) -> double { return q >= 0 && q < nb ? z[64 * q + l] : 0.0; };
+    double cur = z[l & 15], nx = zq(1), pend = l < 16 ? nx : z[l];
     for (int q = 0; q < nb; ++q) {
-        band_phase<0, 1>(a0, a1, slot, l);
-        lds_barrier();
-        band_phase<32, 1>(a0, a1, slot + BAND_CH * 128, l);
-        z[64 * q + l] = a0 / dpl[64 * q + l];       // b of block q is no longer needed
-        a0 = a1;
-        a1 = bn;
-        bn = q + 3 < nb ? z[64 * (q + 3) + l] : 0.0;
-        lds_barrier();
+        const double nx2 = zq(q + 2), dn = B.Dp[64 * min(q + 1, nb - 1) + l];
+        const double fin = band_phase<1>(cur, pend, A, cs, ns, l, nx, nx2);
+        z[64 * q + l] = fin / d;                    // b of these unknowns is no longer needed
+        nx = nx2;
+        d = dn;
+        turn();
     }
-    a0 = z[64 * (nb - 1) + l];
-    a1 = nb >= 2 ? z[64 * (nb - 2) + l] : 0.0;
-    bn = nb >= 3 ? z[64 * (nb - 3) + l] : 0.0;
+    cur = z[64 * (nb - 1) + 48 + (l & 15)];
+    nx = zq(nb - 2);
+    pend = l >= 48 ? nx : z[64 * (nb - 1) + l];
+    // unknown k = 64q + l at point (k mod nc, k div nc), walked down with q
+    int k = 64 * (nb - 1) + l, j = k / nc, i = k - j * nc;
+    const int dj = 64 / nc, di = 64 - dj * nc;
     for (int q = nb - 1; q >= 0; --q) {
-        band_phase<32, -1>(a0, a1, slot, l);
-        lds_barrier();
-        band_phase<0, -1>(a0, a1, slot + BAND_CH * 128, l);
-        if (64 * q + l < m) uv[pos(64 * q + l)] = (T)a0;
-        a0 = a1;
-        a1 = bn;
-        bn = q >= 3 ? z[64 * (q - 3) + l] : 0.0;
-        lds_barrier();
+        const double nx2 = zq(q - 2);
+        const double x = band_phase<-1>(cur, pend, A, cs, ns, l, nx, nx2);
+        if (k < m) uv[(size_t)(j + 1) * Cl.ld + i + 1] = (T)x;
+        k -= 64;
+        j -= dj;
+        i -= di;
+        if (i < 0) {
+            i += nc;
+            --j;
+        }
+        nx = nx2;
+        if (q > 0) turn();
     }
-    for (int c = nch + 1; c < band_phases(nch); ++c) lds_barrier();   // the loaders' last phases
+    for (int c = nch; c < band_phases(nch) - 1; ++c) lds_barrier();   // the loaders' last phases
 }
 
 // ------------------------------------------------------ basic cycle steps

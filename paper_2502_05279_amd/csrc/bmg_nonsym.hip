@@ -460,16 +460,13 @@ __global__ void k_band_expand_ldu(int nc, const double *__restrict__ Lb, const d
     const int l = threadIdx.x & 63;
     const int s = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     if (s >= M) return;
-    const int q = s >> 6, r = s & 63;
     auto Lik = [&](int i, int k) -> double {
         return (i < m && k >= 0 && k < i && i - k <= w) ? Lb[(size_t)i * w + (k - i + w)] : 0.0;
     };
     auto Uik = [&](int i, int k) -> double {
         return (i >= 0 && k < m && i < k && k - i <= w) ? Ub[(size_t)i * w + (k - i - 1)] : 0.0;
     };
-    const size_t o = (size_t)s * 64 + l;
-    CF[o] = l > r ? Lik(64 * q + l, s) : Lik(64 * q + 64 + l, s);
-    CG[o] = l < r ? Uik(64 * q + l, s) : (q >= 1 ? Uik(64 * q - 64 + l, s) : 0.0);
+    band_expand_step(s, l, CF, CG, [&](int i, int k) { return Lik(i, k); }, [&](int i, int k) { return Uik(i, k); });
     if (l == 0) Dp[s] = s < m ? D[s] : 1.0;
 }
 
