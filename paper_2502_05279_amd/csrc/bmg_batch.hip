@@ -10,11 +10,12 @@
 // separated by grid-wide barriers:
 //   OUTER   r = b - A (x_hi + x_lo) in FP64 (accurate), partial ||r||^2, max|r|
 //   DECIDE  per problem: record ||r||/||b||, stop test, power-of-two scale s
-//   SCALE   b32 = fl32(r / s), u32 = 0
-//   PRE(d)  fused pre pass of every problem's level d (d = 0, 1, ...)
-//   SMALL   the sub-cycle of every problem's levels of at most 63 points
-//   POST(d) fused post pass, d descending
-//   UPDATE  (x_hi, x_lo) += s u32
+//   PRE(d)  fused pre pass of every problem's level d (d = 0, 1, ...); on the
+//           fine level b32 = fl32(r / s) and u32 = 0 are formed as rows enter
+//   SMALL   the sub-cycle of every problem's levels of at most SMALL_BATCH
+//           points (a whole problem of that size: also its scaling and update)
+//   POST(d) fused post pass, d descending; on the fine level the rows that
+//           come out go straight into (x_hi, x_lo) += s u32
 // Problems that have stopped skip their items; a step in which every problem
 // has stopped ends the launch.  Each problem's iterates are those of the
 // single-problem solver, bit for bit.
@@ -58,8 +59,34 @@ struct BProb {
     double *hist;                   // relative residual per refinement step
     const double *rhs;              // caller's arrays, n0 x n0
     double *x;
-    double bnorm, rel0, scale;
+    double bnorm, rel0, rel;        // rel: the last entry of hist
+    double scale, rmax;             // scale: least power of two >= rmax = max |r|
     int count, done;                // history entries; stop code (0 running)
+};
+
+// A value that no launch writes, at an address all lanes share, into scalar
+// registers.  The problem table also holds what the launch does write, so the
+// compiler has to take every field read through an ordinary pointer as
+// possibly changed by any store: the passes would fetch each array's address
+// from memory again at every access (a tile step took 17 us that way, 5 us
+// with the addresses in registers).
+template <typename F>
+__device__ __forceinline__ F constant(const F &f)
+{
+    static_assert(sizeof(F) % sizeof(int) == 0 && __is_trivially_copyable(F), "whole words");
+    typedef const __attribute__((address_space(4))) int *cptr;
+    const cptr w = (cptr) reinterpret_cast<const int *>(&f);
+    F out;
+    int *o = reinterpret_cast<int *>(&out);
+#pragma unroll
+    for (size_t k = 0; k < sizeof(F) / sizeof(int); ++k) o[k] = w[k];
+    return out;
+}
+
+struct SmallProb {
+    const SmallH<float> &H;
+    template <typename F>
+    __device__ __forceinline__ F get(const F &f) const { return constant(f); }
 };
 
 struct BLists {
@@ -67,6 +94,12 @@ struct BLists {
     int pre0[MAXD], pre1[MAXD], post0[MAXD], post1[MAXD];
     int ndepth;
 };
+
+constexpr int BAR_GROUPS = 32;
+struct GridBar {
+    unsigned count[16];   // a line of its own each
+};
+constexpr int BAR_LINES = BAR_GROUPS + 2;   // groups, root, generation
 
 struct BArgs {
     BProb *P;
@@ -76,6 +109,7 @@ struct BArgs {
     double tol;
     int maxc;
     int *active;                    // problems still running after the launch
+    GridBar *bar;                   // BAR_LINES of them, zero before the first launch
 };
 
 __device__ __forceinline__ double block_max(double v)
@@ -97,16 +131,16 @@ __device__ __forceinline__ double block_max(double v)
 }
 
 // Accurate FP64 residual of the five-point fine level, as k_resid_dd.
-__device__ __forceinline__ double fine_residual(const BProb &q, size_t p)
+__device__ __forceinline__ double fine_residual(const Lev<double> &L, const double *B0, const double *XH,
+                                                const double *XL, size_t p)
 {
-    const Lev<double> &L = q.L0;
     const size_t ld = L.ld;
     const size_t qq[5] = {p - ld, p - 1, p + 1, p + ld, p};
     const double a[5] = {L.S[p], L.W[p], L.W[p + 1], L.S[p + ld], L.O[p]};
-    double s = q.B0[p], c = 0.0, ns, se;
+    double s = B0[p], c = 0.0, ns, se;
 #pragma unroll
     for (int t = 0; t < 5; ++t) {
-        const double x = q.XH[qq[t]];
+        const double x = XH[qq[t]];
         const double pr = a[t] * x;
         const double pe = fma(a[t], x, -pr);
         two_sum(s, -pr, ns, se);
@@ -115,7 +149,7 @@ __device__ __forceinline__ double fine_residual(const BProb &q, size_t p)
     }
 #pragma unroll
     for (int t = 0; t < 5; ++t) {
-        two_sum(s, -(a[t] * q.XL[qq[t]]), ns, se);
+        two_sum(s, -(a[t] * XL[qq[t]]), ns, se);
         s = ns;
         c = c + se;
     }
@@ -124,14 +158,54 @@ __device__ __forceinline__ double fine_residual(const BProb &q, size_t p)
 
 enum { MODE_INIT = 1, MODE_STEPS = 2, MODE_FINISH = 3 };
 
-// Grid-wide barrier followed by a device-scope fence, so that every load after
-// it (through this CU's L1 and this XCD's L2) sees what other workgroups wrote
-// before the barrier.
-__device__ __forceinline__ void phase_barrier(cg::grid_group &grid)
-{
-    grid.sync();
-    __threadfence();
-}
+// Grid-wide barrier of a cooperative launch (every workgroup is resident, so
+// every wait ends), between device-scope release and acquire fences: every load
+// after it (through this CU's L1 and this XCD's L2) sees what other workgroups
+// wrote before it.  A device-scope fence writes back or invalidates the whole
+// L2, under the loads of every other workgroup of the XCD, so there is one of
+// each per workgroup (its waves share one L1) and none in the wait: the
+// workgroups count themselves in by groups, the last of a group at the root,
+// the last there raises the generation, and one thread per workgroup polls that
+// with plain loads.  (With the cooperative-groups barrier, and fences by every
+// wave around it, the batch of 60 problems took 5.4 ms per step, its early
+// finishers' polling slowing the rest; with this one and the arrays' addresses
+// in scalar registers 1.7 ms.)
+struct PhaseBarrier {
+    GridBar *bar;
+    unsigned gen;
+
+    __device__ __forceinline__ unsigned *generation() const { return bar[BAR_GROUPS + 1].count; }
+    __device__ __forceinline__ void start(GridBar *b)
+    {
+        bar = b;
+        // it only moves once every workgroup has arrived at the next barrier
+        gen = __hip_atomic_load(generation(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // true for the last of n arrivals, which also clears the count for the
+    // next barrier (nobody else touches it before this one ends)
+    __device__ __forceinline__ bool arrive(unsigned *c, unsigned n)
+    {
+        if (__hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 != n) return false;
+        __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
+        return true;
+    }
+    __device__ __forceinline__ void wait()
+    {
+        __syncthreads();
+        ++gen;
+        if (threadIdx.x == 0) {
+            const unsigned nb = gridDim.x, ng = min(nb, (unsigned)BAR_GROUPS), g = blockIdx.x % ng;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            if (arrive(bar[g].count, (nb - g + ng - 1) / ng) && arrive(bar[BAR_GROUPS].count, ng))
+                __hip_atomic_store(generation(), gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            while ((int)(__hip_atomic_load(generation(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - gen) < 0)
+                __builtin_amdgcn_s_sleep(2);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
+        __syncthreads();
+    }
+};
 
 __global__ __launch_bounds__(BT, 4) void k_batch(BArgs A, int mode, int steps)
 {
@@ -146,28 +220,33 @@ __global__ __launch_bounds__(BT, 4) void k_batch(BArgs A, int mode, int steps)
         if (bid == 0 && threadIdx.x == 0) *A.active = -1;
         return;
     }
+    PhaseBarrier phase;
+    phase.start(A.bar);
 
     if (mode == MODE_INIT) {
         // pack the caller's arrays, x_lo = 0, and ||b||^2 by chunks
         for (int it = A.li.chunk0 + bid; it < A.li.chunk1; it += nb) {
-            BProb &q = P[items[it].x];
-            const int c = items[it].y, n = q.n0, ld = q.L0.ld;
+            const int2 w = constant(items[it]);
+            const BProb &q = P[w.x];
+            const int c = w.y, n = constant(q.n0), ld = constant(q.L0.ld);
+            const double *rhs = constant(q.rhs), *x = constant(q.x);
+            double *B0 = constant(q.B0), *XH = constant(q.XH), *XL = constant(q.XL), *part = constant(q.part);
             const int j0 = 1 + c * CHUNK_ROWS, j1 = min(n, j0 + CHUNK_ROWS - 1);
             double acc = 0.0;
             for (int j = j0; j <= j1; ++j)
                 for (int i = 1 + threadIdx.x; i <= n; i += blockDim.x) {
                     const size_t p = (size_t)j * ld + i, s = (size_t)(j - 1) * n + (i - 1);
-                    const double b = q.rhs[s];
-                    q.B0[p] = b;
-                    q.XH[p] = q.x[s];
-                    q.XL[p] = 0.0;
+                    const double b = rhs[s];
+                    B0[p] = b;
+                    XH[p] = x[s];
+                    XL[p] = 0.0;
                     acc += b * b;
                 }
             acc = block_sum(acc);
-            if (threadIdx.x == 0) q.part[2 * c] = acc;
+            if (threadIdx.x == 0) part[2 * c] = acc;
             __syncthreads();
         }
-        phase_barrier(grid);
+        phase.wait();
         for (int it = A.li.prob0 + bid; it < A.li.prob1; it += nb) {
             BProb &q = P[items[it].x];
             if (threadIdx.x == 0) {
@@ -182,13 +261,16 @@ __global__ __launch_bounds__(BT, 4) void k_batch(BArgs A, int mode, int steps)
     }
     if (mode == MODE_FINISH) {
         for (int it = A.li.chunk0 + bid; it < A.li.chunk1; it += nb) {
-            BProb &q = P[items[it].x];
-            const int c = items[it].y, n = q.n0, ld = q.L0.ld;
+            const int2 w = constant(items[it]);
+            const BProb &q = P[w.x];
+            const int c = w.y, n = constant(q.n0), ld = constant(q.L0.ld);
+            const double *XH = constant(q.XH);
+            double *x = constant(q.x);
             const int j0 = 1 + c * CHUNK_ROWS, j1 = min(n, j0 + CHUNK_ROWS - 1);
             const bool zero = q.done == 5;
             for (int j = j0; j <= j1; ++j)
                 for (int i = 1 + threadIdx.x; i <= n; i += blockDim.x)
-                    q.x[(size_t)(j - 1) * n + (i - 1)] = zero ? 0.0 : q.XH[(size_t)j * ld + i];
+                    x[(size_t)(j - 1) * n + (i - 1)] = zero ? 0.0 : XH[(size_t)j * ld + i];
         }
         return;
     }
@@ -196,16 +278,20 @@ __global__ __launch_bounds__(BT, 4) void k_batch(BArgs A, int mode, int steps)
     for (int step = 0; step < steps; ++step) {
         // OUTER: accurate FP64 residual of the pair, by row chunks
         for (int it = A.li.chunk0 + bid; it < A.li.chunk1; it += nb) {
-            BProb &q = P[items[it].x];
+            const int2 w = constant(items[it]);
+            const BProb &q = P[w.x];
             if (q.done) continue;
-            const int c = items[it].y, n = q.n0, ld = q.L0.ld;
+            const Lev<double> L = constant(q.L0);
+            const double *B0 = constant(q.B0), *XH = constant(q.XH), *XL = constant(q.XL);
+            double *part = constant(q.part);
+            const int c = w.y, n = L.n, ld = L.ld;
             const int j0 = 1 + c * CHUNK_ROWS, j1 = min(n, j0 + CHUNK_ROWS - 1);
             double acc = 0.0, mx = 0.0;
             for (int j = j0; j <= j1; ++j)
                 for (int i = 1 + threadIdx.x; i <= n; i += blockDim.x) {
                     const size_t p = (size_t)j * ld + i;
-                    const double r = fine_residual(q, p);
-                    q.L0.r[p] = r;
+                    const double r = fine_residual(L, B0, XH, XL, p);
+                    L.r[p] = r;
                     acc += r * r;
                     mx = fmax(mx, fabs(r));
                 }
@@ -213,122 +299,132 @@ __global__ __launch_bounds__(BT, 4) void k_batch(BArgs A, int mode, int steps)
             __syncthreads();
             mx = block_max(mx);
             if (threadIdx.x == 0) {
-                q.part[2 * c] = acc;
-                q.part[2 * c + 1] = mx;
+                part[2 * c] = acc;
+                part[2 * c + 1] = mx;
             }
             __syncthreads();
         }
-        phase_barrier(grid);
-        // DECIDE: history, stop test, scale (one thread per problem)
+        phase.wait();
+        // DECIDE: history, stop test, scale.  The chunks' partials are fetched
+        // side by side; one thread adds them in order.
         for (int it = A.li.prob0 + bid; it < A.li.prob1; it += nb) {
-            BProb &q = P[items[it].x];
-            if (threadIdx.x != 0 || q.done) continue;
+            BProb &q = P[constant(items[it].x)];
+            if (q.done) continue;
+            double *sp = reinterpret_cast<double *>(smem);      // BT pairs: 4 KB
+            const double *part = constant(q.part);
+            const int nchunks = constant(q.nchunks);
             double s = 0.0, mx = 0.0;
-            for (int c = 0; c < q.nchunks; ++c) {
-                s += q.part[2 * c];
-                mx = fmax(mx, q.part[2 * c + 1]);
+            for (int c0 = 0; c0 < nchunks; c0 += BT) {
+                const int c = c0 + (int)threadIdx.x;
+                if (c < nchunks) {
+                    sp[2 * threadIdx.x] = part[2 * c];
+                    sp[2 * threadIdx.x + 1] = part[2 * c + 1];
+                }
+                __syncthreads();
+                if (threadIdx.x == 0)
+                    for (int k = 0; k < min(BT, nchunks - c0); ++k) {
+                        s += sp[2 * k];
+                        mx = fmax(mx, sp[2 * k + 1]);
+                    }
+                __syncthreads();
             }
+            if (threadIdx.x != 0) continue;
             const double rel = sqrt(s) / q.bnorm;
             const int k = q.count;
-            q.hist[k] = rel;
+            constant(q.hist)[k] = rel;
+            q.rel = rel;
             if (k == 0) q.rel0 = rel;
             q.count = k + 1;
             if (rel <= A.tol) q.done = 1;
             else if (!isfinite(rel) || rel > 1e3 * q.rel0) q.done = 2;
             else if (k + 1 >= A.maxc) q.done = 3;
             else {
-                int e = 0;
-                const double fr = frexp(mx, &e);
-                if (fr == 0.5) e -= 1;
-                if (fr == 0.0) e = 0;
-                q.scale = ldexp(1.0, e);
+                q.rmax = mx;
+                q.scale = ldexp(1.0, ir_exponent(mx));
             }
         }
-        phase_barrier(grid);
+        phase.wait();
         {
             int running = 0;
-            for (int p = 0; p < A.nprob; ++p) running += P[p].done == 0;
-            if (running == 0) {
+            for (int p = threadIdx.x; p < A.nprob; p += BT) running |= P[p].done == 0;
+            if (!__syncthreads_or(running)) {
                 if (bid == 0 && threadIdx.x == 0) *A.active = 0;
                 return;
             }
         }
-        // SCALE: b32 = fl32(r / s), u32 = 0
-        for (int it = A.li.chunk0 + bid; it < A.li.chunk1; it += nb) {
-            BProb &q = P[items[it].x];
-            if (q.done) continue;
-            const int c = items[it].y, n = q.n0, ld = q.L0.ld;
-            const int j0 = 1 + c * CHUNK_ROWS, j1 = min(n, j0 + CHUNK_ROWS - 1);
-            const double inv = 1.0 / q.scale;       // exact: a power of two
-            for (int j = j0; j <= j1; ++j)
-                for (int i = 1 + threadIdx.x; i <= n; i += blockDim.x) {
-                    const size_t p = (size_t)j * ld + i;
-                    q.L[0].b[p] = (float)(q.L0.r[p] * inv);
-                    q.L[0].u[p] = 0.0f;
-                }
-        }
-        phase_barrier(grid);
         // PRE(d): fused nu1 = 2 sweeps, residual, restriction, by tiles
         for (int d = 0; d < A.li.ndepth; ++d) {
-            for (int it = A.li.pre0[d] + bid; it < A.li.pre1[d]; it += nb) {
-                BProb &q = P[items[it].x];
+            const int i0 = A.li.pre0[d], i1 = A.li.pre1[d];
+            for (int it = i0 + bid; it < i1; it += nb) {
+                const int2 w = constant(items[it]);
+                BProb &q = P[w.x];
                 if (q.done) continue;
-                if (d == 0)
-                    pre_tile<float, false, 2>(q.L[0], q.ualt[0], q.C[0], q.L[1], q.gpre[0], items[it].y,
-                                              *reinterpret_cast<TileLds<float, false, 2> *>(smem));
-                else
-                    pre_tile<float, true, 2>(q.L[d], q.ualt[d], q.C[d], q.L[d + 1], q.gpre[d], items[it].y,
-                                             *reinterpret_cast<TileLds<float, true, 2> *>(smem));
+                const Lev<float> L = constant(q.L[d]), Lc = constant(q.L[d + 1]);
+                const Wts<float> C = constant(q.C[d]);
+                const TileGeo g = constant(q.gpre[d]);
+                float *out = constant(q.ualt[d]);
+                if (d == 0) {
+                    // (tile 0 writes the scale once more, the same value)
+                    const IrArgs ir{constant(q.L0.r), &q.rmax, &q.scale, nullptr, nullptr};
+                    pre_tile<float, false, 2, false, true>(L, out, C, Lc, g, w.y,
+                                                           *reinterpret_cast<TileLds<float, false, 2> *>(smem), ir);
+                } else {
+                    pre_tile<float, true, 2>(L, out, C, Lc, g, w.y, *reinterpret_cast<TileLds<float, true, 2> *>(smem));
+                }
                 __syncthreads();
             }
-            phase_barrier(grid);
+            phase.wait();
         }
-        // SMALL: the sub-cycle of the levels of at most 63 points, per problem
+        // SMALL: the sub-cycle of the levels of at most SMALL_BATCH points
         for (int it = A.li.prob0 + bid; it < A.li.prob1; it += nb) {
-            BProb &q = P[items[it].x];
+            const BProb &q = P[constant(items[it].x)];
             if (q.done) continue;
-            if (q.sdepth == 0) small_vcycle_body<float, false>(q.small, reinterpret_cast<float *>(smem), 0);
-            else small_vcycle_body<float, true>(q.small, reinterpret_cast<float *>(smem), 0);
+            if (constant(q.sdepth) == 0) {
+                // the whole problem: its scaling, its cycle and its update
+                const Lev<float> F = constant(q.L[0]);
+                const double *r = constant(q.L0.r);
+                double *XH = constant(q.XH), *XL = constant(q.XL);
+                const double inv = 1.0 / q.scale;       // exact: a power of two
+                auto points = [&](auto f) {
+                    for (int t = threadIdx.x; t < F.n * F.n; t += BT)
+                        f((size_t)(1 + t / F.n) * F.ld + (1 + t % F.n));
+                };
+                points([&](size_t p) { F.b[p] = (float)(r[p] * inv); });
+                __syncthreads();
+                small_vcycle_body<float, false>(SmallProb{q.small}, reinterpret_cast<float *>(smem), 0);
+                __syncthreads();
+                points([&](size_t p) { dd_add_point(XH, XL, p, q.scale * (double)F.u[p]); });
+            } else {
+                small_vcycle_body<float, true>(SmallProb{q.small}, reinterpret_cast<float *>(smem), 0);
+            }
             __syncthreads();
         }
-        phase_barrier(grid);
+        phase.wait();
         // POST(d): interpolation and nu2 = 1 sweep, d descending
         for (int d = A.li.ndepth - 1; d >= 0; --d) {
-            for (int it = A.li.post0[d] + bid; it < A.li.post1[d]; it += nb) {
-                BProb &q = P[items[it].x];
+            const int i0 = A.li.post0[d], i1 = A.li.post1[d];
+            for (int it = i0 + bid; it < i1; it += nb) {
+                const int2 w = constant(items[it]);
+                BProb &q = P[w.x];
                 if (q.done) continue;
-                Lev<float> L = q.L[d];
+                Lev<float> L = constant(q.L[d]);
+                const float *ec = constant(q.L[d + 1].u);
+                const Wts<float> C = constant(q.C[d]);
+                const TileGeo g = constant(q.gpost[d]);
                 float *out = L.u;
-                L.u = q.ualt[d];
-                if (d == 0)
-                    post_tile<float, false, 1, false>(L, out, q.C[0], q.L[1].u, q.gpost[0], items[it].y, nullptr,
-                                                      *reinterpret_cast<TileLds<float, false, 1> *>(smem));
-                else
-                    post_tile<float, true, 1, false>(L, out, q.C[d], q.L[d + 1].u, q.gpost[d], items[it].y, nullptr,
+                L.u = constant(q.ualt[d]);
+                if (d == 0) {
+                    const IrArgs ir{nullptr, nullptr, &q.scale, constant(q.XH), constant(q.XL)};
+                    post_tile<float, false, 1, false, true>(L, out, C, ec, g, w.y, nullptr,
+                                                            *reinterpret_cast<TileLds<float, false, 1> *>(smem), ir);
+                } else {
+                    post_tile<float, true, 1, false>(L, out, C, ec, g, w.y, nullptr,
                                                      *reinterpret_cast<TileLds<float, true, 1> *>(smem));
+                }
                 __syncthreads();
             }
-            phase_barrier(grid);
+            phase.wait();
         }
-        // UPDATE: (x_hi, x_lo) += s u32
-        for (int it = A.li.chunk0 + bid; it < A.li.chunk1; it += nb) {
-            BProb &q = P[items[it].x];
-            if (q.done) continue;
-            const int c = items[it].y, n = q.n0, ld = q.L0.ld;
-            const int j0 = 1 + c * CHUNK_ROWS, j1 = min(n, j0 + CHUNK_ROWS - 1);
-            for (int j = j0; j <= j1; ++j)
-                for (int i = 1 + threadIdx.x; i <= n; i += blockDim.x) {
-                    const size_t p = (size_t)j * ld + i;
-                    const double dd = q.scale * (double)q.L[0].u[p];
-                    double s, e;
-                    two_sum(q.XH[p], dd, s, e);
-                    e = e + q.XL[p];
-                    const double hi = s + e;
-                    q.XL[p] = e - (hi - s);
-                    q.XH[p] = hi;
-                }
-        }
-        phase_barrier(grid);
     }
     if (bid == 0 && threadIdx.x == 0) {
         int running = 0;
@@ -353,6 +449,35 @@ size_t max_items(int n)
     return t;
 }
 
+// First level of the per-problem sub-cycle.
+int small_depth(const bmg_solver *h)
+{
+    int d = 0;
+    while (d < h->nlev - 1 && h->L32[d].n > SMALL_BATCH) ++d;
+    return d;
+}
+
+// Rows per tile of a level of size n: the handle's or the tuned table's, else
+// (n + 1) / 16 between 4 and `tallest`.  A tile re-reads and recomputes about
+// ten rows beyond its own, so tall tiles do less work, but a phase lasts at
+// least one tile and problems that have stopped leave workgroups idle:
+// `tallest` is the height at which the fine levels' tiles together make one
+// round of the resident workgroups, at most 32.  Solving 60 problems of 63^2 to
+// 1023^2: 44.8 ms with 32, 32, 16, 8, 4 rows on 1023^2 .. 63^2, 47 with 16
+// everywhere, 61 with 64 and with the single-problem heights (12 to 2); 10
+// such problems: 21 ms with those rows, 19.5 with at most 12.
+int batch_tallest(double points, int nblocks)
+{
+    const int rows = (int)(points / ((double)(FW - 16) * nblocks)) & ~1;
+    return std::min(32, std::max(4, rows));
+}
+
+int batch_tile_rows(const bmg_solver *h, int n, int tallest)
+{
+    if (h->opt.tile_rows > 0 || tuned_tile_rows(n) > 0) return tile_rows_for(h, n, false);
+    return std::max(4, std::min(tallest, ((n + 1) / 16) & ~1));
+}
+
 }  // namespace
 
 struct bmg_batch {
@@ -360,9 +485,11 @@ struct bmg_batch {
     hipStream_t st = nullptr;
     std::vector<bmg_solver *> sub;
     std::vector<int> n;
+    std::vector<BProb> hP;          // the table as set up; the solve's pointers
     BProb *dP = nullptr;
     int2 *ditems = nullptr;
     int *dactive = nullptr;
+    GridBar *dbar = nullptr;
     BLists li{};
     int nitems = 0;
     int maxc = 0;
@@ -411,7 +538,7 @@ size_t batch_layout(int nprob, const int *n, const bmg_options &op, std::vector<
     off = align_up(off + items * sizeof(int2));
     off = align_up(off + parts * sizeof(double));
     off = align_up(off + (size_t)nprob * (op.max_cycles + 2) * sizeof(double));
-    off = align_up(off + 64);
+    off = align_up(off + 64 + BAR_LINES * sizeof(GridBar));
     return off;
 }
 
@@ -482,20 +609,46 @@ bmg_status bmg_batch_setup(bmg_batch **out, int nprob, const int *n, const doubl
     double *dhist = (double *)(ws + off);
     off = align_up(off + (size_t)nprob * (op.max_cycles + 2) * sizeof(double));
     B->dactive = (int *)(ws + off);
+    B->dbar = (GridBar *)(ws + off + 64);
 
-    std::vector<BProb> hp(nprob);
+    std::vector<BProb> &hp = B->hP;
+    hp.assign(nprob, BProb{});
     std::vector<int2> chunks, probs, pre[MAXD], post[MAXD];
     size_t part_off = 0;
     int ndepth = 0;
+    B->lds = std::max({sizeof(TileLds<float, true, 2>), sizeof(TileLds<float, false, 2>),
+                       sizeof(TileLds<float, true, 1>)});
+    double points = 0.0;
+    for (int p = 0; p < nprob; ++p) {
+        SmallH<float> &S = hp[p].small;
+        const bmg_solver *h = B->sub[p];
+        const int d = small_depth(h);
+        if (d > MAXD) return bail(fail(BMG_EINVAL, "problem %d is too large for the batch", p));
+        S.nl = h->nlev - d;
+        if (S.nl > SMALL_MAXL) return bail(fail(BMG_EINVAL, "problem %d: too many small levels", p));
+        for (int k = 0; k < S.nl; ++k) {
+            S.L[k] = h->L32[d + k];
+            if (k + 1 < S.nl) S.C[k] = h->C32[d + k];
+        }
+        B->lds = std::max(B->lds, (size_t)small_layout(S) * sizeof(float));
+        points += (double)n[p] * n[p];
+    }
+    // every workgroup of the persistent launch must be resident at once
+    if (hipFuncSetAttribute((const void *)k_batch, hipFuncAttributeMaxDynamicSharedMemorySize, (int)B->lds) != hipSuccess)
+        return bail(fail(BMG_EDEVICE, "cannot reserve %zu bytes of LDS", B->lds));
+    int per_cu = 0, dev = 0, ncu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch, BT, B->lds) != hipSuccess ||
+        hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || per_cu < 1)
+        return bail(fail(BMG_EDEVICE, "occupancy query failed"));
+    B->nblocks = per_cu * ncu;
+    const int tallest = batch_tallest(points, B->nblocks);
     for (int p = 0; p < nprob; ++p) {
         bmg_solver *h = B->sub[p];
         BProb &q = hp[p];
-        memset(&q, 0, sizeof q);
         q.n0 = n[p];
         q.nlev = h->nlev;
-        q.sdepth = 0;
-        while (q.sdepth < h->nlev - 1 && h->L32[q.sdepth].n > SMALL_BATCH) ++q.sdepth;
-        if (q.sdepth > MAXD) return bail(fail(BMG_EINVAL, "problem %d is too large for the batch", p));
+        q.sdepth = small_depth(h);
         ndepth = std::max(ndepth, q.sdepth);
         for (int l = 0; l < h->nlev; ++l) {
             q.L[l] = h->L32[l];
@@ -503,24 +656,15 @@ bmg_status bmg_batch_setup(bmg_batch **out, int nprob, const int *n, const doubl
             q.ualt[l] = h->ualt32[l];
         }
         for (int d = 0; d < q.sdepth; ++d) {
-            const int nl = h->L32[d].n, rows = tile_rows_for(h, nl, h->nine[d]);
+            const int nl = h->L32[d].n, rows = batch_tile_rows(h, nl, tallest);
             q.gpre[d] = tile_geo(nl, d == 0 ? 6 : 10, rows);
             q.gpost[d] = tile_geo(nl, d == 0 ? 4 : 6, rows);
             for (int t = 0; t < q.gpre[d].ntiles; ++t) pre[d].push_back(make_int2(p, t));
             for (int t = 0; t < q.gpost[d].ntiles; ++t) post[d].push_back(make_int2(p, t));
         }
-        SmallH<float> &S = q.small;
-        S.nl = h->nlev - q.sdepth;
-        if (S.nl > SMALL_MAXL) return bail(fail(BMG_EINVAL, "problem %d: too many small levels", p));
-        for (int k = 0; k < S.nl; ++k) {
-            S.L[k] = h->L32[q.sdepth + k];
-            if (k + 1 < S.nl) S.C[k] = h->C32[q.sdepth + k];
-        }
-        const int lds_small = small_layout(S) * (int)sizeof(float);
-        B->lds = std::max(B->lds, (size_t)lds_small);
-        S.band = h->band;
-        S.nu1 = 2;
-        S.nu2 = 1;
+        q.small.band = h->band;
+        q.small.nu1 = 2;
+        q.small.nu2 = 1;
         q.L0 = h->L[0];
         q.B0 = h->B0;
         q.XH = h->XH;
@@ -549,21 +693,11 @@ bmg_status bmg_batch_setup(bmg_batch **out, int nprob, const int *n, const doubl
     B->li.ndepth = ndepth;
     if (all.size() > items_cap) return bail(fail(BMG_EINVAL, "item list overflow"));
     B->nitems = (int)all.size();
-    B->lds = std::max({B->lds, sizeof(TileLds<float, true, 2>), sizeof(TileLds<float, false, 2>),
-                       sizeof(TileLds<float, true, 1>)});
-    if (hipMemcpyAsync(B->dP, hp.data(), hp.size() * sizeof(BProb), hipMemcpyHostToDevice, B->st) != hipSuccess ||
+    if (hipMemsetAsync(B->dbar, 0, BAR_LINES * sizeof(GridBar), B->st) != hipSuccess ||
+        hipMemcpyAsync(B->dP, hp.data(), hp.size() * sizeof(BProb), hipMemcpyHostToDevice, B->st) != hipSuccess ||
         hipMemcpyAsync(B->ditems, all.data(), all.size() * sizeof(int2), hipMemcpyHostToDevice, B->st) != hipSuccess ||
         hipStreamSynchronize(B->st) != hipSuccess)
         return bail(fail(BMG_EDEVICE, "uploading the batch tables failed"));
-    // every workgroup of the persistent launch must be resident at once
-    if (hipFuncSetAttribute((const void *)k_batch, hipFuncAttributeMaxDynamicSharedMemorySize, (int)B->lds) != hipSuccess)
-        return bail(fail(BMG_EDEVICE, "cannot reserve %zu bytes of LDS", B->lds));
-    int per_cu = 0, dev = 0, ncu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch, BT, B->lds) != hipSuccess ||
-        hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || per_cu < 1)
-        return bail(fail(BMG_EDEVICE, "occupancy query failed"));
-    B->nblocks = per_cu * ncu;
     *out = B;
     return BMG_OK;
 }
@@ -582,6 +716,7 @@ BArgs batch_args(const bmg_batch *B, double tol)
     A.tol = tol;
     A.maxc = B->maxc;
     A.active = B->dactive;
+    A.bar = B->dbar;
     return A;
 }
 
@@ -649,14 +784,14 @@ bmg_status bmg_batch_solve(bmg_batch *B, const double *const *rhs, double *const
 {
     if (!B || !rhs || !x) return fail(BMG_EINVAL, "NULL argument");
     if (!(tol >= 0.0)) return fail(BMG_EINVAL, "tol must be >= 0");
-    // caller pointers into the problem table
+    // caller pointers into the problem table (what the last solve left in it
+    // is written afresh by the first launch)
     for (int p = 0; p < B->nprob; ++p) {
         if (!rhs[p] || !x[p]) return fail(BMG_EINVAL, "problem %d: NULL array", p);
-        HIPCHK(hipMemcpyAsync((char *)(B->dP + p) + offsetof(BProb, rhs), &rhs[p], sizeof(double *),
-                              hipMemcpyHostToDevice, B->st));
-        HIPCHK(hipMemcpyAsync((char *)(B->dP + p) + offsetof(BProb, x), &x[p], sizeof(double *),
-                              hipMemcpyHostToDevice, B->st));
+        B->hP[p].rhs = rhs[p];
+        B->hP[p].x = x[p];
     }
+    HIPCHK(hipMemcpyAsync(B->dP, B->hP.data(), B->hP.size() * sizeof(BProb), hipMemcpyHostToDevice, B->st));
     TRY(batch_launch(B, MODE_INIT, 0, tol));
     const int per_launch = 8;
     int active = 1;
@@ -687,12 +822,7 @@ bmg_status bmg_batch_solve(bmg_batch *B, const double *const *rhs, double *const
     for (int p = 0; p < B->nprob; ++p) {
         const int steps = hp[p].done == 5 ? 0 : hp[p].count - 1;
         if (steps_out) steps_out[p] = steps;
-        if (rel_res) {
-            double v = 0.0;
-            if (hp[p].count > 0)
-                HIPCHK(hipMemcpy(&v, hp[p].hist + hp[p].count - 1, sizeof v, hipMemcpyDeviceToHost));
-            rel_res[p] = v;
-        }
+        if (rel_res) rel_res[p] = hp[p].count > 0 ? hp[p].rel : 0.0;
         if (hp[p].done == 2 && st == BMG_OK) st = fail(BMG_EDIVERGED, "problem %d diverged", p);
         if (hp[p].done == 3 && st == BMG_OK) st = fail(BMG_ENOCONV, "problem %d did not converge", p);
     }

@@ -1630,43 +1630,57 @@ __host__ __device__ inline int small_layout(SmallH<T> &H)
     return off;
 }
 
-template <typename T, bool NINE0>
-__device__ void small_vcycle_body(const SmallH<T> &H, T *sm, size_t rhs_off)
+// The fields of a small sub-cycle's description H are read through H.get(field
+// of SmallH), so that the batched kernel can keep the description in memory
+// and still have them in scalar registers; a kernel's own argument is there
+// anyway.
+template <typename T>
+struct SmallArg {
+    const SmallH<T> &H;
+    template <typename F>
+    __device__ __forceinline__ F get(const F &f) const { return f; }
+};
+
+template <typename T, bool NINE0, typename Src>
+__device__ void small_vcycle_body(const Src &A, T *sm, size_t rhs_off)
 {
-    const int nl = H.nl, last = nl - 1;
+    const SmallH<T> &H = A.H;
+    const int nl = A.get(H.nl), last = nl - 1;
     // fetch b of the first level, zero every iterate and the coarser b
     for (int l = 0; l < nl; ++l) {
-        const int n = H.L[l].n, p = n + 2;
-        T *u = sm + H.off_u[l], *b = sm + H.off_b[l];
+        const Lev<T> L = A.get(H.L[l]);
+        const int n = L.n, p = n + 2;
+        T *u = sm + A.get(H.off_u[l]), *b = sm + A.get(H.off_b[l]);
         for (int t = threadIdx.x; t < p * p; t += blockDim.x) {
             const int i = t % p, j = t / p;
             u[t] = (T)0;
-            b[t] = (l == 0 && i >= 1 && i <= n && j >= 1 && j <= n) ? H.L[0].b[rhs_off + (size_t)j * H.L[0].ld + i]
+            b[t] = (l == 0 && i >= 1 && i <= n && j >= 1 && j <= n) ? L.b[rhs_off + (size_t)j * L.ld + i]
                                                                      : (T)0;
         }
     }
-    T *r = sm + H.off_r;
-    for (int t = threadIdx.x; t < (H.L[0].n + 2) * (H.L[0].n + 2); t += blockDim.x) r[t] = (T)0;
+    T *r = sm + A.get(H.off_r);
+    const int n0 = A.get(H.L[0].n);
+    for (int t = threadIdx.x; t < (n0 + 2) * (n0 + 2); t += blockDim.x) r[t] = (T)0;
     __syncthreads();
     // down: relax, residual, restrict
     SmallPts<T> P;
     for (int l = 0; l < last; ++l) {
-        const Lev<T> &L = H.L[l];
-        T *u = sm + H.off_u[l], *b = sm + H.off_b[l];
+        const Lev<T> L = A.get(H.L[l]);
+        T *u = sm + A.get(H.off_u[l]), *b = sm + A.get(H.off_b[l]);
         const int p = L.n + 2;
         if (l > 0 || NINE0) {
             small_load<T, true>(L, P);
-            small_relax<T, true>(P, p, u, b, H.nu1);
+            small_relax<T, true>(P, p, u, b, A.get(H.nu1));
             small_resid<T, true>(P, p, u, b, r);
         } else {
             small_load<T, false>(L, P);
-            small_relax<T, false>(P, p, u, b, H.nu1);
+            small_relax<T, false>(P, p, u, b, A.get(H.nu1));
             small_resid<T, false>(P, p, u, b, r);
         }
         __syncthreads();
-        const int nf = L.n, pf = nf + 2, nc = H.L[l + 1].n, pc = nc + 2;
-        const Wts<T> &C = H.C[l];
-        T *bc = sm + H.off_b[l + 1];
+        const int nf = L.n, pf = nf + 2, nc = A.get(H.L[l + 1].n), pc = nc + 2;
+        const Wts<T> C = A.get(H.C[l]);
+        T *bc = sm + A.get(H.off_b[l + 1]);
         for (int t = threadIdx.x; t < nc * nc; t += blockDim.x) {
             const int I = 1 + t % nc, J = 1 + t / nc;
             const size_t c = (size_t)J * C.ld + I, cn = c + C.ld;
@@ -1686,22 +1700,22 @@ __device__ void small_vcycle_body(const SmallH<T> &H, T *sm, size_t rhs_off)
     }
     // coarsest level: the band LDL^T solve in FP64 by the first wave
     if (threadIdx.x < 64) {
-        const int nc = H.L[last].n, pc = nc + 2;
-        const T *b = sm + H.off_b[last];
-        T *u = sm + H.off_u[last];
+        const int nc = A.get(H.L[last].n), pc = nc + 2;
+        const T *b = sm + A.get(H.off_b[last]);
+        T *u = sm + A.get(H.off_u[last]);
         band_solve_direct(
-            H.band, [&](int k) -> double { return (double)b[(k / nc + 1) * pc + k % nc + 1]; },
+            A.get(H.band), [&](int k) -> double { return (double)b[(k / nc + 1) * pc + k % nc + 1]; },
             [&](int k, double x) { u[(k / nc + 1) * pc + k % nc + 1] = (T)x; },
-            reinterpret_cast<double *>(sm + H.off_z));
+            reinterpret_cast<double *>(sm + A.get(H.off_z)));
     }
     __syncthreads();
     // up: interpolate and correct, relax
     for (int l = last - 1; l >= 0; --l) {
-        const Lev<T> &L = H.L[l];
-        T *u = sm + H.off_u[l], *b = sm + H.off_b[l];
-        const T *ec = sm + H.off_u[l + 1];
-        const int n = L.n, p = n + 2, pc = H.L[l + 1].n + 2;
-        const Wts<T> &C = H.C[l];
+        const Lev<T> L = A.get(H.L[l]);
+        T *u = sm + A.get(H.off_u[l]), *b = sm + A.get(H.off_b[l]);
+        const T *ec = sm + A.get(H.off_u[l + 1]);
+        const int n = L.n, p = n + 2, pc = A.get(H.L[l + 1].n) + 2;
+        const Wts<T> C = A.get(H.C[l]);
         const bool nine = (l > 0) || NINE0;
         // the sweeps' stencil is requested before the interpolation runs
         if (nine) small_load<T, true>(L, P); else small_load<T, false>(L, P);
@@ -1728,13 +1742,13 @@ __device__ void small_vcycle_body(const SmallH<T> &H, T *sm, size_t rhs_off)
             u[j * p + i] = u[j * p + i] + e;
         }
         __syncthreads();
-        if (nine) small_relax<T, true>(P, p, u, b, H.nu2); else small_relax<T, false>(P, p, u, b, H.nu2);
+        if (nine) small_relax<T, true>(P, p, u, b, A.get(H.nu2)); else small_relax<T, false>(P, p, u, b, A.get(H.nu2));
     }
     // the first level's iterate back to global memory
     {
-        const Lev<T> &L = H.L[0];
+        const Lev<T> L = A.get(H.L[0]);
         const int n = L.n, p = n + 2;
-        const T *u = sm + H.off_u[0];
+        const T *u = sm + A.get(H.off_u[0]);
         for (int t = threadIdx.x; t < n * n; t += blockDim.x) {
             const int i = 1 + t % n, j = 1 + t / n;
             L.u[rhs_off + (size_t)j * L.ld + i] = u[j * p + i];
@@ -1748,7 +1762,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_vcycle(SmallH<T> H, con
     const int k = blockIdx.x;
     if (stopped(stop ? stop + k * H.kstop : stop)) return;
     extern __shared__ unsigned char smem_raw[];
-    small_vcycle_body<T, NINE0>(H, reinterpret_cast<T *>(smem_raw), k * H.ks0);
+    small_vcycle_body<T, NINE0>(SmallArg<T>{H}, reinterpret_cast<T *>(smem_raw), k * H.ks0);
 }
 
 }  // namespace bmg

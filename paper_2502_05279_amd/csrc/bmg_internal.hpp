@@ -119,6 +119,7 @@ namespace bmgi {
 // Rows per tile of a fused pass on a level of size n: the handle's option, the
 // autotuned table (bmg_tile_rows_set), else a measured default.
 int tile_rows_for(const bmg_solver *h, int n, bool nine);
+int tuned_tile_rows(int n);   // the table's entry, 0 if unset
 TileGeo tile_geo(int n, int hx, int ht);
 }  // namespace bmgi
 

@@ -1479,6 +1479,18 @@ static __global__ void k_resid_dd_fan(Lev<double> L, const double *__restrict__ 
                               part + (size_t)z * F.kpart, w / F.nrhs, g / F.nrhs);
 }
 
+// (xh, xl) += d: TwoSum, add the low part, renormalise with Dekker's fast
+// TwoSum.
+__device__ __forceinline__ void dd_add_point(double *XH, double *XL, size_t p, double d)
+{
+    double s, e;
+    two_sum(XH[p], d, s, e);
+    e = e + XL[p];
+    const double hi = s + e;
+    XL[p] = e - (hi - s);
+    XH[p] = hi;
+}
+
 // (XH, XL) += d in double-FP64 with d = L.u (FP64 inner cycle) or
 // d = scale * (double)U32 (FP32 inner cycle): TwoSum, add the low part,
 // renormalise with Dekker's fast TwoSum.
@@ -1490,13 +1502,7 @@ __device__ __forceinline__ void dd_update_point(const Lev<double> &L, double *__
     const int j = 1 + blockIdx.y * blockDim.y + threadIdx.y;
     if (i > L.n || j > L.n) return;
     const size_t p = (size_t)j * L.ld + i;
-    const double d = U32 ? scale[0] * (double)U32[p] : L.u[p];
-    double s, e;
-    two_sum(XH[p], d, s, e);
-    e = e + XL[p];
-    const double hi = s + e;
-    XL[p] = e - (hi - s);
-    XH[p] = hi;
+    dd_add_point(XH, XL, p, U32 ? scale[0] * (double)U32[p] : L.u[p]);
 }
 
 static __global__ void k_dd_update(Lev<double> L, double *__restrict__ XH, double *__restrict__ XL,

@@ -36,12 +36,17 @@ bmg_status fail(bmg_status s, const char *fmt, ...)
 // Tile rows chosen by the autotuner, per level size n = 2^m - 1 (0 = unset).
 static int g_tile_rows[17];
 
+int tuned_tile_rows(int n)
+{
+    int m = 0;
+    while ((1 << m) < n + 1 && m < 16) ++m;
+    return g_tile_rows[m];
+}
+
 int tile_rows_for(const bmg_solver *h, int n, bool nine)
 {
     if (h && h->opt.tile_rows > 0) return h->opt.tile_rows;
-    int m = 0;
-    while ((1 << m) < n + 1 && m < 16) ++m;
-    if (g_tile_rows[m] > 0) return g_tile_rows[m];
+    if (tuned_tile_rows(n) > 0) return tuned_tile_rows(n);
     // measured defaults (FP64, V(2,1)): the fewest warm-up rows re-read while
     // the tiles still fill the chip in whole rounds (at 4095^2, 96 rows give
     // 731 tiles, one round of three 48 KiB pre-pass or four 40 KiB post-pass
