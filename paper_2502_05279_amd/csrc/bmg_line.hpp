@@ -285,4 +285,176 @@ static __global__ void k_line_put_x(int n, int ld, int par, const double *__rest
     }
 }
 
+// A half-sweep in one launch on levels of at most LINE_FUSED_N points: a
+// workgroup takes G lines of one parity, every thread computes right-hand
+// sides and fetches the factors into LDS, G lanes of the first wave run the
+// recurrences there, and every thread writes the solutions back.  No line
+// needs a line of its own parity, so u is updated in place.  All arrays are in
+// the grid's frame (X: row c of the grid, Y: column c; k along the line).
+// Bound by the recurrence of one line: two dependent operations per row down,
+// three back, and the LDS reads and writes around them, 33 and 43 clocks per row
+// from one wave; for columns also by fetching a cache line per row and array
+// (6 us of 25 at 511).  An x-line's row is contiguous, so G = 1 spreads a level
+// over the most CUs; columns are taken four at a time, which share a 64-byte
+// segment of each row.  Mean half-sweep, measured against the right-hand
+// sides, solve and (x) transposition in two or three launches: 63^2 5.2 us
+// against 12.5, 255^2 13.1 against 28.4, 511^2 24.6 against 51.1, 1023^2 53
+// against 97.  A line of 2047 points takes 65 KB, two x-lines per CU and fewer
+// columns: 243 us against 203, so larger levels keep the streaming kernels.
+constexpr int LINE_FUSED_N = 1023;
+constexpr int LINE_COLS = 4;     // columns a workgroup takes
+constexpr int LINE_THREADS = 256;
+
+__host__ __device__ inline int line_pitch(int n) { return n + 3; }   // even, and lines 4 banks apart
+__host__ __device__ inline size_t line_lds(int n, int g) { return (size_t)4 * g * line_pitch(n) * sizeof(double); }
+
+template <bool X, bool NINE, int G>
+static __global__ __launch_bounds__(LINE_THREADS) void k_line_sweep(Lev<double> L, int par,
+                                                                    const double *__restrict__ lf,
+                                                                    const double *__restrict__ rf, const int *stop)
+{
+    if (stopped(stop)) return;
+    typedef double v2d __attribute__((ext_vector_type(2)));
+    extern __shared__ double line_sm[];
+    const int n = L.n, P = line_pitch(n), nlines = par ? (n + 1) / 2 : (n - 1) / 2;
+    const size_t ld = L.ld;
+    double *sd = line_sm, *sl = sd + G * P, *sr = sl + G * P, *sc = sr + G * P;
+    const int line0 = blockIdx.x * G;
+    // element k (from 0) of line g, and the zero that pads a line to n + 1 rows
+    auto point = [&](int g, int k) -> size_t {
+        const size_t c = (par ? 1 : 2) + 2 * (line0 + g);
+        return X ? c * ld + (k + 1) : (size_t)(k + 1) * ld + c;
+    };
+    const double *u = L.u;
+    // U points per thread at a time, their loads unconditional (a point past
+    // the end reads the last one's) and so all in flight together
+    constexpr int U = 4;
+    const int total = G * (n + 1);
+    for (int t0 = threadIdx.x; t0 < total; t0 += U * LINE_THREADS) {
+        double d[U], l[U], r[U], c[U];
+#pragma unroll
+        for (int e = 0; e < U; ++e) {
+            const int t = t0 + e * LINE_THREADS, g = t % G, k = t / G;
+            const size_t p = point(line0 + g < nlines ? g : 0, k < n ? k : n - 1);
+            l[e] = lf[p];
+            r[e] = rf[p];
+            double s = L.b[p];
+            if (X) {
+                c[e] = L.W[p + 1];
+                if (NINE) s -= L.SW[p] * u[p - ld - 1];
+                s -= L.S[p] * u[p - ld];
+                if (NINE) s -= L.NW[p + 1 - ld] * u[p - ld + 1];   // A_SE
+                if (NINE) s -= L.NW[p] * u[p + ld - 1];
+                s -= L.S[p + ld] * u[p + ld];                      // A_N
+                if (NINE) s -= L.SW[p + ld + 1] * u[p + ld + 1];   // A_NE
+            } else {
+                c[e] = L.S[p + ld];
+                if (NINE) s -= L.SW[p] * u[p - ld - 1];
+                s -= L.W[p] * u[p - 1];
+                if (NINE) s -= L.NW[p] * u[p + ld - 1];
+                if (NINE) s -= L.NW[p + 1 - ld] * u[p - ld + 1];   // A_SE
+                s -= L.W[p + 1] * u[p + 1];                        // A_E
+                if (NINE) s -= L.SW[p + ld + 1] * u[p + ld + 1];   // A_NE
+            }
+            d[e] = s;
+        }
+#pragma unroll
+        for (int e = 0; e < U; ++e) {
+            const int t = t0 + e * LINE_THREADS, g = t % G, k = t / G, q = g * P + k;
+            if (t >= total) continue;
+            const bool ok = k < n;
+            sd[q] = ok ? d[e] : 0.0;
+            sl[q] = ok ? l[e] : 0.0;
+            sr[q] = ok ? r[e] : 0.0;
+            sc[q] = ok ? c[e] : 0.0;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < G) {
+        // n + 1 rows, a power of two: pairs, R of them per round, the next
+        // round's reads ahead of this one's arithmetic.  l of the first row,
+        // c of the last and the padding row are zero, so the recurrences need
+        // no ends of their own: y_1 = d_1 - 0, x_n = (y_n - 0) r_n.
+        v2d *D = reinterpret_cast<v2d *>(sd + threadIdx.x * P);
+        const v2d *Lw = reinterpret_cast<const v2d *>(sl + threadIdx.x * P);
+        const v2d *Rw = reinterpret_cast<const v2d *>(sr + threadIdx.x * P);
+        const v2d *Cw = reinterpret_cast<const v2d *>(sc + threadIdx.x * P);
+        constexpr int R = 8;
+        const int np = (n + 1) >> 1;
+        double y = 0.0;
+        if (np >= 2 * R) {
+            // two sets of registers in turn (a copy between them would cost as
+            // much as the arithmetic); the reads past the last round repeat it.
+            // (Putting the next set's reads between the operations of the
+            // recurrence was slower: 38 and 52 clocks per row down and back
+            // against 33 and 43.)
+            struct Rows { v2d d[R], a[R], b[R]; } A, B;
+            auto fread = [&](Rows &r, int s) {
+#pragma unroll
+                for (int q = 0; q < R; ++q) { r.d[q] = D[s + q]; r.a[q] = Lw[s + q]; }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto fwork = [&](const Rows &r, int s) {
+#pragma unroll
+                for (int q = 0; q < R; ++q) {
+                    v2d v;
+                    v.x = r.d[q].x - r.a[q].x * y;
+                    v.y = y = r.d[q].y - r.a[q].y * v.x;
+                    D[s + q] = v;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            fread(A, 0);
+            for (int s = 0; s < np; s += 2 * R) {
+                fread(B, s + R);
+                fwork(A, s);
+                fread(A, min(s + 2 * R, np - R));
+                fwork(B, s + R);
+            }
+            double x = 0.0;
+            auto bread = [&](Rows &r, int s) {
+#pragma unroll
+                for (int q = 0; q < R; ++q) { r.d[q] = D[s - q]; r.a[q] = Rw[s - q]; r.b[q] = Cw[s - q]; }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto bwork = [&](const Rows &r, int s) {
+#pragma unroll
+                for (int q = 0; q < R; ++q) {
+                    v2d v;
+                    v.y = (r.d[q].y - r.b[q].y * x) * r.a[q].y;
+                    v.x = x = (r.d[q].x - r.b[q].x * v.y) * r.a[q].x;
+                    D[s - q] = v;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            bread(A, np - 1);
+            for (int s = np - 1; s >= 0; s -= 2 * R) {
+                bread(B, s - R);
+                bwork(A, s);
+                bread(A, max(s - 2 * R, R - 1));
+                bwork(B, s - R);
+            }
+        } else {
+            for (int s = 0; s < np; ++s) {
+                v2d v = D[s];
+                v.x = v.x - Lw[s].x * y;
+                v.y = y = v.y - Lw[s].y * v.x;
+                D[s] = v;
+            }
+            double x = 0.0;
+            for (int s = np - 1; s >= 0; --s) {
+                v2d v = D[s];
+                v.y = (v.y - Cw[s].y * x) * Rw[s].y;
+                v.x = x = (v.x - Cw[s].x * v.y) * Rw[s].x;
+                D[s] = v;
+            }
+        }
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < G * n; t += LINE_THREADS) {
+        const int g = t % G, k = t / G;
+        if (line0 + g < nlines) L.u[point(g, k)] = sd[g * P + k];
+    }
+}
+
 }  // namespace bmg

@@ -305,6 +305,21 @@ static inline double stencil_planes(bool nine) { return nine ? 5.0 : 3.0; }
 // -------------------------------------------------------- cycle steps
 const dim3 B2(64, 4);
 
+// Half-sweep of the lines of parity par of level l in one launch.
+template <bool X, int G>
+bmg_status line_half(bmg_solver *h, const Lev<double> &L, bool nine, int par, const int *stop, int l)
+{
+    const int nl = par ? (L.n + 1) / 2 : (L.n - 1) / 2;
+    const dim3 grid((nl + G - 1) / G), blk(LINE_THREADS);
+    const size_t lds = line_lds(L.n, G);
+    const void *f = nine ? (const void *)k_line_sweep<X, true, G> : (const void *)k_line_sweep<X, false, G>;
+    if (lds > 64 * 1024) HIPCHK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    const double *lf = X ? h->lfx[l] : h->lfy[l], *rf = X ? h->rfx[l] : h->rfy[l];
+    if (nine) hipLaunchKernelGGL((k_line_sweep<X, true, G>), grid, blk, lds, h->st, L, par, lf, rf, stop);
+    else hipLaunchKernelGGL((k_line_sweep<X, false, G>), grid, blk, lds, h->st, L, par, lf, rf, stop);
+    return BMG_OK;
+}
+
 // `sweeps` alternating zebra line relaxations of level l (FP64).
 bmg_status line_smooth(bmg_solver *h, const Lev<double> &L, bool nine, int sweeps, const int *stop, int l)
 {
@@ -317,6 +332,10 @@ bmg_status line_smooth(bmg_solver *h, const Lev<double> &L, bool nine, int sweep
     for (int s = 0; s < sweeps; ++s) {
         for (int par = 1; par >= 0; --par) {   // x-lines: odd rows, then even
             const int nl = par ? (n + 1) / 2 : (n - 1) / 2;
+            if (n <= LINE_FUSED_N) {
+                TRY((line_half<true, 1>(h, L, nine, par, stop, l)));
+                continue;
+            }
             if (nine) hipLaunchKernelGGL((k_line_rhs_x<true>), tg, tb, 0, h->st, L, par, D, stop);
             else hipLaunchKernelGGL((k_line_rhs_x<false>), tg, tb, 0, h->st, L, par, D, stop);
             hipLaunchKernelGGL(k_line_solve, dim3((nl + LINE_G - 1) / LINE_G), dim3(64), 0, h->st, n, ld, par, D,
@@ -326,6 +345,10 @@ bmg_status line_smooth(bmg_solver *h, const Lev<double> &L, bool nine, int sweep
         }
         for (int par = 1; par >= 0; --par) {   // y-lines: odd columns, then even
             const int nl = par ? (n + 1) / 2 : (n - 1) / 2;
+            if (n <= LINE_FUSED_N) {
+                TRY((line_half<false, LINE_COLS>(h, L, nine, par, stop, l)));
+                continue;
+            }
             const dim3 rb(64, 4), rg((nl + 63) / 64, (n + 3) / 4);
             if (nine) hipLaunchKernelGGL((k_line_rhs_y<true>), rg, rb, 0, h->st, L, par, D, stop);
             else hipLaunchKernelGGL((k_line_rhs_y<false>), rg, rb, 0, h->st, L, par, D, stop);
@@ -988,6 +1011,16 @@ static bmg_status setup_into(bmg_solver *h, const double *stencil, int n, int ki
             hipLaunchKernelGGL(k_transpose, tg, tb, 0, h->st, L.n, L.ld, (const double *)L.W, h->WT[l]);
             hipLaunchKernelGGL(k_line_factor, fg, fb, 0, h->st, L.n, L.ld, (const double *)h->lineD,
                                (const double *)h->WT[l], h->lfx[l], h->rfx[l], h->flags);
+            if (L.n <= LINE_FUSED_N) {
+                // the fused half-sweeps read the x-lines' factors in the
+                // grid's frame: l into the plane of the transposed W, r into l's
+                hipLaunchKernelGGL(k_transpose, tg, tb, 0, h->st, L.n, L.ld, (const double *)h->lfx[l], h->WT[l]);
+                hipLaunchKernelGGL(k_transpose, tg, tb, 0, h->st, L.n, L.ld, (const double *)h->rfx[l], h->lfx[l]);
+                double *const l_plane = h->WT[l], *const r_plane = h->lfx[l];
+                h->WT[l] = h->rfx[l];   // not read on this level
+                h->lfx[l] = l_plane;
+                h->rfx[l] = r_plane;
+            }
         }
     }
     if (h->f32) {
