@@ -97,9 +97,10 @@ typedef struct {
                         one-workgroup launch per cycle: 2^k - 1 <= 63, or 1 for
                         none; 0 = 63 */
     int square_tiles_below_n; /* nine-point levels of at most this many points
-                        per side run their fused pre and post passes with one
-                        workgroup per 32 x 32 square tile, every sweep of the
-                        pass inside the tile's LDS copy (one right-hand side):
+                        per side run their fused pre pass with one workgroup
+                        per 32 x 32 square tile, every sweep of the pass inside
+                        the tile's LDS copy (one right-hand side; larger levels
+                        and the post passes stream strips of columns):
                         2^k - 1, or 1 for none; 0 = 511 */
     int graph_mode;  /* 1: bmg_solve's plain FP64 cycles on the fused fine-level
                         schedule run as replays of a HIP graph of two cycles,

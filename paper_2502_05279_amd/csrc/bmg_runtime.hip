@@ -108,7 +108,7 @@ double ms_since(std::chrono::steady_clock::time_point t0)
     return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
 }
 int persistent_of(const bmg_options &o) { return o.persistent_below_n > 0 ? o.persistent_below_n : SMALL_MAX_N; }
-// Fused passes of level l in square tiles (k_pre2d, k_post2d)?
+// Fused pre pass of level l in square tiles (k_pre2d)?
 static bool square_tiles(const bmg_solver *h, int l)
 {
     const int lim = h->opt.square_tiles_below_n > 0 ? h->opt.square_tiles_below_n : T2D_MAX_N;
@@ -510,10 +510,38 @@ static bool pre_weights_in_pass(const bmg_solver *h, int l, bool nine)
 #define BMG_FIVE_POINT_STEP_ROWS 2
 #endif
 
+// Tiles of a wave-stream pass on level l of every right-hand side.  An FP64
+// pre pass takes more than 256 registers, one wave per SIMD: the height is the
+// least that leaves all tiles in one round of 1024.  Half-height tiles (a
+// round of 2048, which FP32 and the post passes could hold) re-read more rows
+// for no more speed: 2047^2 pre 138 against 132 us, post 134 against 121.
+constexpr int WAVE_SLOTS = 1024;
+TileGeo wave_tiles(const bmg_solver *h, int l, int hx)
+{
+    const int n = h->L[l].n, useful = WAVE_COLS - 2 * hx, strips = (n + useful) / useful;
+    int rows = h->opt.tile_rows > 0 ? h->opt.tile_rows : tuned_tile_rows(n);
+    if (rows <= 0) {
+        const int blocks = std::max(1, WAVE_SLOTS / (strips * h->nrhs));
+        rows = std::max(2, ((n + blocks - 1) / blocks + 1) & ~1);
+    }
+    TileGeo g;
+    g.hx = hx;
+    g.ht = std::max(2, std::min(rows, (n + 2) & ~1));
+    g.tiles_x = strips;
+    g.ntiles = strips * ((n + g.ht - 1) / g.ht);
+    g.nrhs = h->nrhs;
+    g.kstop = h->kstop;
+    g.kpart = h->kpart;
+    g.ksf = h->ks[l];
+    g.ksc = l + 1 < h->nlev ? h->ks[l + 1] : 0;
+    return g;
+}
+
 // nu sweeps, residual and restriction in one pass (results as SMOOTH,
 // RESIDUAL, RESTRICT in turn); the level's iterate moves to the other buffer.
+// zero_u: the iterate is known to be zero.
 template <typename T>
-bmg_status fused_pre(bmg_solver *h, int l, int nu, const int *stop)
+bmg_status fused_pre(bmg_solver *h, int l, int nu, const int *stop, bool zero_u = false)
 {
     Lev<T> &F = levm<T>(h, l);
     const Lev<T> &Cl = lev<T>(h, l + 1);
@@ -539,6 +567,9 @@ bmg_status fused_pre(bmg_solver *h, int l, int nu, const int *stop)
     // more time than the loads they replace.
     const bool wrec = pre_weights_in_pass<T>(h, l, nine);
     // small nine-point levels: every sweep inside one square tile's LDS copy
+    // (511^2: 23 us against 26 as waves, whose few rows per tile start with a
+    // window of rows each; the post pass, with a shorter one, is faster as
+    // waves there too, 17 us against 20)
     const bool sq = square_tiles(h, l) && nu <= 2;
     // stencil once and b, u read, u written for each right-hand side on the
     // fine level; b and u (zero) written for each on the coarse level, and the
@@ -547,7 +578,15 @@ bmg_status fused_pre(bmg_solver *h, int l, int nu, const int *stop)
     trace_begin(h, BMG_TRACE_PRE, l,
                 sizeof(T) * ((stencil_planes(nine) + 3.0 * K) * (double)F.n * F.n +
                              (2.0 * K + (wrec ? 0.0 : 8.0)) * (double)Cl.n * Cl.n));
-    if (sq) {
+    if (nine && nu <= 2 && !sq) {
+        const TileGeo gw = wave_tiles(h, l, 4 * nu + 2);
+        const dim3 wg = tile_grid(gw), wb(64);
+#define PREWAVE(NU) \
+    if (zero_u) hipLaunchKernelGGL((k_pre_wave<T, NU, true>), wg, wb, 0, h->st, F, out, C, Cl, gw, stop); \
+    else hipLaunchKernelGGL((k_pre_wave<T, NU, false>), wg, wb, 0, h->st, F, out, C, Cl, gw, stop)
+        if (nu == 1) { PREWAVE(1); } else { PREWAVE(2); }
+#undef PREWAVE
+    } else if (sq) {
         const dim3 g2((F.n + T2D - 1) / T2D, (F.n + T2D - 1) / T2D);
         if (nu == 1)
             hipLaunchKernelGGL((k_pre2d<T, 1>), g2, dim3(T2D_THREADS), 0, h->st, F, out, C, Cl, stop);
@@ -558,7 +597,7 @@ bmg_status fused_pre(bmg_solver *h, int l, int nu, const int *stop)
             if (nu == 1) PREW(false, 1); else if (nu == 2) PREW(false, 2); else PREW(false, 3);
         }
     } else if (nine) {
-        if (nu == 1) PRE(true, 1); else if (nu == 2) PRE(true, 2); else PRE(true, 3);
+        PRE(true, 3);   // (one and two sweeps run as waves, above)
     } else if (BMG_FIVE_POINT_STEP_ROWS == 4) {
         if (nu == 1) PRE4(1); else if (nu == 2) PRE4(2); else PRE4(3);
     } else {
@@ -592,9 +631,6 @@ bmg_status fused_post(bmg_solver *h, int l, int nu, const int *stop, bool norm =
     // each sweep invalidates 2 (five-point) or 4 (nine-point) more columns and
     // the fused residual one more
     const TileGeo g = level_tiles(h, l, nine ? 4 * nu + 2 : 2 * nu + 2);
-    // small nine-point levels without the norm: every sweep inside one square
-    // tile's LDS copy
-    const bool sq = !norm && square_tiles(h, l);
     norm = norm && std::is_same<T, double>::value && g.ntiles <= NPART;
     T *out = ualt<T>(h, l);
     const dim3 grid = tile_grid(g), blk(FW);
@@ -607,12 +643,13 @@ bmg_status fused_post(bmg_solver *h, int l, int nu, const int *stop, bool norm =
     const double K = h->nrhs;
     trace_begin(h, BMG_TRACE_POST, l,
                 sizeof(T) * ((stencil_planes(nine) + 3.0 * K) * (double)F.n * F.n + (K + 8.0) * (double)Cl.n * Cl.n));
-    if (sq) {
-        const dim3 g2((F.n + T2D - 1) / T2D, (F.n + T2D - 1) / T2D);
+    if (nine && !norm) {
+        const TileGeo gw = wave_tiles(h, l, 4 * nu + 2);
+        const dim3 wg = tile_grid(gw), wb(64);
         if (nu == 1)
-            hipLaunchKernelGGL((k_post2d<T, 1>), g2, dim3(T2D_THREADS), 0, h->st, F, out, C, (const T *)Cl.u, stop);
+            hipLaunchKernelGGL((k_post_wave<T, 1>), wg, wb, 0, h->st, F, out, C, (const T *)Cl.u, gw, stop);
         else
-            hipLaunchKernelGGL((k_post2d<T, 2>), g2, dim3(T2D_THREADS), 0, h->st, F, out, C, (const T *)Cl.u, stop);
+            hipLaunchKernelGGL((k_post_wave<T, 2>), wg, wb, 0, h->st, F, out, C, (const T *)Cl.u, gw, stop);
     } else if (!nine && BMG_FIVE_POINT_STEP_ROWS == 4) {
         if (norm) { if (nu == 1) POST4(1, true); else POST4(2, true); }
         else { if (nu == 1) POST4(1, false); else POST4(2, false); }
@@ -620,8 +657,7 @@ bmg_status fused_post(bmg_solver *h, int l, int nu, const int *stop, bool norm =
         if (nine) { if (nu == 1) POST(true, 1, true); else POST(true, 2, true); }
         else { if (nu == 1) POST(false, 1, true); else POST(false, 2, true); }
     } else {
-        if (nine) { if (nu == 1) POST(true, 1, false); else POST(true, 2, false); }
-        else { if (nu == 1) POST(false, 1, false); else POST(false, 2, false); }
+        if (nu == 1) POST(false, 1, false); else POST(false, 2, false);
     }
     trace_end(h, BMG_TRACE_POST, l);
 #undef POST
@@ -674,7 +710,7 @@ bmg_status fused_cycle_from(bmg_solver *h, int l, const int *stop, bool norm)
 {
     if (l == h->nlev - 1) return coarse<T>(h, lev<T>(h, l), stop);
     if (l >= 1 && lev<T>(h, l).n <= persistent_of(h->opt)) return small_cycle<T>(h, l, stop);
-    TRY(fused_pre<T>(h, l, h->opt.nu1, stop));
+    TRY(fused_pre<T>(h, l, h->opt.nu1, stop, l >= 1));   // below the fine level a cycle starts from zero
     TRY(fused_cycle_from<T>(h, l + 1, stop, false));
     return fused_post<T>(h, l, h->opt.nu2, stop, norm && l == 0);
 }

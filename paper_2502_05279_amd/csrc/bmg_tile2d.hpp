@@ -1,4 +1,4 @@
-// Passes of the small nine-point levels in square tiles: one workgroup loads a
+// Pre pass of the small nine-point levels in square tiles: one workgroup loads a
 // tile of the level with its halo into LDS at once (u and b; each thread keeps
 // the nine stencil entries of its points in registers), runs every colour
 // phase of the sweeps there with a workgroup barrier between phases, and
@@ -8,9 +8,9 @@
 // The halo makes every owned output exact: the outermost ring of the tile is
 // never updated and each colour phase can carry its staleness one point
 // inward, so nu sweeps (4 nu phases) plus the residual and the restriction
-// need 4 nu + 2 points (the post pass, without residual, 4 nu).  Every point's
-// expressions are those of gs_point, residual_point, interp_point and
-// k_restrict, so the results are those of the separate kernels to the bit.
+// need 4 nu + 2 points.  Every point's expressions are those of gs_point,
+// residual_point and k_restrict, so the results are those of the separate
+// kernels to the bit.
 #pragma once
 
 #include "bmg_kernels.hpp"
@@ -157,33 +157,6 @@ __global__ __launch_bounds__(T2D_THREADS) void k_pre2d(Lev<T> L, T *__restrict__
             Cl.b[c] = s;
             Cl.u[c] = (T)0;
         }
-    }
-}
-
-// Post pass: u += P e_c on the tile, NU sweeps, u of the owned points to uout.
-template <typename T, int NU>
-__global__ __launch_bounds__(T2D_THREADS) void k_post2d(Lev<T> L, T *__restrict__ uout, Wts<T> C,
-                                                       const T *__restrict__ ec, const int *stop)
-{
-    if (stopped(stop)) return;
-    constexpr int HALO = 4 * NU, S = t2d_side(HALO);
-    __shared__ T su[S * S], sb[S * S];
-    const int x0 = 1 + T2D * blockIdx.x, y0 = 1 + T2D * blockIdx.y;
-    T2dPts<T, HALO> P;
-    t2d_load<T, HALO>(L, x0, y0, su, sb, P);
-#pragma unroll
-    for (int s = 0; s < T2dPts<T, HALO>::SL; ++s) {
-        const int k = threadIdx.x + s * T2D_THREADS, gi = P.gi[s], gj = P.gj[s];
-        if (k < S * S && gi >= 1 && gi <= L.n && gj >= 1 && gj <= L.n) su[k] = su[k] + interp_point<T>(C, ec, gi, gj);
-    }
-    __syncthreads();
-    t2d_sweeps<T, HALO, NU>(L, su, sb, P);
-#pragma unroll
-    for (int s = 0; s < T2dPts<T, HALO>::SL; ++s) {
-        const int k = threadIdx.x + s * T2D_THREADS;
-        const int li = k % S, lj = k / S, gi = P.gi[s], gj = P.gj[s];
-        if (k < S * S && li >= HALO && li < HALO + T2D && lj >= HALO && lj < HALO + T2D && gi <= L.n && gj <= L.n)
-            uout[(size_t)gj * L.ld + gi] = su[k];
     }
 }
 

@@ -1,0 +1,517 @@
+// Fused passes of the nine-point levels as streams of single waves.
+//
+// A wave owns a strip of 128 grid columns, two neighbours (even, odd) per lane,
+// and a block of rows, and streams upward through it two rows at a time like
+// the workgroups of bmg_fused.hpp: the same row pipeline, warm-up rows, halo
+// columns and expressions, so the same results to the bit.  What differs is
+// where the values live.  The iterate, the right-hand side and the couplings
+// read in their own column (O, S) stay in registers, in a ring of rows whose
+// slots are compile-time constants (the step loop is unrolled over one turn of
+// the ring, so nothing shifts); a neighbour in the other lane comes by a
+// one-lane wave shift; W, SW and NW, read at the next column too, sit in an LDS
+// ring that only this wave touches.  So no phase waits at a barrier, no value
+// of the iterate goes through LDS, and every lane has a point to update in
+// every colour phase (with one column per lane half of them idle).
+//
+// Measured in a 4095^2 solve (FP64, V(2,1)): 2047^2 pre 142 -> 81 us, post
+// 97 -> 71, 1023^2 66 -> 32 and 34 -> 25.  The 2047^2 passes are bound by
+// memory: 443 MB for the pre pass, 4.9 TB/s, while both neighbours of a tile
+// streamed the same way (91 us); streaming every other row of tiles downward
+// lets two tiles share the rows at their border.
+//
+// The ring holds two rows more than a step's window: the rows of the next step
+// are requested straight into their slots while this step computes.  Points
+// on the grid's ring, and beyond it, carry zero couplings, b = 0 and O = 1, so
+// that the update leaves them at zero without a test.
+#pragma once
+
+#include "bmg_fused.hpp"
+
+namespace bmg {
+
+constexpr int WAVE_COLS = 128;
+
+// Value of the lane to the west (lane 0: zero) or east (lane 63: zero).
+template <int CTRL>
+__device__ __forceinline__ float lane_shift(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double lane_shift(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+template <typename T>
+__device__ __forceinline__ T from_west(T v) { return lane_shift<0x138>(v); }   // wave_shr:1
+template <typename T>
+__device__ __forceinline__ T from_east(T v) { return lane_shift<0x130>(v); }   // wave_shl:1
+
+// Orders this wave's LDS accesses (its lanes read what their neighbours wrote;
+// to the compiler those are unrelated addresses).  No instruction.
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+template <typename T>
+struct Pair {
+    typedef T vec __attribute__((ext_vector_type(2)));
+};
+
+// LDS ring of a wave: W, SW, NW, RX rows of 128 columns (and one element that
+// the last lane's read of "the next column" may touch).
+template <typename T, int NU>
+struct WaveLds {
+    static constexpr int RX = 2 * NU + 6;
+    T W[RX * WAVE_COLS], SW[RX * WAVE_COLS], NW[RX * WAVE_COLS + 2];
+};
+
+// What both passes share: geometry, the ring and the point update.  A tile is
+// streamed upward (DIR = 1) or downward (DIR = -1): the colours' order, even
+// rows before odd ones, is the same seen from either side.  Slot of row
+// e + DIR d at turn M of the unrolled loop (e = es + 2 M DIR mod RX).
+template <typename T, int NU, int DIR>
+struct WaveTile {
+    static constexpr int RX = 2 * NU + 6;
+    using V = typename Pair<T>::vec;
+    template <int M>
+    static constexpr int at(int d) { return ((2 * M + d) % RX + RX) % RX; }
+
+    T u[RX][2], b[RX][2], O[RX][2], S[RX][2];
+    T *sW, *sSW, *sNW;         // this lane's pair in ring row 0
+    int n, ld, i0, i0c, y0, y1;
+    bool in0, in1, own;        // columns interior, pair owned
+
+    __device__ __forceinline__ void place(const Lev<T> &L, const TileGeo &G, int tid, WaveLds<T, NU> &lds)
+    {
+        n = L.n;
+        ld = L.ld;
+        const int lane = threadIdx.x, useful = WAVE_COLS - 2 * G.hx;
+        const int tx = tid % G.tiles_x, ty = tid / G.tiles_x;
+        const int xo = tx * useful;                 // first owned column (0: the ring)
+        i0 = xo - G.hx + 2 * lane;
+        i0c = i0 >= 0 && i0 <= n + 1 ? i0 : n + 1;   // beyond the grid: the ring and the zeros past it
+        in0 = i0 >= 1 && i0 <= n;
+        in1 = i0 + 1 >= 1 && i0 + 1 <= n;
+        own = i0 >= xo && i0 < xo + useful && i0 < n;
+        y0 = 1 + ty * G.ht;
+        y1 = min(y0 + G.ht, n + 1);
+        sW = lds.W + 2 * lane;
+        sSW = lds.SW + 2 * lane;
+        sNW = lds.NW + 2 * lane;
+    }
+    __device__ __forceinline__ int rowc(int row) const { return row >= 0 && row <= n + 1 ? row : n + 1; }
+    __device__ __forceinline__ V load(const T *a, int row) const
+    {
+        return *reinterpret_cast<const V *>(a + (size_t)rowc(row) * ld + i0c);
+    }
+    template <int SL>
+    __device__ __forceinline__ void put_couplings(V w, V sw, V nw)
+    {
+        *reinterpret_cast<V *>(sW + SL * WAVE_COLS) = w;
+        *reinterpret_cast<V *>(sSW + SL * WAVE_COLS) = sw;
+        *reinterpret_cast<V *>(sNW + SL * WAVE_COLS) = nw;
+    }
+    // b, O, S of a row into its slot
+    template <int SL>
+    __device__ __forceinline__ void request(const Lev<T> &L, int row)
+    {
+        const V vb = load(L.b, row), vo = load(L.O, row), vs = load(L.S, row);
+        b[SL][0] = vb.x; b[SL][1] = vb.y;
+        O[SL][0] = vo.x; O[SL][1] = vo.y;
+        S[SL][0] = vs.x; S[SL][1] = vs.y;
+    }
+    // a row that has arrived: O = 1 where there is no equation
+    template <int SL>
+    __device__ __forceinline__ void arrived(int row)
+    {
+        const bool ok = row >= 1 && row <= n;
+        O[SL][0] = ok && in0 ? O[SL][0] : (T)1;
+        O[SL][1] = ok && in1 ? O[SL][1] : (T)1;
+    }
+    // b minus the couplings at column C of the row in slot S0 (SD below, SU
+    // above), in the order of gs_lds
+    template <int C, int SD, int S0, int SU>
+    __device__ __forceinline__ T offdiag() const
+    {
+        const T uwd = C ? u[SD][0] : from_west(u[SD][1]), ued = C ? from_east(u[SD][0]) : u[SD][1];
+        const T uw0 = C ? u[S0][0] : from_west(u[S0][1]), ue0 = C ? from_east(u[S0][0]) : u[S0][1];
+        const T uwu = C ? u[SU][0] : from_west(u[SU][1]), ueu = C ? from_east(u[SU][0]) : u[SU][1];
+        T s = b[S0][C];
+        s -= sSW[S0 * WAVE_COLS + C] * uwd;
+        s -= S[S0][C] * u[SD][C];
+        s -= sNW[SD * WAVE_COLS + C + 1] * ued;
+        s -= sW[S0 * WAVE_COLS + C] * uw0;
+        s -= sW[S0 * WAVE_COLS + C + 1] * ue0;
+        s -= sNW[S0 * WAVE_COLS + C] * uwu;
+        s -= S[SU][C] * u[SU][C];
+        s -= sSW[SU * WAVE_COLS + C + 1] * ueu;
+        return s;
+    }
+    template <int M, int D, int C>
+    __device__ __forceinline__ void relax()
+    {
+        constexpr int SD = at<M>(D - DIR), S0 = at<M>(D), SU = at<M>(D + DIR);
+        u[S0][C] = offdiag<C, SD, S0, SU>() / O[S0][C];
+    }
+    template <int M, int D, int C>
+    __device__ __forceinline__ T resid() const
+    {
+        constexpr int SD = at<M>(D - DIR), S0 = at<M>(D), SU = at<M>(D + DIR);
+        T s = offdiag<C, SD, S0, SU>();
+        s -= O[S0][C] * u[S0][C];
+        return s;
+    }
+    // sweep s of the step: colours 0, 1 on the even row 2s behind e, then 2, 3
+    // on the odd row behind that
+    template <int M, int SW_ = 0>
+    __device__ __forceinline__ void sweeps()
+    {
+        if constexpr (SW_ < NU) {
+            relax<M, -2 * SW_, 0>();
+            relax<M, -2 * SW_, 1>();
+            relax<M, -2 * SW_ - 1, 0>();
+            relax<M, -2 * SW_ - 1, 1>();
+            sweeps<M, SW_ + 1>();
+        }
+    }
+    // the last sweep's two rows are final: the owned ones go out
+    template <int M>
+    __device__ __forceinline__ void write(T *out, int e) const
+    {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int row = e + DIR * (2 - 2 * NU - t);
+            if (row < y0 || row >= y1 || !own) continue;
+            T *p = out + (size_t)row * ld + i0;
+            const T *v = u[at<M>(2 - 2 * NU - t)];
+            if (i0 > 0) *reinterpret_cast<V *>(p) = V{v[0], v[1]};
+            else p[1] = v[1];
+        }
+    }
+};
+
+// Tiles of odd rows of tiles stream downward, so that two tiles that share a
+// border are there at the same time, both at their start or both at their end,
+// and the warm-up rows of one are fetched while the other's L2 still has them.
+__device__ __forceinline__ bool wave_up(const TileGeo &G, int tid) { return !((tid / G.tiles_x) & 1); }
+
+// nu sweeps, residual and restriction (results as pre_tile).  zero_u: the
+// iterate is known to be zero (a coarse level's first visit in a cycle).
+template <typename T, int NU, int DIR>
+struct WavePre : WaveTile<T, NU, DIR> {
+    using B = WaveTile<T, NU, DIR>;
+    using V = typename B::V;
+    static constexpr int RX = B::RX;
+    T pr0[2], pr1[2];          // residual of the coarse row's f and of the odd row behind it
+    T w[8];                    // restriction weights of the next step's coarse row
+    bool rest;
+    int I, nc;
+
+    __device__ __forceinline__ void run(const Lev<T> &L, T *__restrict__ uout, const Wts<T> &Cw, const Lev<T> &Cl,
+                                        const TileGeo &G, int tid, WaveLds<T, NU> &lds, bool zero_u)
+    {
+        B::place(L, G, tid, lds);
+        nc = Cl.n;
+        I = this->i0 >> 1;
+        rest = this->own && I >= 1 && I <= nc;
+        const int y0 = this->y0, y1 = this->y1;
+        // warm-up rows before the owned ones as in pre_tile; the last step
+        // restricts the last owned coarse row
+        const int es = DIR > 0 ? (y0 - 2 * NU) & ~1 : (y1 + 2 * NU) & ~1;
+        const int elast = DIR > 0 ? 2 * ((y1 - 1) >> 1) + 2 * NU + 2 : 2 * ((y0 + 1) >> 1) - 2 * NU - 2;
+        // the rows behind es, and the request of es and the next
+        fill<-2 * NU - 2>(L, es, zero_u);
+        V w0 = B::load(L.W, es), w1 = B::load(L.W, es + DIR), a0 = B::load(L.SW, es), a1 = B::load(L.SW, es + DIR);
+        V c0 = B::load(L.NW, es), c1 = B::load(L.NW, es + DIR);
+        want<0>(L, es, zero_u);
+        weights(Cw, (es - DIR * (2 * NU + 2)) >> 1);
+        pr0[0] = pr0[1] = pr1[0] = pr1[1] = (T)0;
+        for (int e = es; DIR * (elast - e) >= 0; e += DIR * RX)
+            turn<0>(L, uout, Cw, Cl, e, elast, zero_u, w0, w1, a0, a1, c0, c1);
+    }
+
+private:
+    template <int D>
+    __device__ __forceinline__ void fill(const Lev<T> &L, int es, bool zero_u)
+    {
+        if constexpr (D < 0) {
+            constexpr int SL = B::template at<0>(D);
+            const int row = es + DIR * D;
+            const V vu = zero_u ? V{(T)0, (T)0} : B::load(L.u, row);
+            this->u[SL][0] = vu.x;
+            this->u[SL][1] = vu.y;
+            B::template request<SL>(L, row);
+            B::template put_couplings<SL>(B::load(L.W, row), B::load(L.SW, row), B::load(L.NW, row));
+            B::template arrived<SL>(row);
+            fill<D + 1>(L, es, zero_u);
+        }
+    }
+    // request turn M's two rows into their slots
+    template <int M>
+    __device__ __forceinline__ void want(const Lev<T> &L, int e, bool zero_u)
+    {
+        constexpr int S0 = B::template at<M>(0), S1 = B::template at<M>(1);
+        const V u0 = zero_u ? V{(T)0, (T)0} : B::load(L.u, e), u1 = zero_u ? V{(T)0, (T)0} : B::load(L.u, e + DIR);
+        this->u[S0][0] = u0.x; this->u[S0][1] = u0.y;
+        this->u[S1][0] = u1.x; this->u[S1][1] = u1.y;
+        B::template request<S0>(L, e);
+        B::template request<S1>(L, e + DIR);
+    }
+    __device__ __forceinline__ void weights(const Wts<T> &C, int J)
+    {
+        const bool ok = J >= 1 && J <= nc;
+        const size_t c = (size_t)(ok ? J : 1) * C.ld + (rest ? I : 1), cn = c + C.ld;
+        w[0] = C.at(LNE, c);
+        w[1] = C.at(LA, c);
+        w[2] = C.at(LNW, c + 1);
+        w[3] = C.at(LR, c);
+        w[4] = C.at(LL, c + 1);
+        w[5] = C.at(LSE, cn);
+        w[6] = C.at(LB, cn);
+        w[7] = C.at(LSW, cn + 1);
+    }
+    template <int M>
+    __device__ __forceinline__ void turn(const Lev<T> &L, T *__restrict__ uout, const Wts<T> &Cw, const Lev<T> &Cl,
+                                         int e, int elast, bool zero_u, V &w0, V &w1, V &a0, V &a1, V &c0, V &c1)
+    {
+        if constexpr (M < RX / 2) {
+            if (DIR * (e - elast) > 0) return;
+            constexpr int S0 = B::template at<M>(0), S1 = B::template at<M>(1);
+            wave_lds_order();
+            B::template put_couplings<S0>(w0, a0, c0);
+            B::template put_couplings<S1>(w1, a1, c1);
+            wave_lds_order();
+            B::template arrived<S0>(e);
+            B::template arrived<S1>(e + DIR);
+            T wc[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) wc[q] = w[q];
+            // the next step's data
+            const int en2 = e + 2 * DIR;
+            w0 = B::load(L.W, en2); w1 = B::load(L.W, en2 + DIR);
+            a0 = B::load(L.SW, en2); a1 = B::load(L.SW, en2 + DIR);
+            c0 = B::load(L.NW, en2); c1 = B::load(L.NW, en2 + DIR);
+            want<(M + 1) % (RX / 2)>(L, en2, zero_u);
+            weights(Cw, (en2 - DIR * (2 * NU + 2)) >> 1);
+            B::template sweeps<M>();
+            B::template write<M>(uout, e);
+            // residual of the two rows behind the last sweep, restriction of f
+            T r0[2], r1[2];
+            r0[0] = B::template resid<M, -2 * NU, 0>();
+            r0[1] = B::template resid<M, -2 * NU, 1>();
+            r1[0] = B::template resid<M, -2 * NU - 1, 0>();
+            r1[1] = B::template resid<M, -2 * NU - 1, 1>();
+            const int f = e - DIR * (2 * NU + 2), J = f >> 1;
+            // rows f - 1 and f + 1: the odd rows of the previous step and of this one
+            const T *rd = DIR > 0 ? pr1 : r1, *ru = DIR > 0 ? r1 : pr1;
+            const T dw = from_west(rd[1]), mw = from_west(pr0[1]), uw = from_west(ru[1]);
+            if (rest && J >= 1 && J <= nc && f >= this->y0 && f < this->y1) {
+                const size_t c = (size_t)J * Cw.ld + I;
+                T s = wc[0] * dw;
+                s = s + wc[1] * rd[0];
+                s = s + wc[2] * rd[1];
+                s = s + wc[3] * mw;
+                s = s + pr0[0];
+                s = s + wc[4] * pr0[1];
+                s = s + wc[5] * uw;
+                s = s + wc[6] * ru[0];
+                s = s + wc[7] * ru[1];
+                Cl.b[c] = s;
+                Cl.u[c] = (T)0;
+            }
+            pr0[0] = r0[0]; pr0[1] = r0[1];
+            pr1[0] = r1[0]; pr1[1] = r1[1];
+            turn<M + 1>(L, uout, Cw, Cl, en2, elast, zero_u, w0, w1, a0, a1, c0, c1);
+        }
+    }
+};
+
+template <typename T, int NU, bool ZU>
+__global__ __launch_bounds__(64, 1) void k_pre_wave(Lev<T> L, T *__restrict__ uout, Wts<T> C, Lev<T> Cl, TileGeo G,
+                                                    const int *stop)
+{
+    int tid, k;
+    if (!tile_work(G, tid, k)) return;
+    if (stopped(stop ? stop + k * G.kstop : stop)) return;
+    L.u += k * G.ksf; L.b += k * G.ksf; uout += k * G.ksf;
+    Cl.u += k * G.ksc; Cl.b += k * G.ksc;
+    __shared__ WaveLds<T, NU> S;
+    if (wave_up(G, tid)) {
+        WavePre<T, NU, 1> P;
+        P.run(L, uout, C, Cl, G, tid, S, ZU);
+    } else {
+        WavePre<T, NU, -1> P;
+        P.run(L, uout, C, Cl, G, tid, S, ZU);
+    }
+}
+
+// Interpolation and nu sweeps (results as post_tile without the norm).
+template <typename T, int NU, int DIR>
+struct WavePost : WaveTile<T, NU, DIR> {
+    using B = WaveTile<T, NU, DIR>;
+    using V = typename B::V;
+    static constexpr int RX = B::RX;
+    T e0, w[8];                // e_c of row e / 2 at I; the next step's weights
+    T en;                      // e_c of the coarse row after it
+    int Ic, nc, ldc;
+
+    __device__ __forceinline__ void run(const Lev<T> &L, T *__restrict__ uout, const Wts<T> &Cw,
+                                        const T *__restrict__ ec, const TileGeo &G, int tid, WaveLds<T, NU> &lds)
+    {
+        B::place(L, G, tid, lds);
+        nc = (this->n - 1) >> 1;
+        ldc = Cw.ld;
+        Ic = this->i0c >> 1;
+        const int y0 = this->y0, y1 = this->y1;
+        const int es = DIR > 0 ? (y0 - 2 * NU + 1) & ~1 : (y1 - 1 + 2 * NU) & ~1;
+        const int elast = DIR > 0 ? (y1 - 2 + 2 * NU) & ~1 : y0 + 1 - 2 * NU;   // writes the last owned row (y0 is odd)
+        e0 = crow(ec, (es - DIR * (2 * NU + 2)) >> 1);
+        fill<-2 * NU - 2>(L, Cw, ec, es);
+        V w0 = B::load(L.W, es), w1 = B::load(L.W, es + DIR), a0 = B::load(L.SW, es), a1 = B::load(L.SW, es + DIR);
+        V c0 = B::load(L.NW, es), c1 = B::load(L.NW, es + DIR);
+        want<0>(L, es);
+        en = crow(ec, (es >> 1) + DIR);
+        weights(Cw, es);
+        for (int e = es; DIR * (elast - e) >= 0; e += DIR * RX) turn<0>(L, uout, Cw, ec, e, elast, w0, w1, a0, a1, c0, c1);
+    }
+
+private:
+    __device__ __forceinline__ T crow(const T *ec, int J) const
+    {
+        return ec[(size_t)(J >= 0 && J <= nc + 1 ? J : nc + 1) * ldc + Ic];
+    }
+    // weights of rows e (even) and e + DIR: LL, LR at (I + 1, J0), LB, LA at
+    // (I, J1) and LSW, LSE, LNW, LNE at (I + 1, J1)
+    __device__ __forceinline__ void weights(const Wts<T> &C, int e)
+    {
+        const int J0 = e >> 1, J1 = DIR > 0 ? J0 + 1 : J0;
+        const size_t c0 = (size_t)(J0 >= 0 && J0 <= nc + 1 ? J0 : nc + 1) * ldc + Ic;
+        const size_t c1 = (size_t)(J1 >= 0 && J1 <= nc + 1 ? J1 : nc + 1) * ldc + Ic;
+        w[0] = C.at(LL, c0 + 1);
+        w[1] = C.at(LR, c0 + 1);
+        w[2] = C.at(LB, c1);
+        w[3] = C.at(LA, c1);
+        w[4] = C.at(LSW, c1 + 1);
+        w[5] = C.at(LSE, c1 + 1);
+        w[6] = C.at(LNW, c1 + 1);
+        w[7] = C.at(LNE, c1 + 1);
+    }
+    // u += P e_c on rows e and e + DIR (slots S0, S1); ee, eo: e_c of row e / 2
+    // and of the one on the odd row's other side
+    template <int S0, int S1>
+    __device__ __forceinline__ void correct(int e, T ee, T eo)
+    {
+        const T eee = from_east(ee), eoe = from_east(eo);
+        const T el = DIR > 0 ? ee : eo, ele = DIR > 0 ? eee : eoe;   // below the odd row
+        const T eu = DIR > 0 ? eo : ee, eue = DIR > 0 ? eoe : eee;   // above it
+        const int n = this->n;
+        if (e >= 1 && e <= n) {
+            if (this->in0) this->u[S0][0] = this->u[S0][0] + ee;
+            if (this->in1) {
+                const T c = w[0] * ee + w[1] * eee;
+                this->u[S0][1] = this->u[S0][1] + c;
+            }
+        }
+        if (e + DIR >= 1 && e + DIR <= n) {
+            if (this->in0) {
+                const T c = w[2] * el + w[3] * eu;
+                this->u[S1][0] = this->u[S1][0] + c;
+            }
+            if (this->in1) {
+                T c = w[4] * el + w[5] * ele;
+                c = c + w[6] * eu;
+                c = c + w[7] * eue;
+                this->u[S1][1] = this->u[S1][1] + c;
+            }
+        }
+    }
+    template <int D>
+    __device__ __forceinline__ void fill(const Lev<T> &L, const Wts<T> &Cw, const T *ec, int es)
+    {
+        if constexpr (D < 0) {
+            constexpr int S0 = B::template at<0>(D), S1 = B::template at<0>(D + 1);
+            const int row = es + DIR * D;
+            const V u0 = B::load(L.u, row), u1 = B::load(L.u, row + DIR);
+            this->u[S0][0] = u0.x; this->u[S0][1] = u0.y;
+            this->u[S1][0] = u1.x; this->u[S1][1] = u1.y;
+            const T e1 = crow(ec, (row >> 1) + DIR);
+            weights(Cw, row);
+            B::template request<S0>(L, row);
+            B::template request<S1>(L, row + DIR);
+            B::template put_couplings<S0>(B::load(L.W, row), B::load(L.SW, row), B::load(L.NW, row));
+            B::template put_couplings<S1>(B::load(L.W, row + DIR), B::load(L.SW, row + DIR), B::load(L.NW, row + DIR));
+            correct<S0, S1>(row, e0, e1);
+            B::template arrived<S0>(row);
+            B::template arrived<S1>(row + DIR);
+            e0 = e1;
+            fill<D + 2>(L, Cw, ec, es);
+        }
+    }
+    template <int M>
+    __device__ __forceinline__ void want(const Lev<T> &L, int e)
+    {
+        constexpr int S0 = B::template at<M>(0), S1 = B::template at<M>(1);
+        const V u0 = B::load(L.u, e), u1 = B::load(L.u, e + DIR);
+        this->u[S0][0] = u0.x; this->u[S0][1] = u0.y;
+        this->u[S1][0] = u1.x; this->u[S1][1] = u1.y;
+        B::template request<S0>(L, e);
+        B::template request<S1>(L, e + DIR);
+    }
+    template <int M>
+    __device__ __forceinline__ void turn(const Lev<T> &L, T *__restrict__ uout, const Wts<T> &Cw,
+                                         const T *__restrict__ ec, int e, int elast, V &w0, V &w1, V &a0, V &a1,
+                                         V &c0, V &c1)
+    {
+        if constexpr (M < RX / 2) {
+            if (DIR * (e - elast) > 0) return;
+            constexpr int S0 = B::template at<M>(0), S1 = B::template at<M>(1);
+            wave_lds_order();
+            B::template put_couplings<S0>(w0, a0, c0);
+            B::template put_couplings<S1>(w1, a1, c1);
+            wave_lds_order();
+            B::template arrived<S0>(e);
+            B::template arrived<S1>(e + DIR);
+            correct<S0, S1>(e, e0, en);
+            e0 = en;
+            // the next step's data
+            const int en2 = e + 2 * DIR;
+            w0 = B::load(L.W, en2); w1 = B::load(L.W, en2 + DIR);
+            a0 = B::load(L.SW, en2); a1 = B::load(L.SW, en2 + DIR);
+            c0 = B::load(L.NW, en2); c1 = B::load(L.NW, en2 + DIR);
+            want<(M + 1) % (RX / 2)>(L, en2);
+            en = crow(ec, (e >> 1) + 2 * DIR);
+            weights(Cw, en2);
+            B::template sweeps<M>();
+            B::template write<M>(uout, e);
+            turn<M + 1>(L, uout, Cw, ec, en2, elast, w0, w1, a0, a1, c0, c1);
+        }
+    }
+};
+
+template <typename T, int NU>
+__global__ __launch_bounds__(64, 1) void k_post_wave(Lev<T> L, T *__restrict__ uout, Wts<T> C,
+                                                     const T *__restrict__ ec, TileGeo G, const int *stop)
+{
+    int tid, k;
+    if (!tile_work(G, tid, k)) return;
+    if (stopped(stop ? stop + k * G.kstop : stop)) return;
+    L.u += k * G.ksf; L.b += k * G.ksf; uout += k * G.ksf;
+    ec += k * G.ksc;
+    __shared__ WaveLds<T, NU> S;
+    if (wave_up(G, tid)) {
+        WavePost<T, NU, 1> P;
+        P.run(L, uout, C, ec, G, tid, S);
+    } else {
+        WavePost<T, NU, -1> P;
+        P.run(L, uout, C, ec, G, tid, S);
+    }
+}
+
+}  // namespace bmg
