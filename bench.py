@@ -38,7 +38,7 @@ HBM_PEAK_GBS = 8000.0
 # stored weights their 8 planes add 16 B per fine point.
 
 
-KERNEL_NAMES = {"postpre": "k_postpre (fine post pass with the next cycle's fine pre pass)",
+KERNEL_NAMES = {"postpre": "k_postpre_wave (fine post pass with the next cycle's fine pre pass)",
                 "pre": "k_pre (fine pre pass)", "resnorm": "k_resid_dd (FP64 outer residual)",
                 "smooth": "k_gs_colour / line relaxation (fine level)"}
 
@@ -580,7 +580,7 @@ def main():
         tclass = "resnorm"     # the FP64 outer residual (accurate, 64 B per point)
     elif tclass == "pre":
         # FP64 V(2,1) on the five-point fine level: the fine post pass of each
-        # plain cycle runs with the next cycle's fine pre pass (k_postpre)
+        # plain cycle runs with the next cycle's fine pre pass (k_postpre_wave)
         tclass = "postpre"
 
     def step(trace: bool):
@@ -628,7 +628,7 @@ def main():
     # the survey's counting rule for a fused pass: the smoother's stream (stencil,
     # b, u read, u written: 48 B per fine point) once, plus the interpolation
     # weights (16), e_c and b_c (2 each) it reads or writes: 68 B per fine point
-    # for k_postpre; the library's count (bpl) adds the second iterate written
+    # for k_postpre_wave; the library's count (bpl) adds the second iterate written
     # (u_k, 8) and the zeroed coarse iterate (2): 78
     survey_bpl = None
     if tclass == "postpre":

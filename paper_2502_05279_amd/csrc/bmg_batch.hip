@@ -415,11 +415,11 @@ __global__ __launch_bounds__(BT, 4) void k_batch(BArgs A, int mode, int steps)
                 L.u = constant(q.ualt[d]);
                 if (d == 0) {
                     const IrArgs ir{nullptr, nullptr, &q.scale, constant(q.XH), constant(q.XL)};
-                    post_tile<float, false, 1, false, true>(L, out, C, ec, g, w.y, nullptr,
-                                                            *reinterpret_cast<TileLds<float, false, 1> *>(smem), ir);
+                    post_tile<float, false, 1, true>(L, out, C, ec, g, w.y,
+                                                     *reinterpret_cast<TileLds<float, false, 1> *>(smem), ir);
                 } else {
-                    post_tile<float, true, 1, false>(L, out, C, ec, g, w.y, nullptr,
-                                                     *reinterpret_cast<TileLds<float, true, 1> *>(smem));
+                    post_tile<float, true, 1>(L, out, C, ec, g, w.y,
+                                              *reinterpret_cast<TileLds<float, true, 1> *>(smem));
                 }
                 __syncthreads();
             }

@@ -159,11 +159,9 @@ struct IrArgs {
 // {c1, c2(s)} and {c3(s), c0(s+1)}: 2 NU + 1 barriers instead of 4 NU.
 // The window rows are compile-time positions k = row - (e - 2NU - 2); a lane
 // picks its row's entries by its column parity.
-// done(s) runs after the phase that completes sweep s (all lanes past the
-// barrier that follows it).
-template <typename T, int NU, int RU, typename Done>
+template <typename T, int NU, int RU>
 __device__ __forceinline__ void five_point_sweeps(T *su, const T *sW, int lane, int i, bool col_upd, int n, int e,
-                                                  const T *rB, const T *rO, const T *rS, Done &&done)
+                                                  const T *rB, const T *rO, const T *rS)
 {
     const bool odd = i & 1;
     const int base = e - 2 * NU - 2;
@@ -206,15 +204,7 @@ __device__ __forceinline__ void five_point_sweeps(T *su, const T *sW, int lane, 
         __syncthreads();
         pair(true, ke - 1, s + 1 < NU, ke - 2);             // c3 on e - 2s - 1, c0 of s + 1 on e - 2s - 2
         __syncthreads();
-        done(s);
     }
-}
-
-template <typename T, int NU, int RU>
-__device__ __forceinline__ void five_point_sweeps(T *su, const T *sW, int lane, int i, bool col_upd, int n, int e,
-                                                  const T *rB, const T *rO, const T *rS)
-{
-    five_point_sweeps<T, NU, RU>(su, sW, lane, i, col_upd, n, e, rB, rO, rS, [](int) {});
 }
 
 // With WREC the restriction weights are not read: each column computes the
@@ -501,15 +491,13 @@ __global__ __launch_bounds__(FW) void k_pre(Lev<T> L, T *__restrict__ uout, Wts<
 }
 
 // ---------------------------------------------------------- post pass
-// u_out = GS^NU(u_in + P e_c).  With NORM (FP64 fine level) also the
-// per-tile sum of squares of the accurate residual b - A u_out over the owned
-// points into part[tile].  Window: rows e-2NU-2 .. e+1 at step e; the data of
-// step e+2 (rows, coarse row, interpolation weights) is requested while step
+// u_out = GS^NU(u_in + P e_c).  Window: rows e-2NU-2 .. e+1 at step e; the data
+// of step e+2 (rows, coarse row, interpolation weights) is requested while step
 // e computes.
-template <typename T, bool NINE, int NU, bool NORM, bool IRUP = false>
+template <typename T, bool NINE, int NU, bool IRUP = false>
 __device__ __forceinline__ void post_tile(const Lev<T> &L, T *__restrict__ uout, const Wts<T> &C,
                                           const T *__restrict__ ec, const TileGeo &G, int tid,
-                                          double *__restrict__ part, TileLds<T, NINE, NU> &S, IrArgs ir = {})
+                                          TileLds<T, NINE, NU> &S, IrArgs ir = {})
 {
     static_assert(NU <= 2, "post pass supports up to two sweeps");
     constexpr int RW = 2 * NU + 4;
@@ -652,7 +640,6 @@ __device__ __forceinline__ void post_tile(const Lev<T> &L, T *__restrict__ uout,
         pw = ld_iw(e);
     };
     fetch(es);
-    double acc = 0.0;
     for (int e = es; e <= elast; e += 2) {
         // with two ring rows beyond the window the rows this step brings in
         // take slots no lane still reads, and no barrier is needed before them
@@ -715,352 +702,7 @@ __device__ __forceinline__ void post_tile(const Lev<T> &L, T *__restrict__ uout,
                 }
             }
         }
-        if (NORM) {
-            // accurate residual of the final rows e-2NU and e-2NU-1
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int row = e - 2 * NU - t;
-                const int k = row - (e - 2 * NU - 2);
-                if (col_own && row >= y0 && row < y1 && row >= 1) {
-                    const int r0 = slot<RU>(row) * FW + lane, rd = slot<RU>(row - 1) * FW + lane,
-                              ru = slot<RU>(row + 1) * FW + lane;
-                    double a[9], x[9];
-                    a[0] = NINE ? (double)sSW[r0] : 0.0;        x[0] = su[rd - 1];
-                    a[1] = rS[k];                               x[1] = su[rd];
-                    a[2] = NINE ? (double)sNW[rd + 1] : 0.0;    x[2] = su[rd + 1];
-                    a[3] = sW[r0];                              x[3] = su[r0 - 1];
-                    a[4] = sW[r0 + 1];                          x[4] = su[r0 + 1];
-                    a[5] = NINE ? (double)sNW[r0] : 0.0;        x[5] = su[ru - 1];
-                    a[6] = rS[k + 1];                           x[6] = su[ru];
-                    a[7] = NINE ? (double)sSW[ru + 1] : 0.0;    x[7] = su[ru + 1];
-                    a[8] = rO[k];                               x[8] = su[r0];
-                    double s = rB[k], cc = 0.0, ns, se;
-#pragma unroll
-                    for (int q = 0; q < 9; ++q) {
-                        if (!NINE && (q == 0 || q == 2 || q == 5 || q == 7)) continue;
-                        const double pr = a[q] * x[q];
-                        const double pe = fma(a[q], x[q], -pr);
-                        two_sum(s, -pr, ns, se);
-                        s = ns;
-                        cc = cc + (se - pe);
-                    }
-                    const double r = s + cc;
-                    acc += r * r;
-                }
-            }
-        }
     }
-    if (NORM) {
-        __syncthreads();  // the residual ring is free again: reduce through it
-        acc = block_sum(acc, reinterpret_cast<double *>(S.sx));
-        if (threadIdx.x == 0) part[tid] = acc;
-    }
-}
-
-template <typename T, bool NINE, int NU, bool NORM>
-__global__ __launch_bounds__(FW) void k_post(Lev<T> L, T *__restrict__ uout, Wts<T> C, const T *__restrict__ ec,
-                                              TileGeo G, double *__restrict__ part, const int *stop)
-{
-    int tid, k;
-    if (!tile_work(G, tid, k)) return;
-    if (stopped(stop ? stop + k * G.kstop : stop)) return;
-    L.u += k * G.ksf; L.b += k * G.ksf; uout += k * G.ksf;
-    ec += k * G.ksc;
-    if (NORM) part += k * G.kpart;
-    __shared__ TileLds<T, NINE, NU> S;
-    post_tile<T, NINE, NU, NORM>(L, uout, C, ec, G, tid, part, S);
-}
-
-// --------------------------------- post pass and the next cycle's pre pass
-// The fine level's post pass of cycle k and its pre pass of cycle k+1 as one
-// pass (FP64, five-point level, one right-hand side, one post sweep, NB pre
-// sweeps).  Rows enter as u' + P e_c; sweep 0 gives the cycle's result u_k,
-// which is written (a stop decided by its norm finds it) and copied to a
-// four-row LDS ring, from which the per-tile sum of squares of its accurate
-// residual goes to part[tile]; sweeps 1..NB give the next cycle's
-// pre-smoothed iterate u'' (written), whose residual is restricted with the
-// stored weights (the rows the interpolation read, requested again).  Every array
-// value is the one the two separate passes give (the norm's partial sums follow
-// this pass's tiles).  u_c = 0 goes to a separate coarse buffer (ucz), since the
-// coarse correction e_c is still read by other tiles.
-template <int NB>
-struct PostPreLds {
-    static constexpr int NS = NB + 1;
-    static constexpr int RW = 2 * NS + 4;
-    static constexpr int RU = RW + 2;      // ring rows (see postpre_tile)
-    static constexpr int CW = FW / 2 + 2;  // coarse columns of a strip
-    double su[RU * FW], sW[RU * FW], sx[4 * FW];
-    double sec[8 * CW];                    // e_c rows, ring of 8
-    double uk[4 * FW];                     // u_k rows, ring of 4
-};
-
-template <int NB>
-__device__ __forceinline__ void postpre_tile(const Lev<double> &L, double *__restrict__ ukout,
-                                             double *__restrict__ uout, const Wts<double> &C,
-                                             const double *__restrict__ ec, const Lev<double> &Cl,
-                                             double *__restrict__ ucz, const TileGeo &G, int tid,
-                                             double *__restrict__ part, PostPreLds<NB> &S)
-{
-    using T = double;
-    constexpr int NS = NB + 1;                     // sweeps: one post, NB pre
-    constexpr int RW = 2 * NS + 4;                 // window rows e-2NS-2 .. e+1
-    // LDS ring rows: two more than the window, so that the rows a step
-    // brings in take the slots of rows no step still reads, and a step needs
-    // no barrier before writing them (the previous step's residuals read its
-    // whole window)
-    constexpr int RU = PostPreLds<NB>::RU;
-    constexpr int CW = PostPreLds<NB>::CW;
-    T *su = S.su, *sW = S.sW, *sr = S.sx, *sec = S.sec, *suk = S.uk;
-
-    const int n = L.n, ld = L.ld, lane = threadIdx.x, nc = Cl.n, ldc = C.ld;
-    const int useful = FW - 2 * G.hx;
-    const int tx = tid % G.tiles_x, ty = tid / G.tiles_x;
-    const int x0 = 1 + tx * useful;
-    const int i = x0 - G.hx + lane;
-    const bool col_in = i >= 0 && i <= n + 1;
-    const bool col_upd = i >= 1 && i <= n && lane >= 1 && lane < FW - 1;
-    const bool col_own = i >= x0 && i < x0 + useful && i <= n;
-    const int y0 = 1 + ty * G.ht;
-    const int y1 = min(y0 + G.ht, n + 1);
-    const int es = (y0 - 2 * NS) & ~1;
-    const int jlast = (y1 - 1) >> 1;
-    const int elast = 2 * jlast + 2 * NS + 2;
-    const int I = i >> 1;
-    const bool restrictor = !(i & 1) && col_own && I >= 1 && I <= nc;
-    const int ib = (x0 - G.hx) >> 1;               // coarse column of ring entry 0
-    const int Ie = ib + lane;
-    const bool ccol_in = lane < CW && Ie >= 0 && Ie <= nc + 1;
-    const bool odd_i = i & 1;
-    const int Ix = (i + 1) >> 1;
-
-    T rO[RW], rS[RW], rB[RW];
-    auto ld_row = [&](const T *a, int row) -> T {
-        return (col_in && row >= 0 && row <= n + 1) ? a[(size_t)row * ld + i] : (T)0;
-    };
-    auto ld_crow = [&](int J) -> T {
-        return (ccol_in && J >= 0 && J <= nc + 1) ? ec[(size_t)J * ldc + Ie] : (T)0;
-    };
-    // interpolation weights of this column for rows e (even) and e+1 (odd),
-    // as in post_tile
-    struct IW { T w[6]; };
-    const int p2 = odd_i ? LSW : LB, p3 = odd_i ? LSE : LA;
-    auto ld_iw = [&](int e) -> IW {
-        IW r;
-        T *w = r.w;
-        const int J0 = e >> 1, J1 = J0 + 1;
-        const bool ok0 = col_upd && odd_i && e >= 1 && e <= n;
-        const bool ok1 = col_upd && e + 1 >= 1 && e + 1 <= n;
-        const bool ok2 = ok1 && odd_i;
-        const size_t c0 = ok0 ? (size_t)J0 * ldc + Ix : 0;
-        const size_t c1 = ok1 ? (size_t)J1 * ldc + (odd_i ? Ix : (i >> 1)) : 0;
-        w[0] = ok0 ? C.at(LL, c0) : (T)0;
-        w[1] = ok0 ? C.at(LR, c0) : (T)0;
-        w[2] = ok1 ? C.at(p2, c1) : (T)0;
-        w[3] = ok1 ? C.at(p3, c1) : (T)0;
-        w[4] = ok2 ? C.at(LNW, c1) : (T)0;
-        w[5] = ok2 ? C.at(LNE, c1) : (T)0;
-        return r;
-    };
-    // u' + P e_c at (i, row), e_c from the ring (the terms of post_tile)
-    auto interp = [&](int row, T u, const IW &iw) -> T {
-        const T *w = iw.w;
-        if (!col_upd || row < 1 || row > n) return u;
-        T e;
-        if (!(row & 1)) {
-            const T *er = sec + ((row >> 1) & 7) * CW;
-            if (!odd_i) e = er[(i >> 1) - ib];
-            else e = w[0] * er[Ix - 1 - ib] + w[1] * er[Ix - ib];
-        } else {
-            const int J = (row + 1) >> 1;
-            const T *es_ = sec + ((J - 1) & 7) * CW, *en = sec + (J & 7) * CW;
-            if (!odd_i) {
-                e = w[2] * es_[(i >> 1) - ib] + w[3] * en[(i >> 1) - ib];
-            } else {
-                e = w[2] * es_[Ix - 1 - ib] + w[3] * es_[Ix - ib];
-                e = e + w[4] * en[Ix - 1 - ib];
-                e = e + w[5] * en[Ix - ib];
-            }
-        }
-        return u + e;
-    };
-
-    // coarse rows of the first step's window and of the first two steps:
-    // (es-2NS-2)/2 .. es/2 + 1 (NS + 3 <= 8 rows)
-    for (int J = (es - 2 * NS - 2) >> 1; J <= (es >> 1) + 1; ++J) {
-        const T v = ld_crow(J);
-        if (lane < CW) sec[(J & 7) * CW + lane] = v;
-    }
-    __syncthreads();
-    // window of step es without its own two rows: rows es-2NS-2 .. es-1,
-    // interpolated, at positions 2..RW-1 (aligned by the first shift)
-#pragma unroll
-    for (int k = 2; k < RW; k += 2) {
-        const int row = es - 2 * NS - 4 + k;       // even
-        const IW wk = ld_iw(row);
-        su[slot<RU>(row) * FW + lane] = interp(row, ld_row(L.u, row), wk);
-        su[slot<RU>(row + 1) * FW + lane] = interp(row + 1, ld_row(L.u, row + 1), wk);
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            sW[slot<RU>(row + t) * FW + lane] = ld_row(L.W, row + t);
-            rO[k + t] = ld_row(L.O, row + t);
-            rS[k + t] = ld_row(L.S, row + t);
-            rB[k + t] = ld_row(L.b, row + t);
-        }
-    }
-    // the stored weights of the coarse point a restriction step takes, as
-    // k_restrict reads them (even columns that own a coarse point): requested
-    // during step e, used when the restriction of step e runs after the first
-    // barrier of step e + 2.  The post pass read the same rows four steps before, so
-    // they come from the caches; computing them here instead (two lumped
-    // rows and eight divisions per coarse point, in branches the odd and the
-    // even columns each take) cost more time than the loads.
-    T rw[8];
-    auto fetch_rw = [&](int e) {
-        const int J = (e - 2 * NS - 2) >> 1;
-        const bool ok = restrictor && J >= 1 && J <= nc;
-        const size_t c = ok ? (size_t)J * ldc + I : 0, cn = c + ldc;
-        rw[0] = ok ? C.at(LNE, c) : (T)0;
-        rw[1] = ok ? C.at(LA, c) : (T)0;
-        rw[2] = ok ? C.at(LNW, c + 1) : (T)0;
-        rw[3] = ok ? C.at(LR, c) : (T)0;
-        rw[4] = ok ? C.at(LL, c + 1) : (T)0;
-        rw[5] = ok ? C.at(LSE, cn) : (T)0;
-        rw[6] = ok ? C.at(LB, cn) : (T)0;
-        rw[7] = ok ? C.at(LSW, cn + 1) : (T)0;
-    };
-
-    T pu0, pu1, pW0, pW1, pO0, pO1, pS0, pS1, pB0, pB1, pec;
-    IW pw;
-    // data of step e; the e_c row it adds is the one step e + 2 needs
-    auto fetch = [&](int e) {
-        pu0 = ld_row(L.u, e); pu1 = ld_row(L.u, e + 1);
-        pW0 = ld_row(L.W, e); pW1 = ld_row(L.W, e + 1);
-        pO0 = ld_row(L.O, e); pO1 = ld_row(L.O, e + 1);
-        pS0 = ld_row(L.S, e); pS1 = ld_row(L.S, e + 1);
-        pB0 = ld_row(L.b, e); pB1 = ld_row(L.b, e + 1);
-        pec = ld_crow((e >> 1) + 2);
-        pw = ld_iw(e);
-    };
-    fetch(es);
-    double acc = 0.0;
-    // restriction of the coarse row of step e (J = (e - 2NS - 2) / 2) by the
-    // even columns, from the residual ring and the weights step e requested;
-    // it runs after the next step's first barrier (or after the last step),
-    // before that step's residuals overwrite the ring
-    auto restrict_step = [&](int e) {
-        const T *w = rw;
-        const int f = e - 2 * NS - 2, J = f >> 1;
-        if (restrictor && J >= 1 && J <= nc && f >= y0 && f < y1) {
-            const size_t c = (size_t)J * Cl.ld + I;
-            const T *rd = sr + ((f - 1) & 3) * FW + lane, *r0 = sr + (f & 3) * FW + lane,
-                    *ru = sr + ((f + 1) & 3) * FW + lane;
-            T s = w[0] * rd[-1];
-            s = s + w[1] * rd[0];
-            s = s + w[2] * rd[1];
-            s = s + w[3] * r0[-1];
-            s = s + r0[0];
-            s = s + w[4] * r0[1];
-            s = s + w[5] * ru[-1];
-            s = s + w[6] * ru[0];
-            s = s + w[7] * ru[1];
-            Cl.b[c] = s;
-            ucz[c] = (T)0;
-        }
-    };
-
-    for (int e = es; e <= elast; e += 2) {
-        if (lane < CW) sec[(((e >> 1) + 2) & 7) * CW + lane] = pec;
-#pragma unroll
-        for (int k = 0; k < RW - 2; ++k) { rO[k] = rO[k + 2]; rS[k] = rS[k + 2]; rB[k] = rB[k + 2]; }
-        rO[RW - 2] = pO0; rO[RW - 1] = pO1;
-        rS[RW - 2] = pS0; rS[RW - 1] = pS1;
-        rB[RW - 2] = pB0; rB[RW - 1] = pB1;
-        {
-            const int s0 = slot<RU>(e) * FW + lane, s1 = slot<RU>(e + 1) * FW + lane;
-            su[s0] = interp(e, pu0, pw);
-            su[s1] = interp(e + 1, pu1, pw);
-            sW[s0] = pW0; sW[s1] = pW1;
-        }
-        if (e + 2 <= elast) fetch(e + 2);
-        __syncthreads();
-        if (e > es) restrict_step(e - 2);
-        fetch_rw(e);
-        // sweep 0 completes rows e and e-1 of u_k: written, and kept for the norm
-        five_point_sweeps<T, NS, RU>(su, sW, lane, i, col_upd, n, e, rB, rO, rS, [&](int s) {
-            if (s == 0) {
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const int row = e - t;
-                    const T v = su[slot<RU>(row) * FW + lane];
-                    suk[(row & 3) * FW + lane] = v;
-                    if (col_own && row >= y0 && row < y1) ukout[(size_t)row * ld + i] = v;
-                }
-            }
-        });
-        // the last sweep's two rows are final: write the owned ones
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int row = e - 2 * NS + 2 - t;
-            if (col_own && row >= y0 && row < y1)
-                uout[(size_t)row * ld + i] = su[slot<RU>(row) * FW + lane];
-        }
-        // residual of rows e-2NS and e-2NS-1
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int row = e - 2 * NS - t;
-            const int k = row - (e - 2 * NS - 2);
-            T r = 0;
-            if (col_upd && row >= 1 && row <= n)
-                r = res_lds<T, false, RU>(su, sW, nullptr, nullptr, lane, row, rB[k], rO[k], rS[k], rS[k + 1]);
-            sr[(row & 3) * FW + lane] = r;
-        }
-        // accurate residual of u_k at rows e-1 and e-2 (the terms of post_tile)
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int row = e - 1 - t;
-            const int k = row - (e - 2 * NS - 2);
-            if (col_own && row >= y0 && row < y1 && row >= 1) {
-                const int r0 = slot<RU>(row) * FW + lane;
-                const T *xd = suk + ((row - 1) & 3) * FW + lane, *x0_ = suk + (row & 3) * FW + lane,
-                        *xu = suk + ((row + 1) & 3) * FW + lane;
-                double a[5], x[5];
-                a[0] = rS[k];       x[0] = xd[0];
-                a[1] = sW[r0];      x[1] = x0_[-1];
-                a[2] = sW[r0 + 1];  x[2] = x0_[1];
-                a[3] = rS[k + 1];   x[3] = xu[0];
-                a[4] = rO[k];       x[4] = x0_[0];
-                double s = rB[k], cc = 0.0, ns, se;
-#pragma unroll
-                for (int q = 0; q < 5; ++q) {
-                    const double pr = a[q] * x[q];
-                    const double pe = fma(a[q], x[q], -pr);
-                    two_sum(s, -pr, ns, se);
-                    s = ns;
-                    cc = cc + (se - pe);
-                }
-                const double r = s + cc;
-                acc += r * r;
-            }
-        }
-    }
-    __syncthreads();
-    restrict_step(elast);
-    __syncthreads();  // the residual ring is free again: reduce through it
-    acc = block_sum(acc, reinterpret_cast<double *>(S.sx));
-    if (threadIdx.x == 0) part[tid] = acc;
-}
-
-template <int NB>
-__global__ __launch_bounds__(FW) void k_postpre(Lev<double> L, double *__restrict__ ukout, double *__restrict__ uout,
-                                                 Wts<double> C, const double *__restrict__ ec, Lev<double> Cl,
-                                                 double *__restrict__ ucz, TileGeo G, double *__restrict__ part,
-                                                 const int *stop)
-{
-    int tid, k;
-    if (!tile_work(G, tid, k)) return;
-    if (stopped(stop)) return;
-    __shared__ PostPreLds<NB> S;
-    postpre_tile<NB>(L, ukout, uout, C, ec, Cl, ucz, G, tid, part, S);
 }
 
 // The fine-level passes of an FP32 refinement step (IrArgs).  The post pass
@@ -1084,416 +726,8 @@ __global__ __launch_bounds__(FW) void k_post_ir(Lev<T> L, Wts<T> C, const T *__r
     if (!tile_work(G, tid, k)) return;
     if (stopped(stop)) return;
     __shared__ TileLds<T, false, NU> S;
-    post_tile<T, false, NU, false, true>(L, nullptr, C, ec, G, tid, nullptr, S, ir);
+    post_tile<T, false, NU, true>(L, nullptr, C, ec, G, tid, S, ir);
 }
-
-}  // namespace bmg
-
-namespace bmg {
-
-// ------------------------------------ four-row steps (five-point levels)
-// The same pipelines as pre_tile and post_tile with four new rows per step:
-// sweep s updates the even rows e-2s and e-2s+2 (colours 0, 1) and then the
-// odd rows e-2s-1 and e-2s+1 (colours 2, 3).  This is the two-row schedule of
-// steps e and e+2 with their phases merged; every point sees the same
-// neighbour values in the same order, so the results are the same bits, and
-// each workgroup barrier now separates twice the work.  Window: rows
-// e-2NU-2 .. e+3 (RW = 2NU+6), LDS rings of RW rows.
-template <int R>
-__device__ __forceinline__ int qslot(int row) { return (row + 64 * R) % R; }
-
-template <typename T, int NU>
-struct TileLds4 {
-    static constexpr int RW = 2 * NU + 6;
-    T su[RW * FW], sW[RW * FW], sx[8 * FW];
-};
-
-// five-point Gauss-Seidel update and residual from the rings (the terms of
-// gs_point / residual_point in their order)
-template <typename T, int R>
-__device__ __forceinline__ T gs5(const T *su, const T *sW, int lane, int row, T b, T O, T S, T Sn)
-{
-    const int r0 = qslot<R>(row) * FW + lane;
-    const int rd = qslot<R>(row - 1) * FW + lane;
-    const int ru = qslot<R>(row + 1) * FW + lane;
-    T s = b;
-    s -= S * su[rd];
-    s -= sW[r0] * su[r0 - 1];
-    s -= sW[r0 + 1] * su[r0 + 1];
-    s -= Sn * su[ru];
-    return s / O;
-}
-
-template <typename T, int R>
-__device__ __forceinline__ T res5(const T *su, const T *sW, int lane, int row, T b, T O, T S, T Sn)
-{
-    const int r0 = qslot<R>(row) * FW + lane;
-    const int rd = qslot<R>(row - 1) * FW + lane;
-    const int ru = qslot<R>(row + 1) * FW + lane;
-    T s = b;
-    s -= S * su[rd];
-    s -= sW[r0] * su[r0 - 1];
-    s -= sW[r0 + 1] * su[r0 + 1];
-    s -= Sn * su[ru];
-    s -= O * su[r0];
-    return s;
-}
-
-template <typename T, int NU>
-__device__ __forceinline__ void pre_tile4(const Lev<T> &L, T *__restrict__ uout, const Wts<T> &C,
-                                          const Lev<T> &Cl, const TileGeo &G, int tid, TileLds4<T, NU> &S)
-{
-    constexpr int RW = 2 * NU + 6;
-    T *su = S.su, *sW = S.sW, *sr = S.sx;
-
-    const int n = L.n, ld = L.ld, lane = threadIdx.x, nc = Cl.n;
-    const int useful = FW - 2 * G.hx;
-    const int tx = tid % G.tiles_x, ty = tid / G.tiles_x;
-    const int x0 = 1 + tx * useful;
-    const int i = x0 - G.hx + lane;
-    const bool col_in = i >= 0 && i <= n + 1;
-    const bool col_upd = i >= 1 && i <= n && lane >= 1 && lane < FW - 1;
-    const bool col_own = i >= x0 && i < x0 + useful && i <= n;
-    const int y0 = 1 + ty * G.ht;
-    const int y1 = min(y0 + G.ht, n + 1);
-    const int es = (y0 - 2 * NU) & ~1;
-    const int jlast = (y1 - 1) >> 1;
-    const int elast = 2 * jlast + 2 * NU + 2;
-    const int I = i >> 1;
-    const bool restrictor = !(i & 1) && col_own && I >= 1 && I <= nc;
-
-    T rO[RW], rS[RW], rB[RW];
-    auto ld_row = [&](const T *a, int row) -> T {
-        return (col_in && row >= 0 && row <= n + 1) ? a[(size_t)row * ld + i] : (T)0;
-    };
-    auto ld_w = [&](int J, T *w) {
-        const bool ok = restrictor && J >= 1 && J <= nc;
-        const size_t c = ok ? (size_t)J * C.ld + I : 0, cn = c + C.ld;
-        w[0] = ok ? C.at(LNE, c) : (T)0;
-        w[1] = ok ? C.at(LA, c) : (T)0;
-        w[2] = ok ? C.at(LNW, c + 1) : (T)0;
-        w[3] = ok ? C.at(LR, c) : (T)0;
-        w[4] = ok ? C.at(LL, c + 1) : (T)0;
-        w[5] = ok ? C.at(LSE, cn) : (T)0;
-        w[6] = ok ? C.at(LB, cn) : (T)0;
-        w[7] = ok ? C.at(LSW, cn + 1) : (T)0;
-    };
-    // window of step es without its own four rows: rows es-2NU-2 .. es-1 at
-    // positions 4..RW-1 (the first shift by four aligns them)
-#pragma unroll
-    for (int k = 4; k < RW; ++k) {
-        const int row = es - 2 * NU - 6 + k;
-        su[qslot<RW>(row) * FW + lane] = ld_row(L.u, row);
-        sW[qslot<RW>(row) * FW + lane] = ld_row(L.W, row);
-        rO[k] = ld_row(L.O, row);
-        rS[k] = ld_row(L.S, row);
-        rB[k] = ld_row(L.b, row);
-    }
-    T pu[4], pW[4], pO[4], pS[4], pB[4], pw[16], w[16];
-    auto fetch = [&](int e) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            pu[q] = ld_row(L.u, e + q);
-            pW[q] = ld_row(L.W, e + q);
-            pO[q] = ld_row(L.O, e + q);
-            pS[q] = ld_row(L.S, e + q);
-            pB[q] = ld_row(L.b, e + q);
-        }
-        ld_w((e - 2 * NU - 2) >> 1, pw);
-        ld_w(((e - 2 * NU - 2) >> 1) + 1, pw + 8);
-    };
-    fetch(es);
-
-    for (int e = es; e <= elast; e += 4) {
-        __syncthreads();  // the previous step is done with the slots reused below
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int sq = qslot<RW>(e + q) * FW + lane;
-            su[sq] = pu[q];
-            sW[sq] = pW[q];
-        }
-#pragma unroll
-        for (int k = 0; k < RW - 4; ++k) { rO[k] = rO[k + 4]; rS[k] = rS[k + 4]; rB[k] = rB[k + 4]; }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) { rO[RW - 4 + q] = pO[q]; rS[RW - 4 + q] = pS[q]; rB[RW - 4 + q] = pB[q]; }
-#pragma unroll
-        for (int q = 0; q < 16; ++q) w[q] = pw[q];
-        if (e + 4 <= elast) fetch(e + 4);
-        __syncthreads();
-        // NU sweeps, each over colours 0,1 (two even rows) then 2,3 (two odd rows)
-#pragma unroll
-        for (int s = 0; s < NU; ++s) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const int row = (c < 2 ? e - 2 * s : e - 2 * s - 1) + 2 * t;
-                    const int k = row - (e - 2 * NU - 2);
-                    if (col_upd && (i & 1) == (c & 1) && row >= 1 && row <= n)
-                        su[qslot<RW>(row) * FW + lane] =
-                            gs5<T, RW>(su, sW, lane, row, rB[k], rO[k], rS[k], rS[k + 1]);
-                }
-                __syncthreads();
-            }
-        }
-        // the last sweep's four rows are final: write the owned ones
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int row = e - 2 * NU + 1 + t;
-            if (col_own && row >= y0 && row < y1) uout[(size_t)row * ld + i] = su[qslot<RW>(row) * FW + lane];
-        }
-        // residual of rows e-2NU-1 .. e-2NU+2
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int row = e - 2 * NU - 1 + t;
-            const int k = 1 + t;
-            T r = 0;
-            if (col_upd && row >= 1 && row <= n) r = res5<T, RW>(su, sW, lane, row, rB[k], rO[k], rS[k], rS[k + 1]);
-            sr[(row & 7) * FW + lane] = r;
-        }
-        __syncthreads();
-        // restriction of coarse rows (e-2NU-2)/2 and (e-2NU)/2 by the even columns
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int f = e - 2 * NU - 2 + 2 * t, J = f >> 1;
-            if (restrictor && J >= 1 && J <= nc && f >= y0 && f < y1) {
-                const T *wt = w + 8 * t;
-                const size_t c = (size_t)J * C.ld + I;
-                const T *rd = sr + ((f - 1) & 7) * FW + lane, *r0 = sr + (f & 7) * FW + lane,
-                        *ru = sr + ((f + 1) & 7) * FW + lane;
-                T sum = wt[0] * rd[-1];
-                sum = sum + wt[1] * rd[0];
-                sum = sum + wt[2] * rd[1];
-                sum = sum + wt[3] * r0[-1];
-                sum = sum + r0[0];
-                sum = sum + wt[4] * r0[1];
-                sum = sum + wt[5] * ru[-1];
-                sum = sum + wt[6] * ru[0];
-                sum = sum + wt[7] * ru[1];
-                Cl.b[c] = sum;
-                Cl.u[c] = (T)0;
-            }
-        }
-    }
-}
-
-template <typename T, int NU>
-__global__ __launch_bounds__(FW) void k_pre4(Lev<T> L, T *__restrict__ uout, Wts<T> C, Lev<T> Cl, TileGeo G,
-                                              const int *stop)
-{
-    int tid, k;
-    if (!tile_work(G, tid, k)) return;
-    if (stopped(stop ? stop + k * G.kstop : stop)) return;
-    L.u += k * G.ksf; L.b += k * G.ksf; uout += k * G.ksf;
-    Cl.u += k * G.ksc; Cl.b += k * G.ksc;
-    __shared__ TileLds4<T, NU> S;
-    pre_tile4<T, NU>(L, uout, C, Cl, G, tid, S);
-}
-
-template <typename T, int NU, bool NORM>
-__device__ __forceinline__ void post_tile4(const Lev<T> &L, T *__restrict__ uout, const Wts<T> &C,
-                                           const T *__restrict__ ec, const TileGeo &G, int tid,
-                                           double *__restrict__ part, TileLds4<T, NU> &S)
-{
-    static_assert(NU <= 2, "post pass supports up to two sweeps");
-    constexpr int RW = 2 * NU + 6;
-    T *su = S.su, *sW = S.sW, *sec = S.sx;
-
-    const int n = L.n, ld = L.ld, lane = threadIdx.x, ldc = C.ld, nc = (n - 1) >> 1;
-    const int useful = FW - 2 * G.hx;
-    const int tx = tid % G.tiles_x, ty = tid / G.tiles_x;
-    const int x0 = 1 + tx * useful;
-    const int i = x0 - G.hx + lane;
-    const bool col_in = i >= 0 && i <= n + 1;
-    const bool col_upd = i >= 1 && i <= n && lane >= 1 && lane < FW - 1;
-    const bool col_own = i >= x0 && i < x0 + useful && i <= n;
-    const int y0 = 1 + ty * G.ht;
-    const int y1 = min(y0 + G.ht, n + 1);
-    const int es = (y0 - 2 * NU + 1) & ~1;
-    const int elast = ((y1 + 2 * NU) + 1) & ~1;
-    const int ib = (x0 - G.hx) >> 1;
-    const int Ie = ib + lane;
-    const bool ccol_in = lane < FW / 2 + 2 && Ie >= 0 && Ie <= nc + 1;
-    const bool odd_i = i & 1;
-    const int Ix = (i + 1) >> 1;
-
-    T rO[RW], rS[RW], rB[RW];
-    auto ld_row = [&](const T *a, int row) -> T {
-        return (col_in && row >= 0 && row <= n + 1) ? a[(size_t)row * ld + i] : (T)0;
-    };
-    auto ld_crow = [&](int J) -> T {
-        return (ccol_in && J >= 0 && J <= nc + 1) ? ec[(size_t)J * ldc + Ie] : (T)0;
-    };
-    struct IW { T w[6]; };
-    // the planes this column reads for its odd row: LSW, LSE, LNW, LNE (odd
-    // columns) or LB, LA (even columns); every lane issues the same six loads
-    const int p2 = odd_i ? LSW : LB, p3 = odd_i ? LSE : LA;
-    auto ld_iw = [&](int e) -> IW {
-        IW r;
-        T *w = r.w;
-        const int J0 = e >> 1, J1 = J0 + 1;
-        const bool ok0 = col_upd && odd_i && e >= 1 && e <= n;
-        const bool ok1 = col_upd && e + 1 >= 1 && e + 1 <= n;
-        const bool ok2 = ok1 && odd_i;
-        const size_t c0 = ok0 ? (size_t)J0 * ldc + Ix : 0;
-        const size_t c1 = ok1 ? (size_t)J1 * ldc + (odd_i ? Ix : (i >> 1)) : 0;
-        w[0] = ok0 ? C.at(LL, c0) : (T)0;
-        w[1] = ok0 ? C.at(LR, c0) : (T)0;
-        w[2] = ok1 ? C.at(p2, c1) : (T)0;
-        w[3] = ok1 ? C.at(p3, c1) : (T)0;
-        w[4] = ok2 ? C.at(LNW, c1) : (T)0;
-        w[5] = ok2 ? C.at(LNE, c1) : (T)0;
-        return r;
-    };
-    // u + P e_c (the expression of post_tile's interp)
-    auto interp = [&](int row, T u, const IW &iw) -> T {
-        const T *w = iw.w;
-        if (!col_upd || row < 1 || row > n) return u;
-        T e;
-        if (!(row & 1)) {
-            const T *er = sec + ((row >> 1) & 3) * FW;
-            if (!odd_i) e = er[(i >> 1) - ib];
-            else e = w[0] * er[Ix - 1 - ib] + w[1] * er[Ix - ib];
-        } else {
-            const int J = (row + 1) >> 1;
-            const T *es_ = sec + ((J - 1) & 3) * FW, *en = sec + (J & 3) * FW;
-            if (!odd_i) {
-                e = w[2] * es_[(i >> 1) - ib] + w[3] * en[(i >> 1) - ib];
-            } else {
-                e = w[2] * es_[Ix - 1 - ib] + w[3] * es_[Ix - ib];
-                e = e + w[4] * en[Ix - 1 - ib];
-                e = e + w[5] * en[Ix - ib];
-            }
-        }
-        return u + e;
-    };
-
-    // window of step es without its own four rows: rows es-2NU-2 .. es-1,
-    // interpolated, at positions 4..RW-1; their coarse rows
-    // (es-2NU-2)/2 .. es/2 (at most four) fill the e_c ring
-    for (int J = (es - 2 * NU - 2) >> 1; J <= (es >> 1); ++J) sec[(J & 3) * FW + lane] = ld_crow(J);
-    __syncthreads();
-#pragma unroll
-    for (int k = 4; k < RW; k += 2) {
-        const int row = es - 2 * NU - 6 + k;      // even
-        const IW wk = ld_iw(row);
-        su[qslot<RW>(row) * FW + lane] = interp(row, ld_row(L.u, row), wk);
-        su[qslot<RW>(row + 1) * FW + lane] = interp(row + 1, ld_row(L.u, row + 1), wk);
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            sW[qslot<RW>(row + t) * FW + lane] = ld_row(L.W, row + t);
-            rO[k + t] = ld_row(L.O, row + t);
-            rS[k + t] = ld_row(L.S, row + t);
-            rB[k + t] = ld_row(L.b, row + t);
-        }
-    }
-    T pu[4], pW[4], pO[4], pS[4], pB[4], pec[2];
-    IW pw[2];
-    auto fetch = [&](int e) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            pu[q] = ld_row(L.u, e + q);
-            pW[q] = ld_row(L.W, e + q);
-            pO[q] = ld_row(L.O, e + q);
-            pS[q] = ld_row(L.S, e + q);
-            pB[q] = ld_row(L.b, e + q);
-        }
-        pec[0] = ld_crow((e >> 1) + 1);
-        pec[1] = ld_crow((e >> 1) + 2);
-        pw[0] = ld_iw(e);
-        pw[1] = ld_iw(e + 2);
-    };
-    fetch(es);
-    double acc = 0.0;
-    for (int e = es; e <= elast; e += 4) {
-        __syncthreads();
-        // coarse rows e/2+1 and e/2+2 join the e_c ring
-        sec[(((e >> 1) + 1) & 3) * FW + lane] = pec[0];
-        sec[(((e >> 1) + 2) & 3) * FW + lane] = pec[1];
-#pragma unroll
-        for (int k = 0; k < RW - 4; ++k) { rO[k] = rO[k + 4]; rS[k] = rS[k + 4]; rB[k] = rB[k + 4]; }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) { rO[RW - 4 + q] = pO[q]; rS[RW - 4 + q] = pS[q]; rB[RW - 4 + q] = pB[q]; }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int sq = qslot<RW>(e + q) * FW + lane;
-            su[sq] = interp(e + q, pu[q], pw[q >> 1]);
-            sW[sq] = pW[q];
-        }
-        if (e + 4 <= elast) fetch(e + 4);
-        __syncthreads();
-#pragma unroll
-        for (int s = 0; s < NU; ++s) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const int row = (c < 2 ? e - 2 * s : e - 2 * s - 1) + 2 * t;
-                    const int k = row - (e - 2 * NU - 2);
-                    if (col_upd && (i & 1) == (c & 1) && row >= 1 && row <= n)
-                        su[qslot<RW>(row) * FW + lane] =
-                            gs5<T, RW>(su, sW, lane, row, rB[k], rO[k], rS[k], rS[k + 1]);
-                }
-                __syncthreads();
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int row = e - 2 * NU + 1 + t;
-            if (col_own && row >= y0 && row < y1) uout[(size_t)row * ld + i] = su[qslot<RW>(row) * FW + lane];
-        }
-        if (NORM) {
-            // accurate residual of the final rows e-2NU-1 .. e-2NU+2
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int row = e - 2 * NU - 1 + t;
-                const int k = 1 + t;
-                if (col_own && row >= y0 && row < y1 && row >= 1) {
-                    const int r0 = qslot<RW>(row) * FW + lane, rd = qslot<RW>(row - 1) * FW + lane,
-                              ru = qslot<RW>(row + 1) * FW + lane;
-                    const double a[5] = {(double)rS[k], (double)sW[r0], (double)sW[r0 + 1], (double)rS[k + 1],
-                                         (double)rO[k]};
-                    const double x[5] = {(double)su[rd], (double)su[r0 - 1], (double)su[r0 + 1], (double)su[ru],
-                                         (double)su[r0]};
-                    double sacc = rB[k], cc = 0.0, ns, se;
-#pragma unroll
-                    for (int q = 0; q < 5; ++q) {
-                        const double pr = a[q] * x[q];
-                        const double pe = fma(a[q], x[q], -pr);
-                        two_sum(sacc, -pr, ns, se);
-                        sacc = ns;
-                        cc = cc + (se - pe);
-                    }
-                    const double r = sacc + cc;
-                    acc += r * r;
-                }
-            }
-        }
-    }
-    if (NORM) {
-        acc = block_sum(acc);
-        if (threadIdx.x == 0) part[tid] = acc;
-    }
-}
-
-template <typename T, int NU, bool NORM>
-__global__ __launch_bounds__(FW) void k_post4(Lev<T> L, T *__restrict__ uout, Wts<T> C, const T *__restrict__ ec,
-                                               TileGeo G, double *__restrict__ part, const int *stop)
-{
-    int tid, k;
-    if (!tile_work(G, tid, k)) return;
-    if (stopped(stop ? stop + k * G.kstop : stop)) return;
-    L.u += k * G.ksf; L.b += k * G.ksf; uout += k * G.ksf;
-    ec += k * G.ksc;
-    if (NORM) part += k * G.kpart;
-    __shared__ TileLds4<T, NU> S;
-    post_tile4<T, NU, NORM>(L, uout, C, ec, G, tid, part, S);
-}
-
-}  // namespace bmg
-
-namespace bmg {
 
 // ---------------------------------------------- persistent small levels
 // The whole V-cycle below (and including) a small level runs in one workgroup:

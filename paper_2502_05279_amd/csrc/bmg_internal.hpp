@@ -100,7 +100,7 @@ struct bmg_solver {
     int *count = nullptr;       // entries in hist
     int *stop = nullptr;        // stop code of the running solve
     int hist_cap = 0;
-    // graph mode: two plain cycles on the k_postpre schedule, captured once
+    // graph mode: two plain cycles on the cross-cycle schedule, captured once
     // and replayed while the host state (the level buffers) is the one the
     // capture started from and ended in
     hipGraphExec_t pair_exec = nullptr;

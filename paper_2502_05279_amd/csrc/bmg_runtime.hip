@@ -504,12 +504,6 @@ static bool pre_weights_in_pass(const bmg_solver *h, int l, bool nine)
     return BMG_PRE_WEIGHTS_IN_PASS && std::is_same<T, double>::value && !nine && !learned && h->nrhs == 1;
 }
 
-// Rows per step of the fused passes on five-point levels: 4 (k_pre4, k_post4)
-// or 2 (the general k_pre, k_post).
-#ifndef BMG_FIVE_POINT_STEP_ROWS
-#define BMG_FIVE_POINT_STEP_ROWS 2
-#endif
-
 // Tiles of a wave-stream pass on level l of every right-hand side.  An FP64
 // pre pass takes more than 256 registers, one wave per SIMD: the height is the
 // least that leaves all tiles in one round of 1024.  Half-height tiles (a
@@ -559,7 +553,6 @@ bmg_status fused_pre(bmg_solver *h, int l, int nu, const int *stop, bool zero_u 
     const dim3 grid = tile_grid(g), blk(FW);
 #define PRE(NINE, NU) hipLaunchKernelGGL((k_pre<T, NINE, NU>), grid, blk, 0, h->st, F, out, C, Cl, g, stop)
 #define PREW(NINE, NU) hipLaunchKernelGGL((k_pre<T, NINE, NU, true>), grid, blk, 0, h->st, F, out, C, Cl, g, stop)
-#define PRE4(NU) hipLaunchKernelGGL((k_pre4<T, NU>), grid, blk, 0, h->st, F, out, C, Cl, g, stop)
     // Five-point FP64 levels with operator-induced weights compute them in the
     // pass instead of reading the 8 planes (16 of 68 bytes per fine point).
     // Not FP32 levels (their weights are the rounded FP64 ones), not learned
@@ -578,13 +571,16 @@ bmg_status fused_pre(bmg_solver *h, int l, int nu, const int *stop, bool zero_u 
     trace_begin(h, BMG_TRACE_PRE, l,
                 sizeof(T) * ((stencil_planes(nine) + 3.0 * K) * (double)F.n * F.n +
                              (2.0 * K + (wrec ? 0.0 : 8.0)) * (double)Cl.n * Cl.n));
-    if (nine && nu <= 2 && !sq) {
-        const TileGeo gw = wave_tiles(h, l, 4 * nu + 2);
+    if (nu <= 2 && !sq && !wrec) {
+        const TileGeo gw = wave_tiles(h, l, nine ? 4 * nu + 2 : 2 * nu + 2);
         const dim3 wg = tile_grid(gw), wb(64);
-#define PREWAVE(NU) \
-    if (zero_u) hipLaunchKernelGGL((k_pre_wave<T, NU, true>), wg, wb, 0, h->st, F, out, C, Cl, gw, stop); \
-    else hipLaunchKernelGGL((k_pre_wave<T, NU, false>), wg, wb, 0, h->st, F, out, C, Cl, gw, stop)
-        if (nu == 1) { PREWAVE(1); } else { PREWAVE(2); }
+#define PREWAVE(NINE, NU)                                                                                      \
+    do {                                                                                                       \
+        if (zero_u) hipLaunchKernelGGL((k_pre_wave<T, NINE, NU, true>), wg, wb, 0, h->st, F, out, C, Cl, gw, stop); \
+        else hipLaunchKernelGGL((k_pre_wave<T, NINE, NU, false>), wg, wb, 0, h->st, F, out, C, Cl, gw, stop);  \
+    } while (0)
+        if (nine) { if (nu == 1) PREWAVE(true, 1); else PREWAVE(true, 2); }
+        else { if (nu == 1) PREWAVE(false, 1); else PREWAVE(false, 2); }
 #undef PREWAVE
     } else if (sq) {
         const dim3 g2((F.n + T2D - 1) / T2D, (F.n + T2D - 1) / T2D);
@@ -598,15 +594,12 @@ bmg_status fused_pre(bmg_solver *h, int l, int nu, const int *stop, bool zero_u 
         }
     } else if (nine) {
         PRE(true, 3);   // (one and two sweeps run as waves, above)
-    } else if (BMG_FIVE_POINT_STEP_ROWS == 4) {
-        if (nu == 1) PRE4(1); else if (nu == 2) PRE4(2); else PRE4(3);
     } else {
-        if (nu == 1) PRE(false, 1); else if (nu == 2) PRE(false, 2); else PRE(false, 3);
+        PRE(false, 3);
     }
     trace_end(h, BMG_TRACE_PRE, l);
 #undef PRE
 #undef PREW
-#undef PRE4
     LAUNCHCHK();
     std::swap(F.u, ualt<T>(h, l));
     return BMG_OK;
@@ -630,38 +623,31 @@ bmg_status fused_post(bmg_solver *h, int l, int nu, const int *stop, bool norm =
     // halo: the edge lanes are never interpolated (stale from the start), then
     // each sweep invalidates 2 (five-point) or 4 (nine-point) more columns and
     // the fused residual one more
-    const TileGeo g = level_tiles(h, l, nine ? 4 * nu + 2 : 2 * nu + 2);
+    const TileGeo g = wave_tiles(h, l, nine ? 4 * nu + 2 : 2 * nu + 2);
     norm = norm && std::is_same<T, double>::value && g.ntiles <= NPART;
     T *out = ualt<T>(h, l);
-    const dim3 grid = tile_grid(g), blk(FW);
-#define POST(NINE, NU, NORM) \
-    hipLaunchKernelGGL((k_post<T, NINE, NU, NORM>), grid, blk, 0, h->st, F, out, C, (const T *)Cl.u, g, h->part, stop)
-#define POST4(NU, NORM) \
-    hipLaunchKernelGGL((k_post4<T, NU, NORM>), grid, blk, 0, h->st, F, out, C, (const T *)Cl.u, g, h->part, stop)
+    const dim3 grid = tile_grid(g), blk(64);
     // stencil once and b, u read, u written for each right-hand side on the
     // fine level; the coarse correction of each and the 8 weight planes read
     const double K = h->nrhs;
     trace_begin(h, BMG_TRACE_POST, l,
                 sizeof(T) * ((stencil_planes(nine) + 3.0 * K) * (double)F.n * F.n + (K + 8.0) * (double)Cl.n * Cl.n));
-    if (nine && !norm) {
-        const TileGeo gw = wave_tiles(h, l, 4 * nu + 2);
-        const dim3 wg = tile_grid(gw), wb(64);
-        if (nu == 1)
-            hipLaunchKernelGGL((k_post_wave<T, 1>), wg, wb, 0, h->st, F, out, C, (const T *)Cl.u, gw, stop);
-        else
-            hipLaunchKernelGGL((k_post_wave<T, 2>), wg, wb, 0, h->st, F, out, C, (const T *)Cl.u, gw, stop);
-    } else if (!nine && BMG_FIVE_POINT_STEP_ROWS == 4) {
-        if (norm) { if (nu == 1) POST4(1, true); else POST4(2, true); }
-        else { if (nu == 1) POST4(1, false); else POST4(2, false); }
-    } else if (norm) {
-        if (nine) { if (nu == 1) POST(true, 1, true); else POST(true, 2, true); }
-        else { if (nu == 1) POST(false, 1, true); else POST(false, 2, true); }
-    } else {
-        if (nu == 1) POST(false, 1, false); else POST(false, 2, false);
-    }
+#define POSTWAVE(NINE, NU)                                                                                       \
+    do {                                                                                                         \
+        if constexpr (std::is_same<T, double>::value) {                                                          \
+            if (norm) {                                                                                          \
+                hipLaunchKernelGGL((k_post_wave<T, NINE, NU, true>), grid, blk, 0, h->st, F, out, C,             \
+                                   (const T *)Cl.u, g, h->part, stop);                                           \
+                break;                                                                                           \
+            }                                                                                                    \
+        }                                                                                                        \
+        hipLaunchKernelGGL((k_post_wave<T, NINE, NU, false>), grid, blk, 0, h->st, F, out, C, (const T *)Cl.u, g, \
+                           h->part, stop);                                                                       \
+    } while (0)
+    if (nine) { if (nu == 1) POSTWAVE(true, 1); else POSTWAVE(true, 2); }
+    else { if (nu == 1) POSTWAVE(false, 1); else POSTWAVE(false, 2); }
+#undef POSTWAVE
     trace_end(h, BMG_TRACE_POST, l);
-#undef POST
-#undef POST4
     LAUNCHCHK();
     std::swap(F.u, ualt<T>(h, l));
     if (norm) h->norm_parts = g.ntiles;
@@ -728,7 +714,7 @@ bmg_status fused_vcycle32(bmg_solver *h, const int *stop) { return fused_cycle_f
 static bool post_update_fusable(const bmg_solver *h)
 {
     return h->opt.kernels == BMG_KERNELS_FUSED && h->opt.smoother == BMG_SMOOTH_POINT && !h->nine[0] &&
-           BMG_FIVE_POINT_STEP_ROWS == 2 && h->nrhs == 1 && h->nlev >= 2 && h->opt.nu2 >= 1 && h->opt.nu2 <= 2;
+           h->nrhs == 1 && h->nlev >= 2 && h->opt.nu2 >= 1 && h->opt.nu2 <= 2;
 }
 
 static bool ir_fusable(const bmg_solver *h)
@@ -1224,41 +1210,25 @@ static bmg_status cycle_and_norm(bmg_solver *h, double tol, int maxc, double ref
     return resnorm_dd(h, L.b, L.u, nullptr, 0, nullptr, S_SUMSQ, true, tol, maxc, refine);
 }
 
-// Rows per tile of k_postpre: two of its 72 KiB workgroups share a CU, so
-// the fewest warm-up rows with all tiles in one round of 512 (148 rows at
-// 4095^2: 18 strips x 28 tiles).
-static int postpre_tile_rows(const bmg_solver *h, int n, int hx)
-{
-    if (h->opt.tile_rows > 0) return h->opt.tile_rows;
-    const int useful = FW - 2 * hx;
-    const int strips = (n + useful - 1) / useful;
-    const int rows = std::max(1, 512 / strips);
-    return ((n + rows - 1) / rows + 1) & ~1;
-}
-
-// Tiles of k_postpre on the fine level: halo for the interpolation edge, the
-// sweeps, the residual and the restriction.
-static TileGeo postpre_geo(const bmg_solver *h)
-{
-    const int hx = 2 * (h->opt.nu1 + 1) + 4;
-    return tile_geo(h->L[0].n, hx, postpre_tile_rows(h, h->L[0].n, hx));
-}
+// Tiles of k_postpre_wave on the fine level: halo for the interpolation edge,
+// the sweeps, the residual and the restriction.
+static TileGeo postpre_geo(const bmg_solver *h) { return wave_tiles(h, 0, 2 * (h->opt.nu1 + 1) + 4); }
 
 // Plain FP64 cycles where the fine post pass of each cycle runs together with
-// the fine pre pass of the next (k_postpre): an FP64 five-point fine level
+// the fine pre pass of the next (k_postpre_wave): an FP64 five-point fine level
 // with one right-hand side (operator-induced or learned weights: the pass
 // reads the stored ones), one post sweep and one or two pre sweeps, and at
 // most NPART tiles (their norm partials).
 static bool postpre_ok(const bmg_solver *h)
 {
     return !h->f32 && h->opt.kernels == BMG_KERNELS_FUSED && h->opt.smoother == BMG_SMOOTH_POINT && !h->nine[0] &&
-           BMG_FIVE_POINT_STEP_ROWS == 2 && h->nlev >= 2 && h->opt.nu2 == 1 && (h->opt.nu1 == 1 || h->opt.nu1 == 2) &&
+           h->nlev >= 2 && h->opt.nu2 == 1 && (h->opt.nu1 == 1 || h->opt.nu1 == 2) &&
            h->nrhs == 1 && postpre_geo(h).ntiles <= NPART;
 }
 
-// One plain FP64 cycle and its recorded norm on the k_postpre schedule.
+// One plain FP64 cycle and its recorded norm on the cross-cycle schedule.
 // *pending: the fine pre pass of this cycle already ran inside the last
-// k_postpre, its iterate in L0.r (free on this schedule).  Level 0 rotates
+// k_postpre_wave, its iterate in L0.r (free on this schedule).  Level 0 rotates
 // three buffers: the pass reads u' and writes u_k and the next u''; level 1
 // takes u_c = 0 in its second buffer, since e_c is read until the pass ends.
 static bmg_status cycle_and_norm_pp(bmg_solver *h, double tol, int maxc, double refine, bool *pending)
@@ -1279,16 +1249,16 @@ static bmg_status cycle_and_norm_pp(bmg_solver *h, double tol, int maxc, double 
     Lev<double> Fin = F;
     Fin.u = in;
     const TileGeo g = postpre_geo(h);
-    const dim3 grid = tile_grid(g), blk(FW);
+    const dim3 grid = tile_grid(g), blk(64);
     const double nf = (double)F.n * F.n, ncc = (double)C1.n * C1.n;
     // stencil, b and u' read, u_k and u'' written; e_c and the 8 weight planes
     // read, b_c and u_c written
     trace_begin(h, BMG_TRACE_POSTPRE, 0, 8.0 * ((stencil_planes(false) + 4.0) * nf + 11.0 * ncc));
     if (nb == 1)
-        hipLaunchKernelGGL((k_postpre<1>), grid, blk, 0, h->st, Fin, out[0], out[1], h->C[0], (const double *)C1.u, C1,
+        hipLaunchKernelGGL((k_postpre_wave<1>), grid, blk, 0, h->st, Fin, out[0], out[1], h->C[0], (const double *)C1.u, C1,
                            h->ualt[1], g, h->part, h->stop);
     else
-        hipLaunchKernelGGL((k_postpre<2>), grid, blk, 0, h->st, Fin, out[0], out[1], h->C[0], (const double *)C1.u, C1,
+        hipLaunchKernelGGL((k_postpre_wave<2>), grid, blk, 0, h->st, Fin, out[0], out[1], h->C[0], (const double *)C1.u, C1,
                            h->ualt[1], g, h->part, h->stop);
     trace_end(h, BMG_TRACE_POSTPRE, 0);
     LAUNCHCHK();
@@ -1318,7 +1288,7 @@ static std::vector<void *> cycle_state(const bmg_solver *h)
     return v;
 }
 
-// Two plain cycles on the k_postpre schedule (a pre pass pending) as one
+// Two plain cycles on the cross-cycle schedule (a pre pass pending) as one
 // graph launch.  On the k_postpre schedule the level buffers rotate with
 // period two, so a graph captured from one state leaves the host state as it
 // found it and can be replayed for every later pair; the capture itself runs

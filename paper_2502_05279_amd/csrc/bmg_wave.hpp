@@ -1,4 +1,4 @@
-// Fused passes of the nine-point levels as streams of single waves.
+// Fused passes as streams of single waves.
 //
 // A wave owns a strip of 128 grid columns, two neighbours (even, odd) per lane,
 // and a block of rows, and streams upward through it two rows at a time like
@@ -13,8 +13,10 @@
 // of the iterate goes through LDS, and every lane has a point to update in
 // every colour phase (with one column per lane half of them idle).
 //
-// Measured in a 4095^2 solve (FP64, V(2,1)): 2047^2 pre 142 -> 81 us, post
-// 97 -> 71, 1023^2 66 -> 32 and 34 -> 25.  The 2047^2 passes are bound by
+// Measured in a 4095^2 solve (FP64, V(2,1)), against the workgroup passes:
+// nine-point 2047^2 pre 142 -> 81 us, post 97 -> 71, 1023^2 66 -> 32 and
+// 34 -> 25; the cross-cycle pass of the fine level 444 -> 295, 1.45 GB at the
+// 4.9 TB/s of a copy.  The 2047^2 passes are bound by
 // memory: 443 MB for the pre pass, 4.9 TB/s, while both neighbours of a tile
 // streamed the same way (91 us); streaming every other row of tiles downward
 // lets two tiles share the rows at their border.
@@ -64,19 +66,20 @@ struct Pair {
     typedef T vec __attribute__((ext_vector_type(2)));
 };
 
-// LDS ring of a wave: W, SW, NW, RX rows of 128 columns (and one element that
-// the last lane's read of "the next column" may touch).
-template <typename T, int NU>
+// LDS ring of a wave: W and on nine-point levels SW, NW, RX rows of 128
+// columns (and two elements that the last lane's read of "the next column"
+// may touch).
+template <typename T, bool NINE, int NU>
 struct WaveLds {
     static constexpr int RX = 2 * NU + 6;
-    T W[RX * WAVE_COLS], SW[RX * WAVE_COLS], NW[RX * WAVE_COLS + 2];
+    T W[RX * WAVE_COLS], SW[NINE ? RX * WAVE_COLS : 0], NW[NINE ? RX * WAVE_COLS : 0], pad[2];
 };
 
 // What both passes share: geometry, the ring and the point update.  A tile is
 // streamed upward (DIR = 1) or downward (DIR = -1): the colours' order, even
 // rows before odd ones, is the same seen from either side.  Slot of row
 // e + DIR d at turn M of the unrolled loop (e = es + 2 M DIR mod RX).
-template <typename T, int NU, int DIR>
+template <typename T, bool NINE, int NU, int DIR>
 struct WaveTile {
     static constexpr int RX = 2 * NU + 6;
     using V = typename Pair<T>::vec;
@@ -88,7 +91,7 @@ struct WaveTile {
     int n, ld, i0, i0c, y0, y1;
     bool in0, in1, own;        // columns interior, pair owned
 
-    __device__ __forceinline__ void place(const Lev<T> &L, const TileGeo &G, int tid, WaveLds<T, NU> &lds)
+    __device__ __forceinline__ void place(const Lev<T> &L, const TileGeo &G, int tid, WaveLds<T, NINE, NU> &lds)
     {
         n = L.n;
         ld = L.ld;
@@ -111,12 +114,33 @@ struct WaveTile {
     {
         return *reinterpret_cast<const V *>(a + (size_t)rowc(row) * ld + i0c);
     }
-    template <int SL>
-    __device__ __forceinline__ void put_couplings(V w, V sw, V nw)
+    // the couplings of a row that go through LDS
+    struct Couplings {
+        V w, sw, nw;
+    };
+    __device__ __forceinline__ Couplings couplings(const Lev<T> &L, int row) const
     {
-        *reinterpret_cast<V *>(sW + SL * WAVE_COLS) = w;
-        *reinterpret_cast<V *>(sSW + SL * WAVE_COLS) = sw;
-        *reinterpret_cast<V *>(sNW + SL * WAVE_COLS) = nw;
+        Couplings c;
+        c.w = load(L.W, row);
+        if constexpr (NINE) {
+            c.sw = load(L.SW, row);
+            c.nw = load(L.NW, row);
+        }
+        return c;
+    }
+    __device__ __forceinline__ void next_couplings(const Lev<T> &L, int e, Couplings (&c)[2]) const
+    {
+        c[0] = couplings(L, e);
+        c[1] = couplings(L, e + DIR);
+    }
+    template <int SL>
+    __device__ __forceinline__ void put_couplings(const Couplings &c)
+    {
+        *reinterpret_cast<V *>(sW + SL * WAVE_COLS) = c.w;
+        if constexpr (NINE) {
+            *reinterpret_cast<V *>(sSW + SL * WAVE_COLS) = c.sw;
+            *reinterpret_cast<V *>(sNW + SL * WAVE_COLS) = c.nw;
+        }
     }
     // b, O, S of a row into its slot
     template <int SL>
@@ -140,6 +164,15 @@ struct WaveTile {
     template <int C, int SD, int S0, int SU>
     __device__ __forceinline__ T offdiag() const
     {
+        if constexpr (!NINE) {
+            const T uw = C ? u[S0][0] : from_west(u[S0][1]), ue = C ? from_east(u[S0][0]) : u[S0][1];
+            T s = b[S0][C];
+            s -= S[S0][C] * u[SD][C];
+            s -= sW[S0 * WAVE_COLS + C] * uw;
+            s -= sW[S0 * WAVE_COLS + C + 1] * ue;
+            s -= S[SU][C] * u[SU][C];
+            return s;
+        }
         const T uwd = C ? u[SD][0] : from_west(u[SD][1]), ued = C ? from_east(u[SD][0]) : u[SD][1];
         const T uw0 = C ? u[S0][0] : from_west(u[S0][1]), ue0 = C ? from_east(u[S0][0]) : u[S0][1];
         const T uwu = C ? u[SU][0] : from_west(u[SU][1]), ueu = C ? from_east(u[SU][0]) : u[SU][1];
@@ -168,29 +201,73 @@ struct WaveTile {
         s -= O[S0][C] * u[S0][C];
         return s;
     }
+    // square of the accurate residual at column C of the row in slot S0 (the
+    // terms of post_tile)
+    template <int C, int SD, int S0, int SU>
+    __device__ __forceinline__ double resid2() const
+    {
+        constexpr int N = NINE ? 9 : 5;
+        double a[N], x[N];
+        int q = 0;
+        auto term = [&](double ai, double xi) {
+            a[q] = ai;
+            x[q++] = xi;
+        };
+        if constexpr (NINE) term(sSW[S0 * WAVE_COLS + C], C ? u[SD][0] : from_west(u[SD][1]));
+        term(S[S0][C], u[SD][C]);
+        if constexpr (NINE) term(sNW[SD * WAVE_COLS + C + 1], C ? from_east(u[SD][0]) : u[SD][1]);
+        term(sW[S0 * WAVE_COLS + C], C ? u[S0][0] : from_west(u[S0][1]));
+        term(sW[S0 * WAVE_COLS + C + 1], C ? from_east(u[S0][0]) : u[S0][1]);
+        if constexpr (NINE) term(sNW[S0 * WAVE_COLS + C], C ? u[SU][0] : from_west(u[SU][1]));
+        term(S[SU][C], u[SU][C]);
+        if constexpr (NINE) term(sSW[SU * WAVE_COLS + C + 1], C ? from_east(u[SU][0]) : u[SU][1]);
+        term(O[S0][C], u[S0][C]);
+        double s = b[S0][C], cc = 0.0, ns, se;
+#pragma unroll
+        for (int t = 0; t < N; ++t) {
+            const double pr = a[t] * x[t];
+            const double pe = fma(a[t], x[t], -pr);
+            two_sum(s, -pr, ns, se);
+            s = ns;
+            cc = cc + (se - pe);
+        }
+        const double r = s + cc;
+        return r * r;
+    }
+    // the owned points of row e + DIR D (in window row D) into the norm's sum
+    template <int M, int D>
+    __device__ __forceinline__ void norm(int row, double &acc) const
+    {
+        constexpr int SD = at<M>(D - DIR), S0 = at<M>(D), SU = at<M>(D + DIR);
+        const double q0 = resid2<0, SD, S0, SU>(), q1 = resid2<1, SD, S0, SU>();
+        if (own && row >= y0 && row < y1) {
+            acc += q0;
+            acc += q1;
+        }
+    }
     // sweep s of the step: colours 0, 1 on the even row 2s behind e, then 2, 3
     // on the odd row behind that
-    template <int M, int SW_ = 0>
+    template <int M, int SW_, int END>
     __device__ __forceinline__ void sweeps()
     {
-        if constexpr (SW_ < NU) {
+        if constexpr (SW_ < END) {
             relax<M, -2 * SW_, 0>();
             relax<M, -2 * SW_, 1>();
             relax<M, -2 * SW_ - 1, 0>();
             relax<M, -2 * SW_ - 1, 1>();
-            sweeps<M, SW_ + 1>();
+            sweeps<M, SW_ + 1, END>();
         }
     }
-    // the last sweep's two rows are final: the owned ones go out
-    template <int M>
+    // the two rows of sweep SW_ are final: the owned ones go out
+    template <int M, int SW_ = NU - 1>
     __device__ __forceinline__ void write(T *out, int e) const
     {
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            const int row = e + DIR * (2 - 2 * NU - t);
+            const int row = e - DIR * (2 * SW_ + t);
             if (row < y0 || row >= y1 || !own) continue;
             T *p = out + (size_t)row * ld + i0;
-            const T *v = u[at<M>(2 - 2 * NU - t)];
+            const T *v = u[at<M>(-2 * SW_ - t)];
             if (i0 > 0) *reinterpret_cast<V *>(p) = V{v[0], v[1]};
             else p[1] = v[1];
         }
@@ -204,9 +281,9 @@ __device__ __forceinline__ bool wave_up(const TileGeo &G, int tid) { return !((t
 
 // nu sweeps, residual and restriction (results as pre_tile).  zero_u: the
 // iterate is known to be zero (a coarse level's first visit in a cycle).
-template <typename T, int NU, int DIR>
-struct WavePre : WaveTile<T, NU, DIR> {
-    using B = WaveTile<T, NU, DIR>;
+template <typename T, bool NINE, int NU, int DIR>
+struct WavePre : WaveTile<T, NINE, NU, DIR> {
+    using B = WaveTile<T, NINE, NU, DIR>;
     using V = typename B::V;
     static constexpr int RX = B::RX;
     T pr0[2], pr1[2];          // residual of the coarse row's f and of the odd row behind it
@@ -215,7 +292,7 @@ struct WavePre : WaveTile<T, NU, DIR> {
     int I, nc;
 
     __device__ __forceinline__ void run(const Lev<T> &L, T *__restrict__ uout, const Wts<T> &Cw, const Lev<T> &Cl,
-                                        const TileGeo &G, int tid, WaveLds<T, NU> &lds, bool zero_u)
+                                        const TileGeo &G, int tid, WaveLds<T, NINE, NU> &lds, bool zero_u)
     {
         B::place(L, G, tid, lds);
         nc = Cl.n;
@@ -228,13 +305,13 @@ struct WavePre : WaveTile<T, NU, DIR> {
         const int elast = DIR > 0 ? 2 * ((y1 - 1) >> 1) + 2 * NU + 2 : 2 * ((y0 + 1) >> 1) - 2 * NU - 2;
         // the rows behind es, and the request of es and the next
         fill<-2 * NU - 2>(L, es, zero_u);
-        V w0 = B::load(L.W, es), w1 = B::load(L.W, es + DIR), a0 = B::load(L.SW, es), a1 = B::load(L.SW, es + DIR);
-        V c0 = B::load(L.NW, es), c1 = B::load(L.NW, es + DIR);
+        typename B::Couplings c[2];
+        B::next_couplings(L, es, c);
         want<0>(L, es, zero_u);
         weights(Cw, (es - DIR * (2 * NU + 2)) >> 1);
         pr0[0] = pr0[1] = pr1[0] = pr1[1] = (T)0;
         for (int e = es; DIR * (elast - e) >= 0; e += DIR * RX)
-            turn<0>(L, uout, Cw, Cl, e, elast, zero_u, w0, w1, a0, a1, c0, c1);
+            turn<0>(L, uout, Cw, Cl, e, elast, zero_u, c);
     }
 
 private:
@@ -248,7 +325,7 @@ private:
             this->u[SL][0] = vu.x;
             this->u[SL][1] = vu.y;
             B::template request<SL>(L, row);
-            B::template put_couplings<SL>(B::load(L.W, row), B::load(L.SW, row), B::load(L.NW, row));
+            B::template put_couplings<SL>(B::couplings(L, row));
             B::template arrived<SL>(row);
             fill<D + 1>(L, es, zero_u);
         }
@@ -279,14 +356,14 @@ private:
     }
     template <int M>
     __device__ __forceinline__ void turn(const Lev<T> &L, T *__restrict__ uout, const Wts<T> &Cw, const Lev<T> &Cl,
-                                         int e, int elast, bool zero_u, V &w0, V &w1, V &a0, V &a1, V &c0, V &c1)
+                                         int e, int elast, bool zero_u, typename B::Couplings (&c)[2])
     {
         if constexpr (M < RX / 2) {
             if (DIR * (e - elast) > 0) return;
             constexpr int S0 = B::template at<M>(0), S1 = B::template at<M>(1);
             wave_lds_order();
-            B::template put_couplings<S0>(w0, a0, c0);
-            B::template put_couplings<S1>(w1, a1, c1);
+            B::template put_couplings<S0>(c[0]);
+            B::template put_couplings<S1>(c[1]);
             wave_lds_order();
             B::template arrived<S0>(e);
             B::template arrived<S1>(e + DIR);
@@ -295,12 +372,10 @@ private:
             for (int q = 0; q < 8; ++q) wc[q] = w[q];
             // the next step's data
             const int en2 = e + 2 * DIR;
-            w0 = B::load(L.W, en2); w1 = B::load(L.W, en2 + DIR);
-            a0 = B::load(L.SW, en2); a1 = B::load(L.SW, en2 + DIR);
-            c0 = B::load(L.NW, en2); c1 = B::load(L.NW, en2 + DIR);
+            B::next_couplings(L, en2, c);
             want<(M + 1) % (RX / 2)>(L, en2, zero_u);
             weights(Cw, (en2 - DIR * (2 * NU + 2)) >> 1);
-            B::template sweeps<M>();
+            B::template sweeps<M, 0, NU>();
             B::template write<M>(uout, e);
             // residual of the two rows behind the last sweep, restriction of f
             T r0[2], r1[2];
@@ -313,7 +388,7 @@ private:
             const T *rd = DIR > 0 ? pr1 : r1, *ru = DIR > 0 ? r1 : pr1;
             const T dw = from_west(rd[1]), mw = from_west(pr0[1]), uw = from_west(ru[1]);
             if (rest && J >= 1 && J <= nc && f >= this->y0 && f < this->y1) {
-                const size_t c = (size_t)J * Cw.ld + I;
+                const size_t p = (size_t)J * Cw.ld + I;
                 T s = wc[0] * dw;
                 s = s + wc[1] * rd[0];
                 s = s + wc[2] * rd[1];
@@ -323,17 +398,17 @@ private:
                 s = s + wc[5] * uw;
                 s = s + wc[6] * ru[0];
                 s = s + wc[7] * ru[1];
-                Cl.b[c] = s;
-                Cl.u[c] = (T)0;
+                Cl.b[p] = s;
+                Cl.u[p] = (T)0;
             }
             pr0[0] = r0[0]; pr0[1] = r0[1];
             pr1[0] = r1[0]; pr1[1] = r1[1];
-            turn<M + 1>(L, uout, Cw, Cl, en2, elast, zero_u, w0, w1, a0, a1, c0, c1);
+            turn<M + 1>(L, uout, Cw, Cl, en2, elast, zero_u, c);
         }
     }
 };
 
-template <typename T, int NU, bool ZU>
+template <typename T, bool NINE, int NU, bool ZU>
 __global__ __launch_bounds__(64, 1) void k_pre_wave(Lev<T> L, T *__restrict__ uout, Wts<T> C, Lev<T> Cl, TileGeo G,
                                                     const int *stop)
 {
@@ -342,47 +417,25 @@ __global__ __launch_bounds__(64, 1) void k_pre_wave(Lev<T> L, T *__restrict__ uo
     if (stopped(stop ? stop + k * G.kstop : stop)) return;
     L.u += k * G.ksf; L.b += k * G.ksf; uout += k * G.ksf;
     Cl.u += k * G.ksc; Cl.b += k * G.ksc;
-    __shared__ WaveLds<T, NU> S;
+    __shared__ WaveLds<T, NINE, NU> S;
     if (wave_up(G, tid)) {
-        WavePre<T, NU, 1> P;
+        WavePre<T, NINE, NU, 1> P;
         P.run(L, uout, C, Cl, G, tid, S, ZU);
     } else {
-        WavePre<T, NU, -1> P;
+        WavePre<T, NINE, NU, -1> P;
         P.run(L, uout, C, Cl, G, tid, S, ZU);
     }
 }
 
-// Interpolation and nu sweeps (results as post_tile without the norm).
-template <typename T, int NU, int DIR>
-struct WavePost : WaveTile<T, NU, DIR> {
-    using B = WaveTile<T, NU, DIR>;
+// A tile whose rows enter as u + P e_c.
+template <typename T, bool NINE, int NU, int DIR>
+struct WaveInterp : WaveTile<T, NINE, NU, DIR> {
+    using B = WaveTile<T, NINE, NU, DIR>;
     using V = typename B::V;
-    static constexpr int RX = B::RX;
     T e0, w[8];                // e_c of row e / 2 at I; the next step's weights
     T en;                      // e_c of the coarse row after it
     int Ic, nc, ldc;
 
-    __device__ __forceinline__ void run(const Lev<T> &L, T *__restrict__ uout, const Wts<T> &Cw,
-                                        const T *__restrict__ ec, const TileGeo &G, int tid, WaveLds<T, NU> &lds)
-    {
-        B::place(L, G, tid, lds);
-        nc = (this->n - 1) >> 1;
-        ldc = Cw.ld;
-        Ic = this->i0c >> 1;
-        const int y0 = this->y0, y1 = this->y1;
-        const int es = DIR > 0 ? (y0 - 2 * NU + 1) & ~1 : (y1 - 1 + 2 * NU) & ~1;
-        const int elast = DIR > 0 ? (y1 - 2 + 2 * NU) & ~1 : y0 + 1 - 2 * NU;   // writes the last owned row (y0 is odd)
-        e0 = crow(ec, (es - DIR * (2 * NU + 2)) >> 1);
-        fill<-2 * NU - 2>(L, Cw, ec, es);
-        V w0 = B::load(L.W, es), w1 = B::load(L.W, es + DIR), a0 = B::load(L.SW, es), a1 = B::load(L.SW, es + DIR);
-        V c0 = B::load(L.NW, es), c1 = B::load(L.NW, es + DIR);
-        want<0>(L, es);
-        en = crow(ec, (es >> 1) + DIR);
-        weights(Cw, es);
-        for (int e = es; DIR * (elast - e) >= 0; e += DIR * RX) turn<0>(L, uout, Cw, ec, e, elast, w0, w1, a0, a1, c0, c1);
-    }
-
-private:
     __device__ __forceinline__ T crow(const T *ec, int J) const
     {
         return ec[(size_t)(J >= 0 && J <= nc + 1 ? J : nc + 1) * ldc + Ic];
@@ -432,21 +485,36 @@ private:
             }
         }
     }
+    // place() and the rows behind es, interpolated; es and the next requested
+    __device__ __forceinline__ void begin(const Lev<T> &L, const Wts<T> &Cw, const T *ec, int es,
+                                          typename B::Couplings (&c)[2])
+    {
+        e0 = crow(ec, (es - DIR * (2 * NU + 2)) >> 1);
+        fill<-2 * NU - 2>(L, Cw, ec, es);
+        B::next_couplings(L, es, c);
+        want<0>(L, es);
+        en = crow(ec, (es >> 1) + DIR);
+        weights(Cw, es);
+    }
+    __device__ __forceinline__ void coarse(const Wts<T> &Cw)
+    {
+        nc = (this->n - 1) >> 1;
+        ldc = Cw.ld;
+        Ic = this->i0c >> 1;
+    }
     template <int D>
     __device__ __forceinline__ void fill(const Lev<T> &L, const Wts<T> &Cw, const T *ec, int es)
     {
         if constexpr (D < 0) {
             constexpr int S0 = B::template at<0>(D), S1 = B::template at<0>(D + 1);
             const int row = es + DIR * D;
-            const V u0 = B::load(L.u, row), u1 = B::load(L.u, row + DIR);
-            this->u[S0][0] = u0.x; this->u[S0][1] = u0.y;
-            this->u[S1][0] = u1.x; this->u[S1][1] = u1.y;
+            request_u<S0, S1>(L, row);
             const T e1 = crow(ec, (row >> 1) + DIR);
             weights(Cw, row);
             B::template request<S0>(L, row);
             B::template request<S1>(L, row + DIR);
-            B::template put_couplings<S0>(B::load(L.W, row), B::load(L.SW, row), B::load(L.NW, row));
-            B::template put_couplings<S1>(B::load(L.W, row + DIR), B::load(L.SW, row + DIR), B::load(L.NW, row + DIR));
+            B::template put_couplings<S0>(B::couplings(L, row));
+            B::template put_couplings<S1>(B::couplings(L, row + DIR));
             correct<S0, S1>(row, e0, e1);
             B::template arrived<S0>(row);
             B::template arrived<S1>(row + DIR);
@@ -454,63 +522,249 @@ private:
             fill<D + 2>(L, Cw, ec, es);
         }
     }
+    template <int S0, int S1>
+    __device__ __forceinline__ void request_u(const Lev<T> &L, int row)
+    {
+        const V u0 = B::load(L.u, row), u1 = B::load(L.u, row + DIR);
+        this->u[S0][0] = u0.x; this->u[S0][1] = u0.y;
+        this->u[S1][0] = u1.x; this->u[S1][1] = u1.y;
+    }
     template <int M>
     __device__ __forceinline__ void want(const Lev<T> &L, int e)
     {
         constexpr int S0 = B::template at<M>(0), S1 = B::template at<M>(1);
-        const V u0 = B::load(L.u, e), u1 = B::load(L.u, e + DIR);
-        this->u[S0][0] = u0.x; this->u[S0][1] = u0.y;
-        this->u[S1][0] = u1.x; this->u[S1][1] = u1.y;
+        request_u<S0, S1>(L, e);
         B::template request<S0>(L, e);
         B::template request<S1>(L, e + DIR);
     }
+    // the rows of step e take their places, interpolated, and the next step's
+    // data is requested
+    template <int M>
+    __device__ __forceinline__ void enter(const Lev<T> &L, const Wts<T> &Cw, const T *ec, int e,
+                                          typename B::Couplings (&c)[2])
+    {
+        constexpr int S0 = B::template at<M>(0), S1 = B::template at<M>(1);
+        B::template arrived<S0>(e);
+        B::template arrived<S1>(e + DIR);
+        correct<S0, S1>(e, e0, en);
+        e0 = en;
+        B::next_couplings(L, e + 2 * DIR, c);
+        want<(M + 1) % (B::RX / 2)>(L, e + 2 * DIR);
+        en = crow(ec, (e >> 1) + 2 * DIR);
+        weights(Cw, e + 2 * DIR);
+    }
+};
+
+__device__ __forceinline__ void wave_sum_to(double acc, double *out)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
+    if (threadIdx.x == 0) *out = acc;
+}
+
+// Interpolation and nu sweeps, with NORM also the tile's sum of squares of the
+// accurate residual into part[tid] (results as post_tile).
+template <typename T, bool NINE, int NU, int DIR, bool NORM>
+struct WavePost : WaveInterp<T, NINE, NU, DIR> {
+    using A = WaveInterp<T, NINE, NU, DIR>;
+    using B = typename A::B;
+    static constexpr int RX = B::RX;
+    double acc;
+
+    __device__ __forceinline__ void run(const Lev<T> &L, T *__restrict__ uout, const Wts<T> &Cw,
+                                        const T *__restrict__ ec, const TileGeo &G, int tid,
+                                        double *__restrict__ part, WaveLds<T, NINE, NU> &lds)
+    {
+        B::place(L, G, tid, lds);
+        A::coarse(Cw);
+        const int y0 = this->y0, y1 = this->y1;
+        // the last step writes the last owned row (downward y0, which is odd),
+        // with the norm it also has the row beyond it
+        const int es = DIR > 0 ? (y0 - 2 * NU + 1) & ~1 : (y1 - 1 + 2 * NU) & ~1;
+        const int elast = DIR > 0 ? (y1 - (NORM ? 1 : 2) + 2 * NU) & ~1 : y0 + 1 - 2 * NU;
+        typename B::Couplings c[2];
+        A::begin(L, Cw, ec, es, c);
+        acc = 0.0;
+        for (int e = es; DIR * (elast - e) >= 0; e += DIR * RX) turn<0>(L, uout, Cw, ec, e, elast, c);
+        if (NORM) wave_sum_to(acc, part + tid);
+    }
+
+private:
     template <int M>
     __device__ __forceinline__ void turn(const Lev<T> &L, T *__restrict__ uout, const Wts<T> &Cw,
-                                         const T *__restrict__ ec, int e, int elast, V &w0, V &w1, V &a0, V &a1,
-                                         V &c0, V &c1)
+                                         const T *__restrict__ ec, int e, int elast, typename B::Couplings (&c)[2])
     {
         if constexpr (M < RX / 2) {
             if (DIR * (e - elast) > 0) return;
-            constexpr int S0 = B::template at<M>(0), S1 = B::template at<M>(1);
             wave_lds_order();
-            B::template put_couplings<S0>(w0, a0, c0);
-            B::template put_couplings<S1>(w1, a1, c1);
+            B::template put_couplings<B::template at<M>(0)>(c[0]);
+            B::template put_couplings<B::template at<M>(1)>(c[1]);
             wave_lds_order();
-            B::template arrived<S0>(e);
-            B::template arrived<S1>(e + DIR);
-            correct<S0, S1>(e, e0, en);
-            e0 = en;
-            // the next step's data
-            const int en2 = e + 2 * DIR;
-            w0 = B::load(L.W, en2); w1 = B::load(L.W, en2 + DIR);
-            a0 = B::load(L.SW, en2); a1 = B::load(L.SW, en2 + DIR);
-            c0 = B::load(L.NW, en2); c1 = B::load(L.NW, en2 + DIR);
-            want<(M + 1) % (RX / 2)>(L, en2);
-            en = crow(ec, (e >> 1) + 2 * DIR);
-            weights(Cw, en2);
-            B::template sweeps<M>();
+            A::template enter<M>(L, Cw, ec, e, c);
+            B::template sweeps<M, 0, NU>();
             B::template write<M>(uout, e);
-            turn<M + 1>(L, uout, Cw, ec, en2, elast, w0, w1, a0, a1, c0, c1);
+            if constexpr (NORM) {
+                B::template norm<M, 1 - 2 * NU>(e + DIR * (1 - 2 * NU), acc);
+                B::template norm<M, -2 * NU>(e - DIR * 2 * NU, acc);
+            }
+            turn<M + 1>(L, uout, Cw, ec, e + 2 * DIR, elast, c);
         }
     }
 };
 
-template <typename T, int NU>
+template <typename T, bool NINE, int NU, bool NORM>
 __global__ __launch_bounds__(64, 1) void k_post_wave(Lev<T> L, T *__restrict__ uout, Wts<T> C,
-                                                     const T *__restrict__ ec, TileGeo G, const int *stop)
+                                                     const T *__restrict__ ec, TileGeo G, double *__restrict__ part,
+                                                     const int *stop)
 {
     int tid, k;
     if (!tile_work(G, tid, k)) return;
     if (stopped(stop ? stop + k * G.kstop : stop)) return;
     L.u += k * G.ksf; L.b += k * G.ksf; uout += k * G.ksf;
     ec += k * G.ksc;
-    __shared__ WaveLds<T, NU> S;
+    if (NORM) part += k * G.kpart;
+    __shared__ WaveLds<T, NINE, NU> S;
     if (wave_up(G, tid)) {
-        WavePost<T, NU, 1> P;
-        P.run(L, uout, C, ec, G, tid, S);
+        WavePost<T, NINE, NU, 1, NORM> P;
+        P.run(L, uout, C, ec, G, tid, part, S);
     } else {
-        WavePost<T, NU, -1> P;
-        P.run(L, uout, C, ec, G, tid, S);
+        WavePost<T, NINE, NU, -1, NORM> P;
+        P.run(L, uout, C, ec, G, tid, part, S);
+    }
+}
+
+// --------------------------------- post pass and the next cycle's pre pass
+// The fine level's post pass of cycle k and its pre pass of cycle k + 1 as one
+// pass (FP64, five-point level, one right-hand side, one post sweep, NB pre
+// sweeps), so the fine level's arrays are read and written once per cycle
+// (78 bytes per point where the two passes take 118): rows enter as u' + P e_c,
+// sweep 0 gives the cycle's result u_k (written, and its accurate residual's
+// squares summed: rows e, e - 1, e - 2, e - 3 all hold u_k between sweep 0 and
+// sweep 1 of a step), sweeps 1 .. NB give u'' (written), whose residual is
+// restricted.  The weights the interpolation loads stay in an LDS ring until
+// the restriction of their coarse row, four and five steps later (read again
+// from memory they cost 9 bytes per fine point, the caches no longer having
+// them).  u_c = 0 goes to a separate coarse buffer (ucz): other tiles still read
+// e_c.
+template <int NB>
+struct WavePostPreLds {
+    static constexpr int NS = NB + 1, TURNS = NS + 3;
+    WaveLds<double, false, NS> ring;
+    double w[TURNS * 8 * 64];   // turn, plane, lane
+};
+
+template <int NB, int DIR>
+struct WavePostPre : WaveInterp<double, false, NB + 1, DIR> {
+    using T = double;
+    static constexpr int NS = NB + 1;
+    using A = WaveInterp<double, false, NS, DIR>;
+    using B = typename A::B;
+    static constexpr int RX = B::RX, TURNS = RX / 2;
+    static_assert(TURNS == NS + 3, "a coarse row's weights are used up to NS + 2 turns after they arrive");
+    T pr0[2], pr1[2], acc;
+    T *sw;                      // this lane's weights of turn 0
+    int I;
+    bool rest;
+
+    __device__ __forceinline__ void run(const Lev<T> &L, T *__restrict__ ukout, T *__restrict__ uout,
+                                        const Wts<T> &Cw, const T *__restrict__ ec, const Lev<T> &Cl,
+                                        T *__restrict__ ucz, const TileGeo &G, int tid, double *__restrict__ part,
+                                        WavePostPreLds<NB> &lds)
+    {
+        B::place(L, G, tid, lds.ring);
+        sw = lds.w + threadIdx.x;
+        A::coarse(Cw);
+        I = this->i0 >> 1;
+        rest = this->own && I >= 1 && I <= this->nc;
+        const int y0 = this->y0, y1 = this->y1;
+        const int es = DIR > 0 ? (y0 - 2 * NS) & ~1 : (y1 + 2 * NS) & ~1;
+        const int elast = DIR > 0 ? 2 * ((y1 - 1) >> 1) + 2 * NS + 2 : 2 * ((y0 + 1) >> 1) - 2 * NS - 2;
+        typename B::Couplings c[2];
+        A::begin(L, Cw, ec, es, c);
+        pr0[0] = pr0[1] = pr1[0] = pr1[1] = 0.0;
+        acc = 0.0;
+        for (int e = es; DIR * (elast - e) >= 0; e += DIR * RX)
+            turn<0>(L, ukout, uout, Cw, ec, Cl, ucz, e, elast, c);
+        wave_sum_to(acc, part + tid);
+    }
+
+private:
+    // weight PL that arrived K turns before turn M, of the lane `west` lanes west
+    template <int M, int K, int PL, int WEST>
+    __device__ __forceinline__ T kept() const
+    {
+        return sw[(((M - K) % TURNS + TURNS) % TURNS * 8 + PL) * 64 - WEST];
+    }
+    template <int M>
+    __device__ __forceinline__ void turn(const Lev<T> &L, T *__restrict__ ukout, T *__restrict__ uout,
+                                         const Wts<T> &Cw, const T *__restrict__ ec, const Lev<T> &Cl,
+                                         T *__restrict__ ucz, int e, int elast, typename B::Couplings (&c)[2])
+    {
+        if constexpr (M < TURNS) {
+            if (DIR * (e - elast) > 0) return;
+            wave_lds_order();
+            B::template put_couplings<B::template at<M>(0)>(c[0]);
+            B::template put_couplings<B::template at<M>(1)>(c[1]);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) sw[(M * 8 + q) * 64] = this->w[q];
+            wave_lds_order();
+            A::template enter<M>(L, Cw, ec, e, c);
+            B::template sweeps<M, 0, 1>();
+            B::template write<M, 0>(ukout, e);
+            B::template norm<M, -1>(e - DIR, acc);
+            B::template norm<M, -2>(e - 2 * DIR, acc);
+            B::template sweeps<M, 1, NS>();
+            B::template write<M, NS - 1>(uout, e);
+            T r0[2], r1[2];
+            r0[0] = B::template resid<M, -2 * NS, 0>();
+            r0[1] = B::template resid<M, -2 * NS, 1>();
+            r1[0] = B::template resid<M, -2 * NS - 1, 0>();
+            r1[1] = B::template resid<M, -2 * NS - 1, 1>();
+            const int f = e - DIR * (2 * NS + 2), J = f >> 1;
+            const T *rd = DIR > 0 ? pr1 : r1, *ru = DIR > 0 ? r1 : pr1;
+            const T dw = from_west(rd[1]), mw = from_west(pr0[1]), uw = from_west(ru[1]);
+            // planes of `weights`: row J's edges and the corner rows J, J + 1
+            // (the even row f arrived NS + 1 turns ago; upward its corner row
+            // J + 1 came with it, J a turn before, downward J and J + 1)
+            constexpr int KE = NS + 1, KL = DIR > 0 ? NS + 2 : NS + 1, KU = DIR > 0 ? NS + 1 : NS + 2;
+            T s = kept<M, KL, 7, 1>() * dw;                 // LNE(I, J)
+            s = s + kept<M, KL, 3, 0>() * rd[0];            // LA(I, J)
+            s = s + kept<M, KL, 6, 0>() * rd[1];            // LNW(I + 1, J)
+            s = s + kept<M, KE, 1, 1>() * mw;               // LR(I, J)
+            s = s + pr0[0];
+            s = s + kept<M, KE, 0, 0>() * pr0[1];           // LL(I + 1, J)
+            s = s + kept<M, KU, 5, 1>() * uw;               // LSE(I, J + 1)
+            s = s + kept<M, KU, 2, 0>() * ru[0];            // LB(I, J + 1)
+            s = s + kept<M, KU, 4, 0>() * ru[1];            // LSW(I + 1, J + 1)
+            if (rest && J >= 1 && J <= this->nc && f >= this->y0 && f < this->y1) {
+                const size_t p = (size_t)J * this->ldc + I;
+                Cl.b[p] = s;
+                ucz[p] = 0.0;
+            }
+            pr0[0] = r0[0]; pr0[1] = r0[1];
+            pr1[0] = r1[0]; pr1[1] = r1[1];
+            turn<M + 1>(L, ukout, uout, Cw, ec, Cl, ucz, e + 2 * DIR, elast, c);
+        }
+    }
+};
+
+template <int NB>
+__global__ __launch_bounds__(64, 1) void k_postpre_wave(Lev<double> L, double *__restrict__ ukout,
+                                                        double *__restrict__ uout, Wts<double> C,
+                                                        const double *__restrict__ ec, Lev<double> Cl,
+                                                        double *__restrict__ ucz, TileGeo G,
+                                                        double *__restrict__ part, const int *stop)
+{
+    int tid, k;
+    if (!tile_work(G, tid, k)) return;
+    if (stopped(stop)) return;
+    __shared__ WavePostPreLds<NB> S;
+    if (wave_up(G, tid)) {
+        WavePostPre<NB, 1> P;
+        P.run(L, ukout, uout, C, ec, Cl, ucz, G, tid, part, S);
+    } else {
+        WavePostPre<NB, -1> P;
+        P.run(L, ukout, uout, C, ec, Cl, ucz, G, tid, part, S);
     }
 }
 
