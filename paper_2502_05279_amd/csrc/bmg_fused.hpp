@@ -705,8 +705,10 @@ __device__ __forceinline__ void post_tile(const Lev<T> &L, T *__restrict__ uout,
     }
 }
 
-// The fine-level passes of an FP32 refinement step (IrArgs).  The post pass
-// leaves u itself unwritten: the iterate takes the correction directly.
+// The fine-level passes of a refinement step (IrArgs): the FP32 pre pass of
+// three sweeps (fewer run as waves), and the post pass of an FP64 step or of
+// one FP32 cycle by itself (within a solve it takes the next residual too, as
+// waves), which leaves u unwritten: the iterate takes the correction directly.
 template <int NU>
 __global__ __launch_bounds__(FW) void k_pre_ir(Lev<float> L, float *__restrict__ uout, Wts<float> C,
                                                 Lev<float> Cl, TileGeo G, const int *stop, IrArgs ir)

@@ -710,7 +710,7 @@ bmg_status fused_vcycle32(bmg_solver *h, const int *stop) { return fused_cycle_f
 // A refinement step's cycle with the fine post pass adding the correction to
 // (XH, XL) itself (k_post_ir): a five-point fine level, a post sweep count the
 // pass takes, one right-hand side.  With an FP32 inner cycle the fine pre pass
-// also takes the scaled residual itself (k_pre_ir).
+// also takes the scaled residual itself (ir_pre_cycle).
 static bool post_update_fusable(const bmg_solver *h)
 {
     return h->opt.kernels == BMG_KERNELS_FUSED && h->opt.smoother == BMG_SMOOTH_POINT && !h->nine[0] &&
@@ -746,26 +746,30 @@ static bmg_status post_update(bmg_solver *h, const int *stop, const IrArgs &ir)
     return BMG_OK;
 }
 
-static bmg_status ir_fused_cycle(bmg_solver *h, const int *stop, const IrArgs &ir)
+// The fine pre pass of an FP32 refinement step and the cycle below it.
+static bmg_status ir_pre_cycle(bmg_solver *h, const int *stop, const IrArgs &ir)
 {
     Lev<float> &F = h->L32[0];
     const Lev<float> &Cl = h->L32[1];
     const Wts<float> &C = h->C32[0];
     const int nu1 = h->opt.nu1;
     const double nf = (double)F.n * F.n, ncc = (double)Cl.n * Cl.n;
-    const TileGeo g = level_tiles(h, 0, 2 * nu1 + 2);
-    const dim3 grid = tile_grid(g), blk(FW);
     // stencil and the FP64 residual read, u and b written; b and u (zero)
     // written on the coarse level and the 8 weight planes read
     trace_begin(h, BMG_TRACE_PRE, 0, 4.0 * ((stencil_planes(false) + 2.0) * nf + 10.0 * ncc) + 8.0 * nf);
-#define PREI(NU) hipLaunchKernelGGL((k_pre_ir<NU>), grid, blk, 0, h->st, F, h->ualt32[0], C, Cl, g, stop, ir)
-    if (nu1 == 1) PREI(1); else if (nu1 == 2) PREI(2); else PREI(3);
-#undef PREI
+    if (nu1 <= 2) {
+        const TileGeo g = wave_tiles(h, 0, 2 * nu1 + 2);
+        const dim3 grid = tile_grid(g), blk(64);
+        if (nu1 == 1) hipLaunchKernelGGL((k_pre_ir_wave<1>), grid, blk, 0, h->st, F, h->ualt32[0], C, Cl, g, stop, ir);
+        else hipLaunchKernelGGL((k_pre_ir_wave<2>), grid, blk, 0, h->st, F, h->ualt32[0], C, Cl, g, stop, ir);
+    } else {
+        const TileGeo g = level_tiles(h, 0, 2 * nu1 + 2);
+        hipLaunchKernelGGL((k_pre_ir<3>), tile_grid(g), dim3(FW), 0, h->st, F, h->ualt32[0], C, Cl, g, stop, ir);
+    }
     trace_end(h, BMG_TRACE_PRE, 0);
     LAUNCHCHK();
     std::swap(F.u, h->ualt32[0]);
-    TRY(fused_cycle_from<float>(h, 1, stop, false));
-    return post_update<float>(h, stop, ir);
+    return fused_cycle_from<float>(h, 1, stop, false);
 }
 
 // Sum of squares of r = b - A u (res) or of the array x, into scal[slot]; with
@@ -1174,7 +1178,8 @@ static bmg_status ir_correct(bmg_solver *h, const int *stop)
     if (ir_fusable(h)) {
         LAUNCHCHK();
         const IrArgs ir{L.r, h->scal + S_RMAX, h->scal + S_SCALE, h->XH, h->XL};
-        return ir_fused_cycle(h, stop, ir);
+        TRY(ir_pre_cycle(h, stop, ir));
+        return post_update<float>(h, stop, ir);
     }
     hipLaunchKernelGGL(k_ir_scale, grid2(L.n, L.n, B2), B2, 0, h->st, L, F, (const double *)(h->scal + S_RMAX),
                        h->scal + S_SCALE, stop);
@@ -1183,6 +1188,51 @@ static bmg_status ir_correct(bmg_solver *h, const int *stop)
     else TRY(vcycle_from<float>(h, 0, stop));
     hipLaunchKernelGGL(k_dd_update, grid2(L.n, L.n, B2), B2, 0, h->st, L, h->XH, h->XL, (const float *)F.u,
                        (const double *)(h->scal + S_SCALE), stop);
+    LAUNCHCHK();
+    return BMG_OK;
+}
+
+// Tiles of k_post_res_wave: the halo of a post pass with its residual.
+static TileGeo post_res_geo(const bmg_solver *h) { return wave_tiles(h, 0, 2 * h->opt.nu2 + 2); }
+
+// FP32 refinement steps of a solve whose fine post pass also takes the next
+// step's residual: what ir_correct fuses, and at most NPART / 2 tiles (each
+// leaves a partial sum and a partial maximum).
+static bool post_res_ok(const bmg_solver *h) { return ir_fusable(h) && 2 * post_res_geo(h).ntiles <= NPART; }
+
+// One such step on the pair (xh, xl), whose residual is in L0.r with np partial
+// maxima at h->part + np; the new pair goes to (oh, ol), its residual to L0.r
+// and its norm to the history.
+static bmg_status ir_step(bmg_solver *h, int np, double *xh, double *xl, double *oh, double *ol, double tol, int maxe)
+{
+    const Lev<double> &L = h->L[0];
+    hipLaunchKernelGGL(k_absmax_final, dim3(1), dim3(1024), 0, h->st, (const double *)h->part + np, np,
+                       h->scal + S_RMAX, h->stop);
+    LAUNCHCHK();
+    const IrArgs ir{L.r, h->scal + S_RMAX, h->scal + S_SCALE, xh, xl};
+    TRY(ir_pre_cycle(h, h->stop, ir));
+    const Lev<float> &F = h->L32[0];
+    const Lev<float> &Cl = h->L32[1];
+    const TileGeo g = post_res_geo(h);
+    const dim3 grid = tile_grid(g), blk(64);
+    const PairOut out{h->B0, oh, ol, L.r, h->part};
+    const double nf = (double)F.n * F.n, ncc = (double)Cl.n * Cl.n;
+    // FP64 stencil, B and the pair read, the pair and r written, b and u read;
+    // the coarse correction and the 8 weight planes read
+    trace_begin(h, BMG_TRACE_POST, 0, 8.0 * (stencil_planes(false) + 6.0) * nf + 4.0 * (2.0 * nf + 9.0 * ncc));
+    if (h->opt.nu2 == 1)
+        hipLaunchKernelGGL((k_post_res_wave<1>), grid, blk, 0, h->st, F, L, h->C32[0], (const float *)Cl.u, g,
+                           (const int *)h->stop, ir, out);
+    else
+        hipLaunchKernelGGL((k_post_res_wave<2>), grid, blk, 0, h->st, F, L, h->C32[0], (const float *)Cl.u, g,
+                           (const int *)h->stop, ir, out);
+    trace_end(h, BMG_TRACE_POST, 0);
+    LAUNCHCHK();
+    trace_begin(h, BMG_TRACE_RESNORM, 0, 8.0 * g.ntiles);
+    hipLaunchKernelGGL(k_sumsq_final, dim3(1), dim3(1024), 0, h->st, (const double *)h->part, g.ntiles,
+                       h->scal + S_SUMSQ, h->hist, h->count, h->stop, (const double *)(h->scal + S_BNORM), tol, maxe,
+                       0.0);
+    trace_end(h, BMG_TRACE_RESNORM, 0);
     LAUNCHCHK();
     return BMG_OK;
 }
@@ -1479,13 +1529,27 @@ bmg_status bmg_solve(bmg_solver *h, const double *rhs, double *x, double tol, bm
         refining = true;
         const int maxe = maxc + 1;
         TRY(resnorm_dd(h, h->B0, h->XH, h->XL, 1, L.r, S_SUMSQ, true, tol, maxe, 0.0));
-        while (true) {
-            for (int t = 0; t < every; ++t) {
-                TRY(ir_correct(h, h->stop));
-                TRY(resnorm_dd(h, h->B0, h->XH, h->XL, 1, L.r, S_SUMSQ, true, tol, maxe, 0.0));
+        // fused steps: the pair alternates with the FP64 fine planes that this
+        // mode leaves free; steps enqueued past the stop do nothing
+        const bool pr = post_res_ok(h);
+        double *const X[2][2] = {{h->XH, h->XL}, {h->ualt[0], h->L[0].u}};
+        int np = std::min(NPART_ROWS, L.n);
+        for (int k = 0; cs[1] == 0;) {
+            for (int t = 0; t < every; ++t, ++k) {
+                if (pr) {
+                    double *const *from = X[k & 1], *const *to = X[~k & 1];
+                    TRY(ir_step(h, np, from[0], from[1], to[0], to[1], tol, maxe));
+                    np = post_res_geo(h).ntiles;
+                } else {
+                    TRY(ir_correct(h, h->stop));
+                    TRY(resnorm_dd(h, h->B0, h->XH, h->XL, 1, L.r, S_SUMSQ, true, tol, maxe, 0.0));
+                }
             }
             TRY(poll(h, cs));
-            if (cs[1]) break;
+        }
+        if (pr && cs[0] > 0 && !(cs[0] & 1)) {   // an odd number of steps ran
+            std::swap(h->XH, h->ualt[0]);
+            std::swap(h->XL, h->L[0].u);
         }
     }
     if (!refining) {

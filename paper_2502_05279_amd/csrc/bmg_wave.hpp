@@ -15,9 +15,9 @@
 //
 // Measured in a 4095^2 solve (FP64, V(2,1)), against the workgroup passes:
 // nine-point 2047^2 pre 142 -> 81 us, post 97 -> 71, 1023^2 66 -> 32 and
-// 34 -> 25; the cross-cycle pass of the fine level 444 -> 295, 1.45 GB at the
-// 4.9 TB/s of a copy.  The 2047^2 passes are bound by
-// memory: 443 MB for the pre pass, 4.9 TB/s, while both neighbours of a tile
+// 34 -> 25; the cross-cycle pass of the fine level 444 -> 295, 1.48 GB at 5.0
+// TB/s (a copy reaches 4.9).  The 2047^2 passes are bound by
+// memory: 452 MB for the pre pass, 5 TB/s, while both neighbours of a tile
 // streamed the same way (91 us); streaming every other row of tiles downward
 // lets two tiles share the rows at their border.
 //
@@ -110,9 +110,17 @@ struct WaveTile {
         sNW = lds.NW + 2 * lane;
     }
     __device__ __forceinline__ int rowc(int row) const { return row >= 0 && row <= n + 1 ? row : n + 1; }
-    __device__ __forceinline__ V load(const T *a, int row) const
+    template <typename E>
+    __device__ __forceinline__ typename Pair<E>::vec load(const E *a, int row) const
     {
-        return *reinterpret_cast<const V *>(a + (size_t)rowc(row) * ld + i0c);
+        return *reinterpret_cast<const typename Pair<E>::vec *>(a + (size_t)rowc(row) * ld + i0c);
+    }
+    template <typename E>
+    __device__ __forceinline__ void store(E *a, int row, E v0, E v1) const
+    {
+        E *p = a + (size_t)row * ld + i0;
+        if (i0 > 0) *reinterpret_cast<typename Pair<E>::vec *>(p) = typename Pair<E>::vec{v0, v1};
+        else p[1] = v1;
     }
     // the couplings of a row that go through LDS
     struct Couplings {
@@ -143,11 +151,14 @@ struct WaveTile {
         }
     }
     // b, O, S of a row into its slot
-    template <int SL>
+    template <int SL, bool WITH_B = true>
     __device__ __forceinline__ void request(const Lev<T> &L, int row)
     {
-        const V vb = load(L.b, row), vo = load(L.O, row), vs = load(L.S, row);
-        b[SL][0] = vb.x; b[SL][1] = vb.y;
+        if constexpr (WITH_B) {
+            const V vb = load(L.b, row);
+            b[SL][0] = vb.x; b[SL][1] = vb.y;
+        }
+        const V vo = load(L.O, row), vs = load(L.S, row);
         O[SL][0] = vo.x; O[SL][1] = vo.y;
         S[SL][0] = vs.x; S[SL][1] = vs.y;
     }
@@ -266,10 +277,8 @@ struct WaveTile {
         for (int t = 0; t < 2; ++t) {
             const int row = e - DIR * (2 * SW_ + t);
             if (row < y0 || row >= y1 || !own) continue;
-            T *p = out + (size_t)row * ld + i0;
             const T *v = u[at<M>(-2 * SW_ - t)];
-            if (i0 > 0) *reinterpret_cast<V *>(p) = V{v[0], v[1]};
-            else p[1] = v[1];
+            store(out, row, v[0], v[1]);
         }
     }
 };
@@ -280,8 +289,10 @@ struct WaveTile {
 __device__ __forceinline__ bool wave_up(const TileGeo &G, int tid) { return !((tid / G.tiles_x) & 1); }
 
 // nu sweeps, residual and restriction (results as pre_tile).  zero_u: the
-// iterate is known to be zero (a coarse level's first visit in a cycle).
-template <typename T, bool NINE, int NU, int DIR>
+// iterate is known to be zero (a coarse level's first visit in a cycle).  IRIN
+// (see IrArgs): b is the scaled FP64 residual, also stored as the FP32
+// right-hand side.
+template <typename T, bool NINE, int NU, int DIR, bool IRIN = false>
 struct WavePre : WaveTile<T, NINE, NU, DIR> {
     using B = WaveTile<T, NINE, NU, DIR>;
     using V = typename B::V;
@@ -290,11 +301,21 @@ struct WavePre : WaveTile<T, NINE, NU, DIR> {
     T w[8];                    // restriction weights of the next step's coarse row
     bool rest;
     int I, nc;
+    Pair<double>::vec res[2];  // IRIN: the FP64 residual of the next step's rows
+    const double *r;
+    double inv;
 
     __device__ __forceinline__ void run(const Lev<T> &L, T *__restrict__ uout, const Wts<T> &Cw, const Lev<T> &Cl,
-                                        const TileGeo &G, int tid, WaveLds<T, NINE, NU> &lds, bool zero_u)
+                                        const TileGeo &G, int tid, WaveLds<T, NINE, NU> &lds, bool zero_u,
+                                        const IrArgs &ir = {})
     {
         B::place(L, G, tid, lds);
+        if constexpr (IRIN) {
+            const int ex = ir_exponent(*ir.rmax);
+            inv = ldexp(1.0, -ex);
+            r = ir.r;
+            if (tid == 0 && threadIdx.x == 0) ir.scale[0] = ldexp(1.0, ex);
+        }
         nc = Cl.n;
         I = this->i0 >> 1;
         rest = this->own && I >= 1 && I <= nc;
@@ -324,7 +345,8 @@ private:
             const V vu = zero_u ? V{(T)0, (T)0} : B::load(L.u, row);
             this->u[SL][0] = vu.x;
             this->u[SL][1] = vu.y;
-            B::template request<SL>(L, row);
+            B::template request<SL, !IRIN>(L, row);
+            if constexpr (IRIN) scaled<SL>(B::load(r, row));
             B::template put_couplings<SL>(B::couplings(L, row));
             B::template arrived<SL>(row);
             fill<D + 1>(L, es, zero_u);
@@ -338,8 +360,25 @@ private:
         const V u0 = zero_u ? V{(T)0, (T)0} : B::load(L.u, e), u1 = zero_u ? V{(T)0, (T)0} : B::load(L.u, e + DIR);
         this->u[S0][0] = u0.x; this->u[S0][1] = u0.y;
         this->u[S1][0] = u1.x; this->u[S1][1] = u1.y;
-        B::template request<S0>(L, e);
-        B::template request<S1>(L, e + DIR);
+        B::template request<S0, !IRIN>(L, e);
+        B::template request<S1, !IRIN>(L, e + DIR);
+        if constexpr (IRIN) {
+            res[0] = B::load(r, e);
+            res[1] = B::load(r, e + DIR);
+        }
+    }
+    template <int SL>
+    __device__ __forceinline__ void scaled(Pair<double>::vec v)
+    {
+        this->b[SL][0] = (T)(v.x * inv);
+        this->b[SL][1] = (T)(v.y * inv);
+    }
+    // every owned row arrives once: keep its FP32 right-hand side
+    template <int SL>
+    __device__ __forceinline__ void scaled(const Lev<T> &L, Pair<double>::vec v, int row)
+    {
+        scaled<SL>(v);
+        if (this->own && row >= this->y0 && row < this->y1) B::store(L.b, row, this->b[SL][0], this->b[SL][1]);
     }
     __device__ __forceinline__ void weights(const Wts<T> &C, int J)
     {
@@ -367,6 +406,10 @@ private:
             wave_lds_order();
             B::template arrived<S0>(e);
             B::template arrived<S1>(e + DIR);
+            if constexpr (IRIN) {
+                scaled<S0>(L, res[0], e);
+                scaled<S1>(L, res[1], e + DIR);
+            }
             T wc[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q) wc[q] = w[q];
@@ -424,6 +467,26 @@ __global__ __launch_bounds__(64, 1) void k_pre_wave(Lev<T> L, T *__restrict__ uo
     } else {
         WavePre<T, NINE, NU, -1> P;
         P.run(L, uout, C, Cl, G, tid, S, ZU);
+    }
+}
+
+// The fine pre pass of an FP32 refinement step (one or two sweeps), at the rate
+// of memory: 8191^2, two sweeps, 537 us for 38 bytes per point, 4.7 TB/s (as
+// workgroups 631).
+template <int NU>
+__global__ __launch_bounds__(64, 1) void k_pre_ir_wave(Lev<float> L, float *__restrict__ uout, Wts<float> C,
+                                                       Lev<float> Cl, TileGeo G, const int *stop, IrArgs ir)
+{
+    int tid, k;
+    if (!tile_work(G, tid, k)) return;
+    if (stopped(stop)) return;
+    __shared__ WaveLds<float, false, NU> S;
+    if (wave_up(G, tid)) {
+        WavePre<float, false, NU, 1, true> P;
+        P.run(L, uout, C, Cl, G, tid, S, true, ir);
+    } else {
+        WavePre<float, false, NU, -1, true> P;
+        P.run(L, uout, C, Cl, G, tid, S, true, ir);
     }
 }
 
@@ -630,6 +693,245 @@ __global__ __launch_bounds__(64, 1) void k_post_wave(Lev<T> L, T *__restrict__ u
     } else {
         WavePost<T, NINE, NU, -1, NORM> P;
         P.run(L, uout, C, ec, G, tid, part, S);
+    }
+}
+
+// The fine post pass of an FP32 refinement step together with the next step's
+// FP64 residual: interpolation and nu sweeps in FP32, (x_hi, x_lo) += s u on
+// the rows that come out (IrArgs), and r = B - A (x_hi + x_lo), as k_resid_dd
+// forms it, on the rows whose neighbours have come out too, with the tile's
+// sum of r^2 in part[tid] and max |r| in part[ntiles + tid].  The FP32
+// operator is the FP64 one rounded, so the pass reads only the FP64 one: 89
+// bytes per fine point (stencil 24, b and u 8, weights and e_c 9, the pair 32,
+// B 8, r 8) where the post pass and the residual take 61 + 64.  Every halo point
+// updates its own copy of the pair, so the new pair goes to buffers of its own
+// (oh, ol).  Bound by memory: 8191^2, one sweep, 1286 us, 4.6 TB/s, where the
+// two passes took 1009 + 948.
+template <int NU>
+struct WavePostResLds {
+    static constexpr int RX = 2 * NU + 6;
+    WaveLds<float, false, NU> ring;
+    double W[RX * WAVE_COLS + 2];
+};
+
+struct PairOut {
+    const double *B;
+    double *oh, *ol, *r, *part;
+};
+
+template <int NU, int DIR>
+struct WavePostRes : WaveInterp<float, false, NU, DIR> {
+    using A = WaveInterp<float, false, NU, DIR>;
+    using B = typename A::B;
+    using V = typename A::V;
+    using D2 = Pair<double>::vec;
+    static constexpr int RX = B::RX;
+    double O2[RX][2], S2[RX][2];
+    double xh[4][2], xl[4][2];     // the new pair: the two rows a step finalises, the two of the step before
+    D2 ph[2], pl[2], pb[2];        // the pair and B of the next step's rows
+    D2 w2[2];
+    double *sW2, sc, acc, mx;
+
+    __device__ __forceinline__ void run(const Lev<float> &L, const Lev<double> &F, const Wts<float> &Cw,
+                                        const float *__restrict__ ec, const IrArgs &ir, const PairOut &out,
+                                        const TileGeo &G, int tid, WavePostResLds<NU> &lds)
+    {
+        B::place(L, G, tid, lds.ring);
+        A::coarse(Cw);
+        sW2 = lds.W + 2 * threadIdx.x;
+        sc = *ir.scale;
+        const int y0 = this->y0, y1 = this->y1;
+        const int es = DIR > 0 ? (y0 - 2 * NU + 1) & ~1 : (y1 - 1 + 2 * NU) & ~1;
+        const int elast = DIR > 0 ? (y1 - 1 + 2 * NU) & ~1 : y0 + 1 - 2 * NU;
+        this->e0 = A::crow(ec, (es - DIR * (2 * NU + 2)) >> 1);
+        fill64<-2 * NU - 2>(L, F, Cw, ec, es);
+        want64<0>(L, F, es);
+        pair_rows(ir, out, es);
+        this->en = A::crow(ec, (es >> 1) + DIR);
+        A::weights(Cw, es);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) xh[t][0] = xh[t][1] = xl[t][0] = xl[t][1] = 0.0;
+        acc = mx = 0.0;
+        for (int e = es; DIR * (elast - e) >= 0; e += DIR * RX) turn<0>(L, F, Cw, ec, ir, out, e, elast);
+        wave_sum_to(acc, out.part + tid);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_down(mx, o, 64));
+        if (threadIdx.x == 0) out.part[G.ntiles + tid] = mx;
+    }
+
+private:
+    template <int SL>
+    __device__ __forceinline__ void request64(const Lev<float> &L, const Lev<double> &F, int row)
+    {
+        const V vb = B::load(L.b, row), vu = B::load(L.u, row);
+        this->b[SL][0] = vb.x; this->b[SL][1] = vb.y;
+        this->u[SL][0] = vu.x; this->u[SL][1] = vu.y;
+        const D2 vo = B::load(F.O, row), vs = B::load(F.S, row);
+        O2[SL][0] = vo.x; O2[SL][1] = vo.y;
+        S2[SL][0] = vs.x; S2[SL][1] = vs.y;
+    }
+    template <int M>
+    __device__ __forceinline__ void want64(const Lev<float> &L, const Lev<double> &F, int e)
+    {
+        request64<B::template at<M>(0)>(L, F, e);
+        request64<B::template at<M>(1)>(L, F, e + DIR);
+        w2[0] = B::load(F.W, e);
+        w2[1] = B::load(F.W, e + DIR);
+    }
+    // the FP32 operator of a row that has arrived, and its W into both rings
+    template <int SL>
+    __device__ __forceinline__ void arrived64(int row, D2 w)
+    {
+        *reinterpret_cast<D2 *>(sW2 + SL * WAVE_COLS) = w;
+        typename B::Couplings c;
+        c.w = V{(float)w.x, (float)w.y};
+        B::template put_couplings<SL>(c);
+        this->O[SL][0] = (float)O2[SL][0];
+        this->O[SL][1] = (float)O2[SL][1];
+        this->S[SL][0] = (float)S2[SL][0];
+        this->S[SL][1] = (float)S2[SL][1];
+        B::template arrived<SL>(row);
+    }
+    template <int D>
+    __device__ __forceinline__ void fill64(const Lev<float> &L, const Lev<double> &F, const Wts<float> &Cw,
+                                           const float *ec, int es)
+    {
+        if constexpr (D < 0) {
+            constexpr int S0 = B::template at<0>(D), S1 = B::template at<0>(D + 1);
+            const int row = es + DIR * D;
+            request64<S0>(L, F, row);
+            request64<S1>(L, F, row + DIR);
+            const float e1 = A::crow(ec, (row >> 1) + DIR);
+            A::weights(Cw, row);
+            arrived64<S0>(row, B::load(F.W, row));
+            arrived64<S1>(row + DIR, B::load(F.W, row + DIR));
+            A::template correct<S0, S1>(row, this->e0, e1);
+            this->e0 = e1;
+            fill64<D + 2>(L, F, Cw, ec, es);
+        }
+    }
+    // the pair of the rows step e finalises and B of the rows whose residual it takes
+    __device__ __forceinline__ void pair_rows(const IrArgs &ir, const PairOut &out, int e)
+    {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int row = e - DIR * (2 * NU - 2 + t);
+            ph[t] = B::load((const double *)ir.XH, row);
+            pl[t] = B::load((const double *)ir.XL, row);
+            pb[t] = B::load(out.B, row - DIR);
+        }
+    }
+    // r at column C of window row D (its slot S0, SD below and SU above): the
+    // pair of rows below, here, above in p, q, s of xh, xl
+    template <int C, int SD, int S0, int SU, int P, int Q, int R>
+    __device__ __forceinline__ double resid64(double bq) const
+    {
+        const double a[5] = {S2[S0][C], sW2[S0 * WAVE_COLS + C], sW2[S0 * WAVE_COLS + C + 1], S2[SU][C], O2[S0][C]};
+        const double x[5] = {xh[P][C], C ? xh[Q][0] : from_west(xh[Q][1]), C ? from_east(xh[Q][0]) : xh[Q][1],
+                             xh[R][C], xh[Q][C]};
+        const double z[5] = {xl[P][C], C ? xl[Q][0] : from_west(xl[Q][1]), C ? from_east(xl[Q][0]) : xl[Q][1],
+                             xl[R][C], xl[Q][C]};
+        double s = bq, c = 0.0, ns, se;
+#pragma unroll
+        for (int t = 0; t < 5; ++t) {
+            const double pr = a[t] * x[t];
+            const double pe = fma(a[t], x[t], -pr);
+            two_sum(s, -pr, ns, se);
+            s = ns;
+            c = c + (se - pe);
+        }
+#pragma unroll
+        for (int t = 0; t < 5; ++t) {
+            two_sum(s, -(a[t] * z[t]), ns, se);
+            s = ns;
+            c = c + se;
+        }
+        return s + c;
+    }
+    // the residual of row e + DIR D; P, Q, R: its neighbours behind, itself and
+    // ahead among the four kept rows
+    template <int M, int D, int P, int Q, int R>
+    __device__ __forceinline__ void residual_row(const PairOut &out, int row, D2 bq)
+    {
+        constexpr int SD = B::template at<M>(D - DIR), S0 = B::template at<M>(D), SU = B::template at<M>(D + DIR);
+        constexpr int lo = DIR > 0 ? P : R, hi = DIR > 0 ? R : P;
+        const double r0 = resid64<0, SD, S0, SU, lo, Q, hi>(bq.x), r1 = resid64<1, SD, S0, SU, lo, Q, hi>(bq.y);
+        if (this->own && row >= this->y0 && row < this->y1) {
+            B::store(out.r, row, r0, r1);
+            const double q0 = this->i0 > 0 ? r0 : 0.0;      // (column 0 is the ring)
+            acc += q0 * q0;
+            acc += r1 * r1;
+            mx = fmax(mx, fmax(fabs(q0), fabs(r1)));
+        }
+    }
+    template <int M>
+    __device__ __forceinline__ void turn(const Lev<float> &L, const Lev<double> &F, const Wts<float> &Cw,
+                                         const float *__restrict__ ec, const IrArgs &ir, const PairOut &out, int e,
+                                         int elast)
+    {
+        if constexpr (M < RX / 2) {
+            if (DIR * (e - elast) > 0) return;
+            constexpr int S0 = B::template at<M>(0), S1 = B::template at<M>(1);
+            wave_lds_order();
+            arrived64<S0>(e, w2[0]);
+            arrived64<S1>(e + DIR, w2[1]);
+            wave_lds_order();
+            A::template correct<S0, S1>(e, this->e0, this->en);
+            this->e0 = this->en;
+            D2 ch[2] = {ph[0], ph[1]}, cl[2] = {pl[0], pl[1]}, cb[2] = {pb[0], pb[1]};
+            want64<(M + 1) % (RX / 2)>(L, F, e + 2 * DIR);
+            pair_rows(ir, out, e + 2 * DIR);
+            this->en = A::crow(ec, (e >> 1) + 2 * DIR);
+            A::weights(Cw, e + 2 * DIR);
+            B::template sweeps<M, 0, NU>();
+            // the two rows that are final: (xh, xl) += s u, kept as rows 0, 1
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int row = e - DIR * (2 * NU - 2 + t);
+                const float *v = this->u[B::template at<M>(2 - 2 * NU - t)];
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const double d = sc * (double)v[c];
+                    double hs, he;
+                    two_sum(c ? ch[t].y : ch[t].x, d, hs, he);
+                    he = he + (c ? cl[t].y : cl[t].x);
+                    const double hi = hs + he;
+                    xl[t][c] = he - (hi - hs);
+                    xh[t][c] = hi;
+                }
+                if (this->own && row >= this->y0 && row < this->y1) {
+                    B::store(out.oh, row, xh[t][0], xh[t][1]);
+                    B::store(out.ol, row, xl[t][0], xl[t][1]);
+                }
+            }
+            // residuals of the odd row and of the even row behind it
+            residual_row<M, 1 - 2 * NU, 2, 1, 0>(out, e + DIR * (1 - 2 * NU), cb[0]);
+            residual_row<M, -2 * NU, 3, 2, 1>(out, e - DIR * 2 * NU, cb[1]);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                xh[2][c] = xh[0][c]; xl[2][c] = xl[0][c];
+                xh[3][c] = xh[1][c]; xl[3][c] = xl[1][c];
+            }
+            turn<M + 1>(L, F, Cw, ec, ir, out, e + 2 * DIR, elast);
+        }
+    }
+};
+
+template <int NU>
+__global__ __launch_bounds__(64, 1) void k_post_res_wave(Lev<float> L, Lev<double> F, Wts<float> C,
+                                                         const float *__restrict__ ec, TileGeo G, const int *stop,
+                                                         IrArgs ir, PairOut out)
+{
+    int tid, k;
+    if (!tile_work(G, tid, k)) return;
+    if (stopped(stop)) return;
+    __shared__ WavePostResLds<NU> S;
+    if (wave_up(G, tid)) {
+        WavePostRes<NU, 1> P;
+        P.run(L, F, C, ec, ir, out, G, tid, S);
+    } else {
+        WavePostRes<NU, -1> P;
+        P.run(L, F, C, ec, ir, out, G, tid, S);
     }
 }
 
