@@ -84,50 +84,223 @@ static __global__ void k_pack_weights(const float *__restrict__ P, bf16_t *__res
     out[g] = v;
 }
 
-// ------------------------------------------------------------------ features
-// X(p) = bf16(fl32(a_c(p) / O(p))) for the nine coefficients SW..NE of every
-// interior point, channels 9..15 and the ring zero.  One thread per point of
-// the padded grid, 32 bytes each.
-static __global__ void k_net_features(Lev<double> L, bool nine, bf16_t *__restrict__ X)
+// Two floats to bfloat16, to nearest even (v_cvt_pk_bf16_f32: the bits of
+// bf16_rne for every float).
+__device__ __forceinline__ unsigned bf16_pair(float a, float b)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int j = blockIdx.y * blockDim.y + threadIdx.y;
-    const int n = L.n, side = n + 2;
-    if (i >= side || j >= side) return;
-    bf16_t v[16] = {};
-    if (i >= 1 && i <= n && j >= 1 && j <= n) {
-        const size_t ld = L.ld, p = (size_t)j * ld + i;
-        double a[9];
-        a[0] = nine ? L.SW[p] : 0.0;
-        a[1] = L.S[p];
-        a[2] = nine ? L.NW[p + 1 - ld] : 0.0;
-        a[3] = L.W[p];
-        a[4] = L.O[p];
-        a[5] = L.W[p + 1];
-        a[6] = nine ? L.NW[p] : 0.0;
-        a[7] = L.S[p + ld];
-        a[8] = nine ? L.SW[p + ld + 1] : 0.0;
-        const double o = a[4];
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
+
+// --------------------------------------- features, first and second layer
+// One pass for the features X(p) = bf16(fl32(a_c(p) / O(p))) of the nine
+// coefficients SW..NE, the first layer H1 = bf16(max(conv(X), 0)) on the fine
+// points and the second layer H2 on the coarse points (stride 2, centre 2I).
+// A workgroup owns 62 coarse columns and a block of coarse rows, and streams
+// through the rows: step J forms X rows 2J+1 and 2J+2, H1 rows 2J and 2J+1 from
+// the four X rows it holds, and H2 row J from H1 rows 2J-1, 2J, 2J+1, the rows
+// in LDS rings of four, two barriers a step.  The first layer's 128 columns by
+// two rows are 16 groups of 16 points for the four waves, the second layer's
+// 64 points one group each; both layers' weights stay in registers for the
+// whole block.  X, H1 (the backward pass and exports read them) and H2 go to
+// memory once and none is read back here.  The products are accumulated taps
+// outermost, then blocks of 16 input channels, as in k_conv.  A 4095^2 level:
+// 653 us, 2.3 GB at 3.6 TB/s, the matrix cores busy for a third of it, where
+// the three passes took 204 + 991 + 674 (each wave of a layer fetched the
+// weights for 64 points, and X and H1 were read back).
+//
+// LDS holds blocks of four channels apart, [block][column] of 8 bytes with H1's
+// odd and even columns apart: the 16 points a group reads are contiguous, and
+// the strides put the reads and writes of two channel blocks into different
+// halves of the 64 banks.
+constexpr int NC_I = 62;                       // coarse columns of a workgroup
+constexpr int NC_XB = 144, NC_XR = 4 * NC_XB;  // X: column blocks, row (in 8 bytes)
+constexpr int NC_HB = 80, NC_HP = 8 * NC_HB + 8, NC_HR = 2 * NC_HP;   // H1: block, parity, row
+
+struct Conv12 {
+    Lev<double> L;
+    const uint2 *w1, *w2;
+    const float *b1, *b2;
+    bf16_t *X, *H1, *H2;
+    int rows;                  // coarse rows of a workgroup
+};
+
+__device__ __forceinline__ bf16x4 as_bf16x4(uint2 v) { return __builtin_bit_cast(bf16x4, v); }
+
+template <bool NINE>
+__global__ __launch_bounds__(256, 2) void k_net_conv12(Conv12 a)
+{
+    __shared__ uint2 sX[4 * NC_XR], sH[4 * NC_HR];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, l15 = lane & 15, kb4 = lane >> 4;
+    const int n = a.L.n, nc = (n - 1) / 2, xs = n + 2, hs = n + 3, cs = nc + 3;
+    const size_t ld = a.L.ld;
+    const int I0 = 1 + (int)blockIdx.x * NC_I, J0 = 1 + (int)blockIdx.y * a.rows, J1 = min(J0 + a.rows, nc + 2);
+    const int c0 = 2 * I0 - 1;                  // H1 column 0 of the strip; X column 0 is c0 - 1
+    const int clast = min(c0 + 2 * NC_I - 1, n);   // last owned fine column
+    const int rfirst = 2 * J0 - 1, rlast = min(2 * J1 - 2, n);   // owned fine rows
+
+    bf16x4 w1[18], w2[36];
 #pragma unroll
-        for (int c = 0; c < 9; ++c) v[c] = bf16_rne((float)(a[c] / o));
+    for (int q = 0; q < 18; ++q) w1[q] = as_bf16x4(a.w1[q * 64 + lane]);
+#pragma unroll
+    for (int q = 0; q < 36; ++q) w2[q] = as_bf16x4(a.w2[q * 64 + lane]);
+    f32x4 b1[2], b2[2];
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            b1[mb][e] = a.b1[mb * 16 + 4 * kb4 + e];
+            b2[mb][e] = a.b2[mb * 16 + 4 * kb4 + e];
+        }
+
+    // features: this thread's point of step J is row 2J + 1 + (t >> 7), column
+    // c0 - 1 + (t & 127); its coefficients are requested one step ahead
+    const int fx = t & 127, fi = c0 - 1 + fx, fr = t >> 7;
+    const bool fcol = fi >= 1 && fi <= n;
+    double f[9];
+    auto want = [&](int J) {
+        const int row = 2 * J + 1 + fr;
+        const bool ok = fcol && row >= 1 && row <= n;
+        const size_t p = ok ? (size_t)row * ld + fi : ld + 1;
+        f[1] = a.L.S[p];
+        f[3] = a.L.W[p];
+        f[4] = a.L.O[p];
+        f[5] = a.L.W[p + 1];
+        f[7] = a.L.S[p + ld];
+        if (NINE) {
+            f[0] = a.L.SW[p];
+            f[2] = a.L.NW[p + 1 - ld];
+            f[6] = a.L.NW[p];
+            f[8] = a.L.SW[p + ld + 1];
+        }
+    };
+    auto features = [&](int J, bool keep) {
+        const int row = 2 * J + 1 + fr;
+        const bool ok = fcol && row >= 1 && row <= n;
+        float v[9];
+        const double o = f[4];
+        // (a five-point row's corners: zero over the centre, computed once)
+        const float z = NINE ? 0.0f : (float)(0.0 / o);
+#pragma unroll
+        for (int c = 0; c < 9; ++c) {
+            const bool corner = c == 0 || c == 2 || c == 6 || c == 8;
+            v[c] = ok ? (corner && !NINE ? z : (float)(f[c] / o)) : 0.0f;
+        }
+        uint2 q[3];
+        q[0] = make_uint2(bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3]));
+        q[1] = make_uint2(bf16_pair(v[4], v[5]), bf16_pair(v[6], v[7]));
+        q[2] = make_uint2(bf16_pair(v[8], 0.0f), 0u);
+        uint2 *s = sX + (row & 3) * NC_XR + fx;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) s[k * NC_XB] = q[k];
+        if (keep && ok && row >= rfirst && row <= rlast && fi >= c0 && fi <= clast) {
+            uint4 *dst = reinterpret_cast<uint4 *>(a.X + ((size_t)row * xs + fi) * 16);
+            dst[0] = make_uint4(q[0].x, q[0].y, q[1].x, q[1].y);
+            dst[1] = make_uint4(q[2].x, q[2].y, 0u, 0u);
+        }
+    };
+
+    // X columns past the strip's 128 are read by the last group's points that
+    // nothing uses: their block is zero, as are channels 12 .. 15
+    for (int q = t; q < 4 * NC_XR; q += 256) sX[q] = make_uint2(0, 0);
+    want(J0 - 2);
+    __syncthreads();
+    features(J0 - 2, false);
+    want(J0 - 1);
+    features(J0 - 1, true);
+    for (int J = J0 - 1; J < J1; ++J) {
+        __syncthreads();
+        if (J + 1 < J1) want(J + 1);
+        // H1: row 2J + (wave >> 1), four groups of 16 columns
+        {
+            const int row = 2 * J + (wave >> 1), g0 = 64 * (wave & 1);
+            const bool rok = row >= 1 && row <= n, rown = row >= rfirst && row <= rlast;
+            uint2 *h = sH + (row & 3) * NC_HR + (l15 & 1) * NC_HP + kb4 * NC_HB;
+            const uint2 *x[3];
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy) x[dy] = sX + ((row + dy - 1) & 3) * NC_XR + kb4 * NC_XB + g0 + l15;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                bf16x4 in[9];
+#pragma unroll
+                for (int q = 0; q < 9; ++q) in[q] = as_bf16x4(x[q / 3][16 * g + q % 3]);
+                f32x4 acc[2] = {b1[0], b1[1]};
+#pragma unroll
+                for (int q = 0; q < 9; ++q)
+#pragma unroll
+                    for (int mb = 0; mb < 2; ++mb)
+                        acc[mb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w1[2 * q + mb], in[q], acc[mb], 0, 0, 0);
+                const int rel = g0 + 16 * g + l15, i = c0 + rel;
+                const bool ok = rok && i <= n;
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb) {
+                    uint2 v = make_uint2(bf16_pair(fmaxf(acc[mb][0], 0.0f), fmaxf(acc[mb][1], 0.0f)),
+                                         bf16_pair(fmaxf(acc[mb][2], 0.0f), fmaxf(acc[mb][3], 0.0f)));
+                    if (!ok) v = make_uint2(0, 0);
+                    h[mb * 4 * NC_HB + (rel >> 1)] = v;
+                    if (rown && i <= clast)
+                        *reinterpret_cast<uint2 *>(a.H1 + ((size_t)row * hs + i) * 32 + mb * 16 + 4 * kb4) = v;
+                }
+            }
+        }
+        __syncthreads();
+        if (J >= J0) {
+            const int I = I0 + 16 * wave + l15;
+            f32x4 acc[2] = {b2[0], b2[1]};
+#pragma unroll
+            for (int q = 0; q < 9; ++q) {
+                const int dx = q % 3, dy = q / 3 - 1;
+                const uint2 *h = sH + ((2 * J + dy) & 3) * NC_HR + (dx & 1) * NC_HP + kb4 * NC_HB + 16 * wave + l15 +
+                                 (dx >> 1);
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) {
+                    const bf16x4 in = as_bf16x4(h[kb * 4 * NC_HB]);
+#pragma unroll
+                    for (int mb = 0; mb < 2; ++mb)
+                        acc[mb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w2[(q * 2 + kb) * 2 + mb], in, acc[mb], 0,
+                                                                           0, 0);
+                }
+            }
+            if (I < I0 + NC_I && I <= nc + 1) {
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb)
+                    *reinterpret_cast<uint2 *>(a.H2 + ((size_t)J * cs + I) * 32 + mb * 16 + 4 * kb4) =
+                        make_uint2(bf16_pair(fmaxf(acc[mb][0], 0.0f), fmaxf(acc[mb][1], 0.0f)),
+                                   bf16_pair(fmaxf(acc[mb][2], 0.0f), fmaxf(acc[mb][3], 0.0f)));
+            }
+        }
+        if (J + 1 < J1) features(J + 1, true);
     }
-    uint2 *dst = reinterpret_cast<uint2 *>(X + ((size_t)j * side + i) * 16);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) dst[q] = pack4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+}
+
+// The zero rings of X (0, n+1), H1 (0, n+1, n+2) and H2 (0, nc+2): blockIdx.y
+// selects the array, one thread 16 bytes of one point.
+static __global__ void k_net_rings(bf16_t *X, bf16_t *H1, bf16_t *H2, int n)
+{
+    const int nc = (n - 1) / 2, which = blockIdx.y;
+    bf16_t *a = which == 0 ? X : which == 1 ? H1 : H2;
+    const int side = which == 0 ? n + 2 : which == 1 ? n + 3 : nc + 3, ch = which == 0 ? 2 : 4;
+    const int edges = which == 1 ? 3 : 2;      // rows, then columns, of the ring
+    const int g = blockIdx.x * blockDim.x + threadIdx.x, part = g % ch, p = g / ch;
+    if (p >= 2 * edges * side) return;
+    const int e = p / side, k = p % side, b = e % edges;
+    const int at = b == 0 ? 0 : side - b;
+    const size_t q = e < edges ? (size_t)at * side + k : (size_t)k * side + at;
+    reinterpret_cast<uint4 *>(a)[q * ch + part] = make_uint4(0, 0, 0, 0);
 }
 
 // ------------------------------------------------------------- convolutions
 // Implicit-GEMM 3x3 convolution, D[out channel][point] = sum over taps and
 // input channels of W * input, groups of 16 output points of one grid row per wave.
-// MODE 0: input centre = output point (stride 1); 1: centre = 2 x output point
-// (stride 2); 2: transposed stride 1 (input at point - tap, backward of a
-// stride-1 layer); 3: transposed stride 2 (input at (point - tap) / 2 where
-// both coordinates are even).  Epilogues: EP_RELU stores bf16(max(z, 0));
+// MODE 0: input centre = output point (the third layer); 2: transposed stride 1
+// (input at point - tap, backward of a stride-1 layer); 3: transposed stride 2
+// (input at (point - tap) / 2 where both coordinates are even).  Epilogues:
 // EP_MASK stores bf16(z) where the mask activation is non-zero, else 0;
 // EP_OUT stores the eight FP32 outputs per point (the corrections that
 // k_net_apply turns into weight planes).  Points of the output domain outside
 // the valid region are written as zeros.
-enum { EP_RELU = 0, EP_MASK = 1, EP_OUT = 2 };
+enum { EP_MASK, EP_OUT };
 
 struct ConvArgs {
     const bf16_t *in;
@@ -137,7 +310,7 @@ struct ConvArgs {
     int cout;                    // real output channels
     int lo, hi;                  // output domain [lo, hi]^2
     int vlo, vhi;                // valid region [vlo, vhi]^2
-    bf16_t *out;                 // EP_RELU / EP_MASK
+    bf16_t *out;                 // EP_MASK
     int out_side;
     const bf16_t *mask;          // EP_MASK: activation (COUTP channels per point)
     int mask_side;
@@ -191,7 +364,6 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a)
             bool ok = valid;
             int sx, sy;
             if (MODE == 0) { sx = pi + dx; sy = j + dy; }
-            else if (MODE == 1) { sx = 2 * pi + dx; sy = 2 * j + dy; }
             else if (MODE == 2) { sx = pi - dx; sy = j - dy; }
             else {
                 ok = ok && (((pi - dx) & 1) == 0) && (((j - dy) & 1) == 0);
@@ -250,17 +422,12 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a)
         for (int mb = 0; mb < MB; ++mb) {
             const int c0 = mb * 16 + kq;
             bf16_t h[4];
-            if (EP == EP_MASK) {
-                uint2 mv = make_uint2(0, 0);
-                if (valid) mv = *reinterpret_cast<const uint2 *>(a.mask + ((size_t)j * a.mask_side + pi) * COUTP + c0);
-                const bf16_t m[4] = {(bf16_t)(mv.x & 0xffff), (bf16_t)(mv.x >> 16), (bf16_t)(mv.y & 0xffff),
-                                     (bf16_t)(mv.y >> 16)};
+            uint2 mv = make_uint2(0, 0);
+            if (valid) mv = *reinterpret_cast<const uint2 *>(a.mask + ((size_t)j * a.mask_side + pi) * COUTP + c0);
+            const bf16_t m[4] = {(bf16_t)(mv.x & 0xffff), (bf16_t)(mv.x >> 16), (bf16_t)(mv.y & 0xffff),
+                                 (bf16_t)(mv.y >> 16)};
 #pragma unroll
-                for (int e = 0; e < 4; ++e) h[e] = (valid && m[e] != 0) ? bf16_rne(acc[mb][e]) : (bf16_t)0;
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) h[e] = valid ? bf16_rne(fmaxf(acc[mb][e], 0.0f)) : (bf16_t)0;
-            }
+            for (int e = 0; e < 4; ++e) h[e] = (valid && m[e] != 0) ? bf16_rne(acc[mb][e]) : (bf16_t)0;
             *reinterpret_cast<uint2 *>(a.out + base + c0) = pack4(h[0], h[1], h[2], h[3]);
         }
     }
@@ -632,21 +799,18 @@ bmg_status forward(bmg_net *h, const Lev<double> &L, bool nine, double *Ci, int 
     if (n > h->max_n) return fail(BMG_EINVAL, "level of %d points exceeds the network's max_n=%d", n, h->max_n);
     const Wts<double> C{Ci, ldc, ps};
     launch_weights(L, C, nc, flags, tiles(nc + 1, nc + 1), dim3(32, 8), h->st);
-    hipLaunchKernelGGL(k_net_features, tiles(n + 2, n + 2), dim3(32, 8), 0, h->st, L, nine, h->X);
-    LAUNCHCHK();
     const float *P = h->P;
+    hipLaunchKernelGGL(k_net_rings, dim3((6 * (n + 3) * 4 + 255) / 256, 3), dim3(256), 0, h->st, h->X, h->H1, h->H2, n);
+    // two workgroups fit on a CU: as few rows each as fill one round of them
+    const int strips = (nc + 1 + NC_I - 1) / NC_I, blocks = std::max(1, 512 / strips);
+    const int rows = (nc + 1 + blocks - 1) / blocks;
+    const Conv12 c{L, h->PK + PKO1, h->PK + PKO2, P + OB1, P + OB2, h->X, h->H1, h->H2, rows};
+    const dim3 g12(strips, (nc + 1 + rows - 1) / rows);
+    if (nine) hipLaunchKernelGGL((k_net_conv12<true>), g12, dim3(256), 0, h->st, c);
+    else hipLaunchKernelGGL((k_net_conv12<false>), g12, dim3(256), 0, h->st, c);
+    LAUNCHCHK();
     ConvArgs a{};
-    // conv1: fine points [1, n], written over [0, n+2] (zero ring of H1)
-    a.in = h->X; a.in_side = n + 2; a.w = h->PK + PKO1; a.bias = P + OB1; a.cout = 32;
-    a.lo = 0; a.hi = n + 2; a.vlo = 1; a.vhi = n; a.out = h->H1; a.out_side = n + 3;
-    TRY((conv<16, 32, 0, EP_RELU>(h, a)));
-    // conv2: coarse points [1, nc+1] centred on fine 2I, written over [0, nc+2]
-    a = ConvArgs{};
-    a.in = h->H1; a.in_side = n + 3; a.w = h->PK + PKO2; a.bias = P + OB2; a.cout = 32;
-    a.lo = 0; a.hi = nc + 2; a.vlo = 1; a.vhi = nc + 1; a.out = h->H2; a.out_side = nc + 3;
-    TRY((conv<32, 32, 1, EP_RELU>(h, a)));
-    // conv3: the eight outputs at [1, nc+1], zeros at index 0
-    a = ConvArgs{};
+    // third layer: the eight outputs at [1, nc+1], zeros at index 0
     a.in = h->H2; a.in_side = nc + 3; a.w = h->PK + PKO3; a.bias = P + OB3; a.cout = 8;
     a.lo = 0; a.hi = nc + 1; a.vlo = 1; a.vhi = nc + 1; a.yout = h->Y; a.out_side = nc + 2;
     TRY((conv<32, 16, 0, EP_OUT>(h, a)));
