@@ -293,28 +293,21 @@ static __global__ void k_net_rings(bf16_t *X, bf16_t *H1, bf16_t *H2, int n)
 // ------------------------------------------------------------- convolutions
 // Implicit-GEMM 3x3 convolution, D[out channel][point] = sum over taps and
 // input channels of W * input, groups of 16 output points of one grid row per wave.
-// MODE 0: input centre = output point (the third layer); 2: transposed stride 1
-// (input at point - tap, backward of a stride-1 layer); 3: transposed stride 2
-// (input at (point - tap) / 2 where both coordinates are even).  Epilogues:
-// EP_MASK stores bf16(z) where the mask activation is non-zero, else 0;
-// EP_OUT stores the eight FP32 outputs per point (the corrections that
-// k_net_apply turns into weight planes).  Points of the output domain outside
-// the valid region are written as zeros.
-enum { EP_MASK, EP_OUT };
+// The backward layers, STRIDE 1: input at point - tap; 2: input at
+// (point - tap) / 2 where both coordinates are even.  Stores bf16(z) where the
+// mask activation is non-zero, else 0; points of the output domain outside the
+// valid region are written as zeros.
 
 struct ConvArgs {
     const bf16_t *in;
     int in_side;                 // points per row of the input grid
     const uint2 *w;              // packed A operands of this layer
-    const float *bias;           // nullptr: none
-    int cout;                    // real output channels
     int lo, hi;                  // output domain [lo, hi]^2
     int vlo, vhi;                // valid region [vlo, vhi]^2
-    bf16_t *out;                 // EP_MASK
+    bf16_t *out;
     int out_side;
-    const bf16_t *mask;          // EP_MASK: activation (COUTP channels per point)
+    const bf16_t *mask;          // activation (COUTP channels per point)
     int mask_side;
-    float *yout;                 // EP_OUT: 8 values per point, out_side points per row
 };
 
 // Each wave keeps the layer's A operands (all taps and channel blocks) in
@@ -323,7 +316,7 @@ struct ConvArgs {
 // per group; every group's products are accumulated in the same order as
 // before (taps, input blocks, output blocks).
 constexpr int CONV_GROUPS = 4;
-template <int CINP, int COUTP, int MODE, int EP>
+template <int CINP, int COUTP, int STRIDE>
 __global__ __launch_bounds__(256) void k_conv(ConvArgs a)
 {
     constexpr int KB = CINP / 16, MB = COUTP / 16, NA = 9 * KB * MB;
@@ -343,15 +336,6 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a)
         wr[q][2] = (short)(wv.y & 0xffff);
         wr[q][3] = (short)(wv.y >> 16);
     }
-    float bias[MB][4];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int co = mb * 16 + kq + e;
-            bias[mb][e] = (a.bias && co < a.cout) ? a.bias[co] : 0.0f;
-        }
-
     // the input fragments of a group (tap t, channel block kb); those of the
     // next group are requested before this group's products, so a wave waits
     // for its inputs once rather than once per group
@@ -363,8 +347,7 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a)
             const int dx = t % 3 - 1, dy = t / 3 - 1;
             bool ok = valid;
             int sx, sy;
-            if (MODE == 0) { sx = pi + dx; sy = j + dy; }
-            else if (MODE == 2) { sx = pi - dx; sy = j - dy; }
+            if (STRIDE == 1) { sx = pi - dx; sy = j - dy; }
             else {
                 ok = ok && (((pi - dx) & 1) == 0) && (((j - dy) & 1) == 0);
                 sx = (pi - dx) >> 1;
@@ -392,7 +375,7 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a)
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[mb][e] = bias[mb][e];
+            for (int e = 0; e < 4; ++e) acc[mb][e] = 0.0f;
 #pragma unroll
         for (int t = 0; t < 9; ++t)
 #pragma unroll
@@ -406,17 +389,6 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a)
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) cur[t][kb] = nxt[t][kb];
         if (!in_dom) continue;
-        if (EP == EP_OUT) {
-            if (kq < 8) {
-                float4 v;
-                v.x = valid ? acc[0][0] : 0.0f;
-                v.y = valid ? acc[0][1] : 0.0f;
-                v.z = valid ? acc[0][2] : 0.0f;
-                v.w = valid ? acc[0][3] : 0.0f;
-                *reinterpret_cast<float4 *>(a.yout + ((size_t)j * a.out_side + pi) * 8 + kq) = v;
-            }
-            continue;
-        }
         const size_t base = ((size_t)j * a.out_side + pi) * COUTP;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
@@ -433,55 +405,129 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a)
     }
 }
 
-// The weight planes of a level from BoxMG's (already in C) and the network's
-// outputs y (8 FP32 values per coarse point, side nc + 2): corrections that
-// keep each F-point's weight sum, in FP64,
+// The third layer (eight FP32 outputs y per coarse point, kept in Y, side
+// nc + 2) and the weight planes of a level from BoxMG's (already in C) and y:
+// corrections that keep each F-point's weight sum, in FP64,
 //   x-edge: e = 0.5 (y_LR - y_LL), LR += e, LL -= e;
 //   y-edge: e = 0.5 (y_LA - y_LB), LA += e, LB -= e;
 //   cell centre: m = 0.25 (((y_LNE + y_LNW) + y_LSE) + y_LSW), w += y_w - m;
 // the weights of F-points that do not exist (x-edges in row nc + 1, y-edges in
 // column nc + 1) and the row and column 0 are zero.
-static __global__ void k_net_apply(Wts<double> C, int nc, const float *__restrict__ Y)
+//
+// A wave owns 16 columns and streams up a block of rows: the three input rows
+// of a point and the one being fetched stay in registers (slots are
+// compile-time, the loop is unrolled over the four), the layer's weights too,
+// and the next row's planes are requested one row ahead.  The products give
+// lanes 0-15 outputs 0-3 of their point and lanes 16-31 outputs 4-7, so each
+// of the two corrects four planes, with the other's outputs by a lane swap.
+struct NetOut {
+    const bf16_t *H2;
+    const uint2 *w;
+    const float *bias;
+    float *Y;
+    Wts<double> C;
+    int nc, rows;
+};
+
+struct NetOutWave {
+    bf16x4 w[18], in[4][6];    // weights; rows, (dx, channel block)
+    double pl[4];              // the next row's planes
+    f32x4 b;
+    const bf16_t *col[3];
+    double *plane;             // this lane's first plane at row 0
+    int I, nc, kb4, ld;
+    size_t ps, side;
+
+    template <int SL>
+    __device__ __forceinline__ void request(int row)
+    {
+        const size_t o = (size_t)min(max(row, 0), nc + 2) * side * 32;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) in[SL][q] = *reinterpret_cast<const bf16x4 *>(col[q >> 1] + o + (q & 1) * 16);
+    }
+    __device__ __forceinline__ void planes(int row)
+    {
+        const double *p = plane + (size_t)min(row, nc + 1) * ld;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pl[k] = p[k * ps];
+    }
+    // rows J + M, ..: slot of row J + M + d is (M + 1 + d) & 3
+    template <int M>
+    __device__ __forceinline__ void turn(const NetOut &a, int J, int J1)
+    {
+        if constexpr (M < 4) {
+            if (J >= J1) return;
+            double c[4] = {pl[0], pl[1], pl[2], pl[3]};
+            request<(M + 3) & 3>(J + 2);
+            planes(J + 1);
+            f32x4 acc = b;
+#pragma unroll
+            for (int t = 0; t < 9; ++t)
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w[t * 2 + kb],
+                                                                   in[(M + t / 3) & 3][(t % 3) * 2 + kb], acc, 0, 0, 0);
+            const bool some = I >= 1 && J >= 1;
+            float own[4], other[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                own[e] = some ? acc[e] : 0.0f;
+                other[e] = __shfl_xor(own[e], 16);
+            }
+            if (kb4 < 2 && I <= nc + 1) {
+                *reinterpret_cast<float4 *>(a.Y + ((size_t)J * (nc + 2) + I) * 8 + 4 * kb4) =
+                    make_float4(own[0], own[1], own[2], own[3]);
+                const bool hi = kb4 == 1;
+                double y[8];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    y[e] = (double)(hi ? other[e] : own[e]);
+                    y[4 + e] = (double)(hi ? own[e] : other[e]);
+                }
+                const double ex = 0.5 * (y[LR] - y[LL]), ey = 0.5 * (y[LA] - y[LB]);
+                const double m = 0.25 * (((y[LNE] + y[LNW]) + y[LSE]) + y[LSW]);
+                // planes LNE, LA, LNW, LR or LL, LSE, LB, LSW
+                const double d[4] = {hi ? -ex : y[LNE] - m, hi ? y[LSE] - m : ey, hi ? -ey : y[LNW] - m,
+                                     hi ? y[LSW] - m : ex};
+                const bool xe = some && J <= nc, ye = some && I <= nc;
+                const bool ok[4] = {hi ? xe : some, hi ? some : ye, hi ? ye : some, hi ? some : xe};
+                double *p = plane + (size_t)J * ld;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) p[k * ps] = ok[k] ? c[k] + d[k] : 0.0;
+            }
+            turn<M + 1>(a, J + 1, J1);
+        }
+    }
+};
+
+static __global__ __launch_bounds__(256, 2) void k_net_out(NetOut a)
 {
-    const int I = blockIdx.x * blockDim.x + threadIdx.x;
-    const int J = blockIdx.y * blockDim.y + threadIdx.y;
-    if (I > nc + 1 || J > nc + 1) return;
-    const size_t c = (size_t)J * C.ld + I;
-    double *w = C.p;
-    if (I == 0 || J == 0) {
+    const int lane = threadIdx.x & 63, nc = a.nc, g = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (16 * g > nc + 1) return;   // no barriers below
+    NetOutWave W;
+    W.nc = nc;
+    W.I = 16 * g + (lane & 15);
+    W.kb4 = lane >> 4;
+    W.ld = a.C.ld;
+    W.ps = a.C.ps;
+    W.side = nc + 3;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) w[k * C.ps + c] = 0.0;
-        return;
-    }
-    double y[8];
-    const float *yp = Y + ((size_t)J * (nc + 2) + I) * 8;
+    for (int q = 0; q < 18; ++q) W.w[q] = as_bf16x4(a.w[q * 64 + lane]);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) y[k] = (double)yp[k];
-    if (J <= nc) {
-        const double e = 0.5 * (y[LR] - y[LL]);
-        w[LR * C.ps + c] = w[LR * C.ps + c] + e;
-        w[LL * C.ps + c] = w[LL * C.ps + c] - e;
-    } else {
-        w[LR * C.ps + c] = 0.0;
-        w[LL * C.ps + c] = 0.0;
-    }
-    if (I <= nc) {
-        const double e = 0.5 * (y[LA] - y[LB]);
-        w[LA * C.ps + c] = w[LA * C.ps + c] + e;
-        w[LB * C.ps + c] = w[LB * C.ps + c] - e;
-    } else {
-        w[LA * C.ps + c] = 0.0;
-        w[LB * C.ps + c] = 0.0;
-    }
-    const double m = 0.25 * (((y[LNE] + y[LNW]) + y[LSE]) + y[LSW]);
-    w[LNE * C.ps + c] = w[LNE * C.ps + c] + (y[LNE] - m);
-    w[LNW * C.ps + c] = w[LNW * C.ps + c] + (y[LNW] - m);
-    w[LSE * C.ps + c] = w[LSE * C.ps + c] + (y[LSE] - m);
-    w[LSW * C.ps + c] = w[LSW * C.ps + c] + (y[LSW] - m);
+    for (int e = 0; e < 4; ++e) W.b[e] = W.kb4 < 2 ? a.bias[4 * W.kb4 + e] : 0.0f;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) W.col[d] = a.H2 + (size_t)min(max(W.I + d - 1, 0), nc + 2) * 32 + 4 * W.kb4;
+    W.plane = a.C.p + (size_t)(4 * (W.kb4 & 1)) * a.C.ps + min(W.I, nc + 1);
+    const int J0 = blockIdx.y * a.rows, J1 = min(J0 + a.rows, nc + 2);
+    W.request<0>(J0 - 1);
+    W.request<1>(J0);
+    W.request<2>(J0 + 1);
+    W.planes(J0);
+    for (int J = J0; J < J1; J += 4) W.turn<0>(a, J, J1);
 }
 
 // dL/dy of the output layer as the layer's bfloat16 input gradient: the
-// transpose of k_net_apply's map from y to the planes (the same FP64 order)
+// transpose of k_net_out's map from y to the planes (the same FP64 order)
 // at the valid coarse points, zeros on the ring and in channels 8..15.
 static __global__ void k_net_dy(const double *__restrict__ dCi, int ldc, size_t ps, int nc, bf16_t *__restrict__ D3)
 {
@@ -765,12 +811,12 @@ bmg_status repack(bmg_net *h)
     return BMG_OK;
 }
 
-template <int CINP, int COUTP, int MODE, int EP>
+template <int CINP, int COUTP, int STRIDE>
 bmg_status conv(bmg_net *h, ConvArgs a)
 {
     const int w = a.hi - a.lo + 1;
     const int per_block = 4 * 16 * CONV_GROUPS;
-    hipLaunchKernelGGL((k_conv<CINP, COUTP, MODE, EP>), dim3((w + per_block - 1) / per_block, w), dim3(256), 0, h->st,
+    hipLaunchKernelGGL((k_conv<CINP, COUTP, STRIDE>), dim3((w + per_block - 1) / per_block, w), dim3(256), 0, h->st,
                        a);
     LAUNCHCHK();
     return BMG_OK;
@@ -809,12 +855,10 @@ bmg_status forward(bmg_net *h, const Lev<double> &L, bool nine, double *Ci, int 
     if (nine) hipLaunchKernelGGL((k_net_conv12<true>), g12, dim3(256), 0, h->st, c);
     else hipLaunchKernelGGL((k_net_conv12<false>), g12, dim3(256), 0, h->st, c);
     LAUNCHCHK();
-    ConvArgs a{};
-    // third layer: the eight outputs at [1, nc+1], zeros at index 0
-    a.in = h->H2; a.in_side = nc + 3; a.w = h->PK + PKO3; a.bias = P + OB3; a.cout = 8;
-    a.lo = 0; a.hi = nc + 1; a.vlo = 1; a.vhi = nc + 1; a.yout = h->Y; a.out_side = nc + 2;
-    TRY((conv<32, 16, 0, EP_OUT>(h, a)));
-    hipLaunchKernelGGL(k_net_apply, tiles(nc + 2, nc + 2), dim3(32, 8), 0, h->st, C, nc, (const float *)h->Y);
+    // 12 waves fit on a CU: as few rows each as fill them all once
+    const int wgs = (nc + 2 + 63) / 64, parts = std::max(1, 768 / wgs), r3 = (nc + 2 + parts - 1) / parts;
+    const NetOut o{h->H2, h->PK + PKO3, P + OB3, h->Y, C, nc, r3};
+    hipLaunchKernelGGL(k_net_out, dim3(wgs, (nc + 2 + r3 - 1) / r3), dim3(256), 0, h->st, o);
     LAUNCHCHK();
     h->last_n = n;
     h->last_nine = nine;
@@ -831,17 +875,17 @@ bmg_status backward(bmg_net *h, const double *dCi, int ldc, size_t ps)
     // conv3: weights, then dH2 (masked by H2 > 0) -> D2
     TRY((wgrad<32, 16, 1>(h, h->H2, nc + 3, h->D3, nc + 3, 1, nc + 1, 32, 8, OW3, OB3)));
     ConvArgs a{};
-    a.in = h->D3; a.in_side = nc + 3; a.w = h->PK + PKO3T; a.cout = 32;
+    a.in = h->D3; a.in_side = nc + 3; a.w = h->PK + PKO3T;
     a.lo = 0; a.hi = nc + 2; a.vlo = 1; a.vhi = nc + 1; a.out = h->D2; a.out_side = nc + 3;
     a.mask = h->H2; a.mask_side = nc + 3;
-    TRY((conv<16, 32, 2, EP_MASK>(h, a)));
+    TRY((conv<16, 32, 1>(h, a)));
     // conv2: weights, then dH1 (masked by H1 > 0) -> D1 on the fine points
     TRY((wgrad<32, 32, 2>(h, h->H1, n + 3, h->D2, nc + 3, 1, nc + 1, 32, 32, OW2, OB2)));
     a = ConvArgs{};
-    a.in = h->D2; a.in_side = nc + 3; a.w = h->PK + PKO2T; a.cout = 32;
+    a.in = h->D2; a.in_side = nc + 3; a.w = h->PK + PKO2T;
     a.lo = 1; a.hi = n; a.vlo = 1; a.vhi = n; a.out = h->D1; a.out_side = n + 2;
     a.mask = h->H1; a.mask_side = n + 3;
-    TRY((conv<32, 32, 3, EP_MASK>(h, a)));
+    TRY((conv<32, 32, 2>(h, a)));
     // conv1: weights
     TRY((wgrad<16, 32, 1>(h, h->X, n + 2, h->D1, n + 2, 1, n, 9, 32, OW1, OB1)));
     return BMG_OK;
