@@ -1537,9 +1537,16 @@ bmg_status bmg_solve(bmg_solver *h, const double *rhs, double *x, double tol, bm
         const double refine = h->opt.refine_factor > 0 ? h->opt.refine_factor * tol : 0.0;
         const bool pp = postpre_ok(h);
         bool pending = false;
+        // a cycle with one fused pass that moves the fine iterate and one that
+        // runs unfused (its sweep count too large, or zero) leaves it in the
+        // other buffer, also when it is enqueued past the stop and does nothing
+        const bool moves_once = fused(h) && h->nlev >= 2 && (h->opt.nu1 >= 1 && h->opt.nu1 <= 3) !=
+                                                                (h->opt.nu2 >= 1 && h->opt.nu2 <= 2);
+        int enqueued = 0;
         while (true) {
             for (int t = 0; t < every; ++t) {
                 if (!refining) {
+                    ++enqueued;
                     if (pp && pending && h->opt.graph_mode && !h->pair_off && h->tr_class < 0 && t + 1 < every) {
                         TRY(cycle_pair_graph(h, tol, maxc, refine, &pending));
                         ++t;
@@ -1554,6 +1561,7 @@ bmg_status bmg_solve(bmg_solver *h, const double *rhs, double *x, double tol, bm
                 }
             }
             TRY(poll(h, cs));
+            if (cs[1] && !refining && moves_once && ((enqueued - cs[0]) & 1)) std::swap(h->L[0].u, h->ualt[0]);
             if (cs[1] == 4 && !refining) {
                 // the iterate becomes (XH, XL) = (u, 0); the next cycle starts
                 // from zero on r = B0 - A XH (the residual just recorded)
