@@ -504,26 +504,11 @@ static bool pre_weights_in_pass(const bmg_solver *h, int l, bool nine)
     return BMG_PRE_WEIGHTS_IN_PASS && std::is_same<T, double>::value && !nine && !learned && h->nrhs == 1;
 }
 
-// Tiles of a wave-stream pass on level l of every right-hand side.  An FP64
-// pre pass takes more than 256 registers, one wave per SIMD: the height is the
-// least that leaves all tiles in one round of 1024.  Half-height tiles (a
-// round of 2048, which FP32 and the post passes could hold) re-read more rows
-// for no more speed: 2047^2 pre 138 against 132 us, post 134 against 121.
-constexpr int WAVE_SLOTS = 1024;
+// Tiles of a wave-stream pass on level l of every right-hand side.
 TileGeo wave_tiles(const bmg_solver *h, int l, int hx)
 {
-    const int n = h->L[l].n, useful = WAVE_COLS - 2 * hx, strips = (n + useful) / useful;
-    int rows = h->opt.tile_rows > 0 ? h->opt.tile_rows : tuned_tile_rows(n);
-    if (rows <= 0) {
-        const int blocks = std::max(1, WAVE_SLOTS / (strips * h->nrhs));
-        rows = std::max(2, ((n + blocks - 1) / blocks + 1) & ~1);
-    }
-    TileGeo g;
-    g.hx = hx;
-    g.ht = std::max(2, std::min(rows, (n + 2) & ~1));
-    g.tiles_x = strips;
-    g.ntiles = strips * ((n + g.ht - 1) / g.ht);
-    g.nrhs = h->nrhs;
+    const int n = h->L[l].n;
+    TileGeo g = wave_geo(n, hx, h->opt.tile_rows > 0 ? h->opt.tile_rows : tuned_tile_rows(n), h->nrhs);
     g.kstop = h->kstop;
     g.kpart = h->kpart;
     g.ksf = h->ks[l];

@@ -33,6 +33,34 @@ namespace bmg {
 
 constexpr int WAVE_COLS = 128;
 
+// Stencils: five-point, nine-point (both symmetric, half of the couplings
+// stored), and five-point nonsymmetric, all four couplings of a row stored
+// with it: S and W in their planes, E in the one of SW and N in the one of NW.
+enum : int { FIVE = 0, NINE = 1, FIVE_NS = 2 };
+
+// Tiles of a wave-stream pass over n^2 points for nrhs right-hand sides, hx halo
+// columns on each side of a strip, of `rows` rows (0: chosen).  An FP64 pre pass
+// takes more than 256 registers, one wave per SIMD: the height is the least that
+// leaves all tiles in one round of 1024.  Half-height tiles (a round of 2048,
+// which FP32 and the post passes could hold) re-read more rows for no more
+// speed: 2047^2 pre 138 against 132 us, post 134 against 121.
+constexpr int WAVE_SLOTS = 1024;
+inline TileGeo wave_geo(int n, int hx, int rows, int nrhs)
+{
+    const int useful = WAVE_COLS - 2 * hx, strips = (n + useful) / useful;
+    if (rows <= 0) {
+        const int blocks = std::max(1, WAVE_SLOTS / (strips * nrhs));
+        rows = std::max(2, ((n + blocks - 1) / blocks + 1) & ~1);
+    }
+    TileGeo g;
+    g.hx = hx;
+    g.ht = std::max(2, std::min(rows, (n + 2) & ~1));
+    g.tiles_x = strips;
+    g.ntiles = strips * ((n + g.ht - 1) / g.ht);
+    g.nrhs = nrhs;
+    return g;
+}
+
 // Value of the lane to the west (lane 0: zero) or east (lane 63: zero).
 template <int CTRL>
 __device__ __forceinline__ float lane_shift(float v)
@@ -66,20 +94,20 @@ struct Pair {
     typedef T vec __attribute__((ext_vector_type(2)));
 };
 
-// LDS ring of a wave: W and on nine-point levels SW, NW, RX rows of 128
-// columns (and two elements that the last lane's read of "the next column"
+// LDS ring of a wave: W and on nine-point levels SW, NW (FIVE_NS: E), RX rows of
+// 128 columns (and two elements that the last lane's read of "the next column"
 // may touch).
-template <typename T, bool NINE, int NU>
+template <typename T, int KIND, int NU>
 struct WaveLds {
     static constexpr int RX = 2 * NU + 6;
-    T W[RX * WAVE_COLS], SW[NINE ? RX * WAVE_COLS : 0], NW[NINE ? RX * WAVE_COLS : 0], pad[2];
+    T W[RX * WAVE_COLS], SW[KIND != FIVE ? RX * WAVE_COLS : 0], NW[KIND == NINE ? RX * WAVE_COLS : 0], pad[2];
 };
 
 // What both passes share: geometry, the ring and the point update.  A tile is
 // streamed upward (DIR = 1) or downward (DIR = -1): the colours' order, even
 // rows before odd ones, is the same seen from either side.  Slot of row
 // e + DIR d at turn M of the unrolled loop (e = es + 2 M DIR mod RX).
-template <typename T, bool NINE, int NU, int DIR>
+template <typename T, int KIND, int NU, int DIR>
 struct WaveTile {
     static constexpr int RX = 2 * NU + 6;
     using V = typename Pair<T>::vec;
@@ -87,11 +115,12 @@ struct WaveTile {
     static constexpr int at(int d) { return ((2 * M + d) % RX + RX) % RX; }
 
     T u[RX][2], b[RX][2], O[RX][2], S[RX][2];
+    T N[KIND == FIVE_NS ? RX : 1][2];
     T *sW, *sSW, *sNW;         // this lane's pair in ring row 0
     int n, ld, i0, i0c, y0, y1;
     bool in0, in1, own;        // columns interior, pair owned
 
-    __device__ __forceinline__ void place(const Lev<T> &L, const TileGeo &G, int tid, WaveLds<T, NINE, NU> &lds)
+    __device__ __forceinline__ void place(const Lev<T> &L, const TileGeo &G, int tid, WaveLds<T, KIND, NU> &lds)
     {
         n = L.n;
         ld = L.ld;
@@ -130,10 +159,8 @@ struct WaveTile {
     {
         Couplings c;
         c.w = load(L.W, row);
-        if constexpr (NINE) {
-            c.sw = load(L.SW, row);
-            c.nw = load(L.NW, row);
-        }
+        if constexpr (KIND != FIVE) c.sw = load(L.SW, row);
+        if constexpr (KIND == NINE) c.nw = load(L.NW, row);
         return c;
     }
     __device__ __forceinline__ void next_couplings(const Lev<T> &L, int e, Couplings (&c)[2]) const
@@ -145,10 +172,8 @@ struct WaveTile {
     __device__ __forceinline__ void put_couplings(const Couplings &c)
     {
         *reinterpret_cast<V *>(sW + SL * WAVE_COLS) = c.w;
-        if constexpr (NINE) {
-            *reinterpret_cast<V *>(sSW + SL * WAVE_COLS) = c.sw;
-            *reinterpret_cast<V *>(sNW + SL * WAVE_COLS) = c.nw;
-        }
+        if constexpr (KIND != FIVE) *reinterpret_cast<V *>(sSW + SL * WAVE_COLS) = c.sw;
+        if constexpr (KIND == NINE) *reinterpret_cast<V *>(sNW + SL * WAVE_COLS) = c.nw;
     }
     // b, O, S of a row into its slot
     template <int SL, bool WITH_B = true>
@@ -161,6 +186,10 @@ struct WaveTile {
         const V vo = load(L.O, row), vs = load(L.S, row);
         O[SL][0] = vo.x; O[SL][1] = vo.y;
         S[SL][0] = vs.x; S[SL][1] = vs.y;
+        if constexpr (KIND == FIVE_NS) {
+            const V vn = load(L.NW, row);
+            N[SL][0] = vn.x; N[SL][1] = vn.y;
+        }
     }
     // a row that has arrived: O = 1 where there is no equation
     template <int SL>
@@ -175,13 +204,14 @@ struct WaveTile {
     template <int C, int SD, int S0, int SU>
     __device__ __forceinline__ T offdiag() const
     {
-        if constexpr (!NINE) {
+        if constexpr (KIND != NINE) {
             const T uw = C ? u[S0][0] : from_west(u[S0][1]), ue = C ? from_east(u[S0][0]) : u[S0][1];
             T s = b[S0][C];
             s -= S[S0][C] * u[SD][C];
             s -= sW[S0 * WAVE_COLS + C] * uw;
-            s -= sW[S0 * WAVE_COLS + C + 1] * ue;
-            s -= S[SU][C] * u[SU][C];
+            s -= (KIND == FIVE_NS ? sSW[S0 * WAVE_COLS + C] : sW[S0 * WAVE_COLS + C + 1]) * ue;
+            if constexpr (KIND == FIVE_NS) s -= N[S0][C] * u[SU][C];
+            else s -= S[SU][C] * u[SU][C];
             return s;
         }
         const T uwd = C ? u[SD][0] : from_west(u[SD][1]), ued = C ? from_east(u[SD][0]) : u[SD][1];
@@ -213,25 +243,30 @@ struct WaveTile {
         return s;
     }
     // square of the accurate residual at column C of the row in slot S0 (the
-    // terms of post_tile)
+    // terms of post_tile; FIVE_NS: of the plain residual)
     template <int C, int SD, int S0, int SU>
     __device__ __forceinline__ double resid2() const
     {
-        constexpr int N = NINE ? 9 : 5;
+        if constexpr (KIND == FIVE_NS) {
+            T s = offdiag<C, SD, S0, SU>();
+            s -= O[S0][C] * u[S0][C];
+            return s * s;
+        }
+        constexpr int N = KIND == NINE ? 9 : 5;
         double a[N], x[N];
         int q = 0;
         auto term = [&](double ai, double xi) {
             a[q] = ai;
             x[q++] = xi;
         };
-        if constexpr (NINE) term(sSW[S0 * WAVE_COLS + C], C ? u[SD][0] : from_west(u[SD][1]));
+        if constexpr (KIND == NINE) term(sSW[S0 * WAVE_COLS + C], C ? u[SD][0] : from_west(u[SD][1]));
         term(S[S0][C], u[SD][C]);
-        if constexpr (NINE) term(sNW[SD * WAVE_COLS + C + 1], C ? from_east(u[SD][0]) : u[SD][1]);
+        if constexpr (KIND == NINE) term(sNW[SD * WAVE_COLS + C + 1], C ? from_east(u[SD][0]) : u[SD][1]);
         term(sW[S0 * WAVE_COLS + C], C ? u[S0][0] : from_west(u[S0][1]));
         term(sW[S0 * WAVE_COLS + C + 1], C ? from_east(u[S0][0]) : u[S0][1]);
-        if constexpr (NINE) term(sNW[S0 * WAVE_COLS + C], C ? u[SU][0] : from_west(u[SU][1]));
+        if constexpr (KIND == NINE) term(sNW[S0 * WAVE_COLS + C], C ? u[SU][0] : from_west(u[SU][1]));
         term(S[SU][C], u[SU][C]);
-        if constexpr (NINE) term(sSW[SU * WAVE_COLS + C + 1], C ? from_east(u[SU][0]) : u[SU][1]);
+        if constexpr (KIND == NINE) term(sSW[SU * WAVE_COLS + C + 1], C ? from_east(u[SU][0]) : u[SU][1]);
         term(O[S0][C], u[S0][C]);
         double s = b[S0][C], cc = 0.0, ns, se;
 #pragma unroll
@@ -292,9 +327,9 @@ __device__ __forceinline__ bool wave_up(const TileGeo &G, int tid) { return !((t
 // iterate is known to be zero (a coarse level's first visit in a cycle).  IRIN
 // (see IrArgs): b is the scaled FP64 residual, also stored as the FP32
 // right-hand side.
-template <typename T, bool NINE, int NU, int DIR, bool IRIN = false>
-struct WavePre : WaveTile<T, NINE, NU, DIR> {
-    using B = WaveTile<T, NINE, NU, DIR>;
+template <typename T, int KIND, int NU, int DIR, bool IRIN = false>
+struct WavePre : WaveTile<T, KIND, NU, DIR> {
+    using B = WaveTile<T, KIND, NU, DIR>;
     using V = typename B::V;
     static constexpr int RX = B::RX;
     T pr0[2], pr1[2];          // residual of the coarse row's f and of the odd row behind it
@@ -306,7 +341,7 @@ struct WavePre : WaveTile<T, NINE, NU, DIR> {
     double inv;
 
     __device__ __forceinline__ void run(const Lev<T> &L, T *__restrict__ uout, const Wts<T> &Cw, const Lev<T> &Cl,
-                                        const TileGeo &G, int tid, WaveLds<T, NINE, NU> &lds, bool zero_u,
+                                        const TileGeo &G, int tid, WaveLds<T, KIND, NU> &lds, bool zero_u,
                                         const IrArgs &ir = {})
     {
         B::place(L, G, tid, lds);
@@ -451,7 +486,7 @@ private:
     }
 };
 
-template <typename T, bool NINE, int NU, bool ZU>
+template <typename T, int KIND, int NU, bool ZU>
 __global__ __launch_bounds__(64, 1) void k_pre_wave(Lev<T> L, T *__restrict__ uout, Wts<T> C, Lev<T> Cl, TileGeo G,
                                                     const int *stop)
 {
@@ -460,12 +495,12 @@ __global__ __launch_bounds__(64, 1) void k_pre_wave(Lev<T> L, T *__restrict__ uo
     if (stopped(stop ? stop + k * G.kstop : stop)) return;
     L.u += k * G.ksf; L.b += k * G.ksf; uout += k * G.ksf;
     Cl.u += k * G.ksc; Cl.b += k * G.ksc;
-    __shared__ WaveLds<T, NINE, NU> S;
+    __shared__ WaveLds<T, KIND, NU> S;
     if (wave_up(G, tid)) {
-        WavePre<T, NINE, NU, 1> P;
+        WavePre<T, KIND, NU, 1> P;
         P.run(L, uout, C, Cl, G, tid, S, ZU);
     } else {
-        WavePre<T, NINE, NU, -1> P;
+        WavePre<T, KIND, NU, -1> P;
         P.run(L, uout, C, Cl, G, tid, S, ZU);
     }
 }
@@ -491,9 +526,9 @@ __global__ __launch_bounds__(64, 1) void k_pre_ir_wave(Lev<float> L, float *__re
 }
 
 // A tile whose rows enter as u + P e_c.
-template <typename T, bool NINE, int NU, int DIR>
-struct WaveInterp : WaveTile<T, NINE, NU, DIR> {
-    using B = WaveTile<T, NINE, NU, DIR>;
+template <typename T, int KIND, int NU, int DIR>
+struct WaveInterp : WaveTile<T, KIND, NU, DIR> {
+    using B = WaveTile<T, KIND, NU, DIR>;
     using V = typename B::V;
     T e0, w[8];                // e_c of row e / 2 at I; the next step's weights
     T en;                      // e_c of the coarse row after it
@@ -627,16 +662,16 @@ __device__ __forceinline__ void wave_sum_to(double acc, double *out)
 
 // Interpolation and nu sweeps, with NORM also the tile's sum of squares of the
 // accurate residual into part[tid] (results as post_tile).
-template <typename T, bool NINE, int NU, int DIR, bool NORM>
-struct WavePost : WaveInterp<T, NINE, NU, DIR> {
-    using A = WaveInterp<T, NINE, NU, DIR>;
+template <typename T, int KIND, int NU, int DIR, bool NORM>
+struct WavePost : WaveInterp<T, KIND, NU, DIR> {
+    using A = WaveInterp<T, KIND, NU, DIR>;
     using B = typename A::B;
     static constexpr int RX = B::RX;
     double acc;
 
     __device__ __forceinline__ void run(const Lev<T> &L, T *__restrict__ uout, const Wts<T> &Cw,
                                         const T *__restrict__ ec, const TileGeo &G, int tid,
-                                        double *__restrict__ part, WaveLds<T, NINE, NU> &lds)
+                                        double *__restrict__ part, WaveLds<T, KIND, NU> &lds)
     {
         B::place(L, G, tid, lds);
         A::coarse(Cw);
@@ -675,7 +710,7 @@ private:
     }
 };
 
-template <typename T, bool NINE, int NU, bool NORM>
+template <typename T, int KIND, int NU, bool NORM>
 __global__ __launch_bounds__(64, 1) void k_post_wave(Lev<T> L, T *__restrict__ uout, Wts<T> C,
                                                      const T *__restrict__ ec, TileGeo G, double *__restrict__ part,
                                                      const int *stop)
@@ -686,12 +721,12 @@ __global__ __launch_bounds__(64, 1) void k_post_wave(Lev<T> L, T *__restrict__ u
     L.u += k * G.ksf; L.b += k * G.ksf; uout += k * G.ksf;
     ec += k * G.ksc;
     if (NORM) part += k * G.kpart;
-    __shared__ WaveLds<T, NINE, NU> S;
+    __shared__ WaveLds<T, KIND, NU> S;
     if (wave_up(G, tid)) {
-        WavePost<T, NINE, NU, 1, NORM> P;
+        WavePost<T, KIND, NU, 1, NORM> P;
         P.run(L, uout, C, ec, G, tid, part, S);
     } else {
-        WavePost<T, NINE, NU, -1, NORM> P;
+        WavePost<T, KIND, NU, -1, NORM> P;
         P.run(L, uout, C, ec, G, tid, part, S);
     }
 }
