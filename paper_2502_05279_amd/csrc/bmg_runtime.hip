@@ -107,7 +107,22 @@ double ms_since(std::chrono::steady_clock::time_point t0)
 {
     return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
 }
-int persistent_of(const bmg_options &o) { return o.persistent_below_n > 0 ? o.persistent_below_n : SMALL_MAX_N; }
+// Levels whose whole sub-cycle runs in one workgroup: by default from 31 points
+// down, and none where the coarsest level has 15 or more.  One workgroup saves
+// the launches of the smallest levels but runs a 63^2 level on one CU and the
+// coarsest solve without the loader waves that a larger factor needs.  A cycle
+// of 127^2, FP64, from 63 down / from 31 down / apart: coarsest 3 134 / 124 /
+// 146 us, 7 129 / 122 / 134, 15 138 / 131 / 125, 31 207 / - / 141; 1023^2 with
+// coarsest 31: 364 / - / 266.  Solves to 1e-8: 127^2, 7 1.93 / 1.88 / 2.24 ms,
+// 15 1.98 / 1.87 / 1.79; 1023^2, 7 6.9 / 6.6 / 7.1, 15 7.3 / 7.0 / 6.6, 31 7.9 /
+// - / 5.3.  (The other way round, by 3%, only where a 127^2 solve takes a few
+// cycles and the launches of a batch that the stop leaves empty count.)
+constexpr int SMALL_FROM_N = 31, SMALL_COARSEST = 7;
+int persistent_of(const bmg_options &o)
+{
+    if (o.persistent_below_n > 0) return o.persistent_below_n;
+    return coarsest_of(o) <= SMALL_COARSEST ? SMALL_FROM_N : 1;
+}
 // Fused pre pass of level l in square tiles (k_pre2d)?
 static bool square_tiles(const bmg_solver *h, int l)
 {
@@ -263,8 +278,8 @@ bmg_status check_options(const bmg_options &o)
         return fail(BMG_EINVAL, "coarsest_n=%d must be 2^k-1 in [3, %d] (0 = 3)", o.coarsest_n, BAND_MAX_NC);
     if (o.persistent_below_n != 0 && o.persistent_below_n != 1 &&
         (!valid_n(o.persistent_below_n) || o.persistent_below_n > SMALL_MAX_N))
-        return fail(BMG_EINVAL, "persistent_below_n=%d must be 2^k-1 <= %d, 1 (none) or 0 (= %d)",
-                    o.persistent_below_n, SMALL_MAX_N, SMALL_MAX_N);
+        return fail(BMG_EINVAL, "persistent_below_n=%d must be 2^k-1 <= %d, 1 (none) or 0 (default)",
+                    o.persistent_below_n, SMALL_MAX_N);
     if (o.graph_mode != 0 && o.graph_mode != 1) return fail(BMG_EINVAL, "graph_mode=%d must be 0 or 1", o.graph_mode);
     if (o.square_tiles_below_n != 0 && o.square_tiles_below_n != 1 && !valid_n(o.square_tiles_below_n))
         return fail(BMG_EINVAL, "square_tiles_below_n=%d must be 2^k-1, 1 (none) or 0 (= %d)",
