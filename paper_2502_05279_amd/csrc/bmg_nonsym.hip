@@ -120,39 +120,48 @@ __global__ void k_ns_weights_corners(LevN F, Wts<double> C, int nc, bool transpo
 // support of basis IJ + d; couplings to ring coarse points are zero: their
 // sums are formed with the weights of the nearest interior point (so every
 // load is in range and none waits behind a branch) and then replaced by zero.
-__global__ __launch_bounds__(256) void k_ns_rap(LevN F, Wts<double> P, Wts<double> R, LevN Cl)
+// The nine sums run together, p outermost, so a row of A is loaded once and not
+// once per d (coarse 2047^2 from a five-point level, whose zero corners are
+// left out: 377 us, with one d after the other 1588).
+template <bool FIVE_POINT>
+__global__ __launch_bounds__(128) void k_ns_rap(LevN F, Wts<double> P, Wts<double> R, LevN Cl)
 {
     const int I = 1 + blockIdx.x * blockDim.x + threadIdx.x;
     const int J = 1 + blockIdx.y * blockDim.y + threadIdx.y;
     const int nc = Cl.n;
     if (I > nc || J > nc) return;
     const size_t c = (size_t)J * Cl.ld + I;
+    auto inside = [&](int k) { return k < 1 ? 1 : k > nc ? nc : k; };
+    double acc[NSD] = {};
 #pragma unroll
-    for (int d = 0; d < NSD; ++d) {
-        const int ki = I + d % 3 - 1, kj = J + d / 3 - 1;
-        const bool live = ki >= 1 && ki <= nc && kj >= 1 && kj <= nc;
-        const int KI = ki < 1 ? 1 : ki > nc ? nc : ki, KJ = kj < 1 ? 1 : kj > nc ? nc : kj;
-        double acc = 0.0;
+    for (int jj = -1; jj <= 1; ++jj) {
 #pragma unroll
-        for (int jj = -1; jj <= 1; ++jj) {
+        for (int ii = -1; ii <= 1; ++ii) {
+            const size_t p = (size_t)(2 * J + jj) * F.ld + (2 * I + ii);
+            double a[NSD];
 #pragma unroll
-            for (int ii = -1; ii <= 1; ++ii) {
-                const int pi = 2 * I + ii, pj = 2 * J + jj;
-                const double wp = basis_weight(R, I, J, ii, jj);
-                double a[NSD];
-                ns_row(F, (size_t)pj * F.ld + pi, false, a);
+            for (int e = 0; e < NSD; ++e)
+                if (!FIVE_POINT || e == E_S || e == E_W || e == E_O || e == E_E || e == E_N) a[e] = F.A[e][p];
+            const double wp = basis_weight(R, I, J, ii, jj);
+#pragma unroll
+            for (int d = 0; d < NSD; ++d) {
                 double t = 0.0;
 #pragma unroll
                 for (int e = 0; e < NSD; ++e) {
+                    if (FIVE_POINT && e % 2 == 0 && e != E_O) continue;
                     // q - 2(IJ + d), the same for the clamped point's support
                     const int dx = ii + e % 3 - 1 - 2 * (d % 3 - 1), dy = jj + e / 3 - 1 - 2 * (d / 3 - 1);
                     if (dx < -1 || dx > 1 || dy < -1 || dy > 1) continue;
-                    t = t + a[e] * basis_weight(P, KI, KJ, dx, dy);
+                    t = t + a[e] * basis_weight(P, inside(I + d % 3 - 1), inside(J + d / 3 - 1), dx, dy);
                 }
-                acc = acc + wp * t;
+                acc[d] = acc[d] + wp * t;
             }
         }
-        Cl.A[d][c] = live ? acc : 0.0;
+    }
+#pragma unroll
+    for (int d = 0; d < NSD; ++d) {
+        const int ki = I + d % 3 - 1, kj = J + d / 3 - 1;
+        Cl.A[d][c] = ki >= 1 && ki <= nc && kj >= 1 && kj <= nc ? acc[d] : 0.0;
     }
 }
 
@@ -853,7 +862,11 @@ bmg_status bmg_ns_setup(bmg_ns **out, const double *stencil, int n, int kind, co
             hipLaunchKernelGGL(k_ns_weights_corners, grid2(nc + 1, nc + 1, NB), NB, 0, h->st, h->L[l], C, nc,
                                tr != 0, h->flags);
         }
-        hipLaunchKernelGGL(k_ns_rap, grid2(nc, nc, NB), NB, 0, h->st, h->L[l], h->P[l], h->R[l], h->L[l + 1]);
+        const dim3 rb(64, 2);
+        if (l == 0 && kind == 5)
+            hipLaunchKernelGGL((k_ns_rap<true>), grid2(nc, nc, rb), rb, 0, h->st, h->L[l], h->P[l], h->R[l], h->L[l + 1]);
+        else
+            hipLaunchKernelGGL((k_ns_rap<false>), grid2(nc, nc, rb), rb, 0, h->st, h->L[l], h->P[l], h->R[l], h->L[l + 1]);
     }
     hipLaunchKernelGGL(k_band_ldu_factor, dim3(1), dim3(NSB_THREADS), ns_band_lds(), h->st, h->L[h->nlev - 1], h->Lb,
                        h->Ub, h->Dd, h->flags);
