@@ -34,12 +34,15 @@ struct LevN {
 
 __device__ __forceinline__ ptrdiff_t ns_off(int e, int ld) { return (e % 3 - 1) + (ptrdiff_t)(e / 3 - 1) * ld; }
 
-// Row p of A, or of A^T (A^T(p, p + d) = A(p + d, p), entry 8 - e of row p + d).
-__device__ __forceinline__ void ns_row(const LevN &L, size_t p, bool transpose, double a[NSD])
+// Row p of A, or of A^T (A^T(p, p + d) = A(p + d, p), entry 8 - e of row p + d);
+// the corners of a five-point level are not read.
+template <bool FIVE_POINT, bool TRANSPOSE>
+__device__ __forceinline__ void ns_row(const LevN &L, size_t p, double a[NSD])
 {
 #pragma unroll
     for (int e = 0; e < NSD; ++e)
-        a[e] = (!transpose || e == E_O) ? L.A[e][p] : L.A[NSD - 1 - e][(size_t)((ptrdiff_t)p + ns_off(e, L.ld))];
+        a[e] = FIVE_POINT && e % 2 == 0 && e != E_O ? 0.0
+               : (!TRANSPOSE || e == E_O)           ? L.A[e][p] : L.A[NSD - 1 - e][(size_t)((ptrdiff_t)p + ns_off(e, L.ld))];
 }
 
 // [n][n][K] stencil (K = 5: S, W, O, E, N; K = 9: SW..NE) into level 0, with
@@ -65,9 +68,12 @@ __global__ void k_ns_import(const double *__restrict__ st, int K, LevN L, int *_
     if (bad) atomicOr(flags, bad);
 }
 
-// Operator-induced edge weights of A (transpose = false: P) or of A^T (R's
-// weights), the formulas of the symmetric solver on the lumped rows.
-__global__ void k_ns_weights_edges(LevN F, Wts<double> C, int nc, bool transpose, int *__restrict__ flags)
+// Operator-induced edge weights of A (P's) or of A^T (R's), the formulas of the
+// symmetric solver on the lumped rows.  Bound by memory; a 4095^2 five-point
+// level without its corner planes: 203 and 179 us (with them 300), the corner
+// weights 135 (187).
+template <bool FIVE_POINT, bool TRANSPOSE>
+__global__ void k_ns_weights_edges(LevN F, Wts<double> C, int nc, int *__restrict__ flags)
 {
     const int I = blockIdx.x * blockDim.x + threadIdx.x + 1;
     const int J = blockIdx.y * blockDim.y + threadIdx.y + 1;
@@ -77,7 +83,7 @@ __global__ void k_ns_weights_edges(LevN F, Wts<double> C, int nc, bool transpose
     int bad = 0;
     double a[NSD];
     if (J <= nc) {
-        ns_row(F, (size_t)(2 * J) * ld + (2 * I - 1), transpose, a);
+        ns_row<FIVE_POINT, TRANSPOSE>(F, (size_t)(2 * J) * ld + (2 * I - 1), a);
         lump_row(a);
         const double D = (a[E_O] + a[E_N]) + a[E_S];
         if (!(D > 0.0)) bad = F_BREAK_INTERP;
@@ -85,7 +91,7 @@ __global__ void k_ns_weights_edges(LevN F, Wts<double> C, int nc, bool transpose
         C.p[LR * C.ps + c] = -((a[E_E] + a[E_NE]) + a[E_SE]) / D;
     }
     if (I <= nc) {
-        ns_row(F, (size_t)(2 * J - 1) * ld + (2 * I), transpose, a);
+        ns_row<FIVE_POINT, TRANSPOSE>(F, (size_t)(2 * J - 1) * ld + (2 * I), a);
         lump_row(a);
         const double D = (a[E_O] + a[E_W]) + a[E_E];
         if (!(D > 0.0)) bad = F_BREAK_INTERP;
@@ -95,7 +101,8 @@ __global__ void k_ns_weights_edges(LevN F, Wts<double> C, int nc, bool transpose
     if (bad) atomicOr(flags, bad);
 }
 
-__global__ void k_ns_weights_corners(LevN F, Wts<double> C, int nc, bool transpose, int *__restrict__ flags)
+template <bool FIVE_POINT, bool TRANSPOSE>
+__global__ void k_ns_weights_corners(LevN F, Wts<double> C, int nc, int *__restrict__ flags)
 {
     const int I = blockIdx.x * blockDim.x + threadIdx.x + 1;
     const int J = blockIdx.y * blockDim.y + threadIdx.y + 1;
@@ -103,7 +110,7 @@ __global__ void k_ns_weights_corners(LevN F, Wts<double> C, int nc, bool transpo
     const size_t c = (size_t)J * C.ld + I;
     const size_t cs = c - C.ld, cw = c - 1;
     double a[NSD];
-    ns_row(F, (size_t)(2 * J - 1) * F.ld + (2 * I - 1), transpose, a);
+    ns_row<FIVE_POINT, TRANSPOSE>(F, (size_t)(2 * J - 1) * F.ld + (2 * I - 1), a);
     lump_row(a);
     if (!(a[E_O] > 0.0)) atomicOr(flags, F_BREAK_INTERP);
     const double lr = C.at(LR, c), ll = C.at(LL, c), la = C.at(LA, c), lb = C.at(LB, c);
@@ -855,15 +862,18 @@ bmg_status bmg_ns_setup(bmg_ns **out, const double *stencil, int n, int kind, co
     hipLaunchKernelGGL(k_ns_import, grid2(n, n, NB), NB, 0, h->st, stencil, kind, h->L[0], h->flags);
     for (int l = 0; l + 1 < h->nlev; ++l) {
         const int nc = h->L[l + 1].n;
-        for (int tr = 0; tr < 2; ++tr) {
-            const Wts<double> &C = tr ? h->R[l] : h->P[l];
-            hipLaunchKernelGGL(k_ns_weights_edges, grid2(nc + 1, nc + 1, NB), NB, 0, h->st, h->L[l], C, nc, tr != 0,
-                               h->flags);
-            hipLaunchKernelGGL(k_ns_weights_corners, grid2(nc + 1, nc + 1, NB), NB, 0, h->st, h->L[l], C, nc,
-                               tr != 0, h->flags);
-        }
+        const bool five = l == 0 && kind == 5;
+        const dim3 wb(64, 4), wg = grid2(nc + 1, nc + 1, wb);
+#define NS_WEIGHTS(FIVE_POINT, TRANSPOSE, C)                                                                        \
+    do {                                                                                                            \
+        hipLaunchKernelGGL((k_ns_weights_edges<FIVE_POINT, TRANSPOSE>), wg, wb, 0, h->st, h->L[l], C, nc, h->flags);   \
+        hipLaunchKernelGGL((k_ns_weights_corners<FIVE_POINT, TRANSPOSE>), wg, wb, 0, h->st, h->L[l], C, nc, h->flags); \
+    } while (0)
+        if (five) { NS_WEIGHTS(true, false, h->P[l]); NS_WEIGHTS(true, true, h->R[l]); }
+        else { NS_WEIGHTS(false, false, h->P[l]); NS_WEIGHTS(false, true, h->R[l]); }
+#undef NS_WEIGHTS
         const dim3 rb(64, 2);
-        if (l == 0 && kind == 5)
+        if (five)
             hipLaunchKernelGGL((k_ns_rap<true>), grid2(nc, nc, rb), rb, 0, h->st, h->L[l], h->P[l], h->R[l], h->L[l + 1]);
         else
             hipLaunchKernelGGL((k_ns_rap<false>), grid2(nc, nc, rb), rb, 0, h->st, h->L[l], h->P[l], h->R[l], h->L[l + 1]);
