@@ -209,9 +209,8 @@ __device__ __forceinline__ void five_point_sweeps(T *su, const T *sW, int lane, 
 
 // With WREC the restriction weights are not read: each column computes the
 // operator-induced weights of its own F-points from the stencil rows in the
-// window (the expressions of k_weights_edges / k_weights_corners in their
-// order, so the same bits), and the restricting columns collect their
-// neighbours' through LDS.  Step e computes the y-edges and cell centres of
+// window (the expressions of k_weights in their order, so the same bits), and
+// the restricting columns collect their neighbours' through LDS.  Step e computes the y-edges and cell centres of
 // row e-2NU-1 and the x-edges of row e-2NU; the weights of the rows below come
 // from the previous step.
 template <typename T, bool NINE, int NU, bool WREC = false, bool IRIN = false>

@@ -173,58 +173,71 @@ __device__ __forceinline__ void lump_row(double a[9])
 }
 
 // Edge weights: x-edge X(I,J) = (2I-1, 2J) for I <= nc+1, J <= nc collapses the
-// lumped stencil along y; y-edge Y(I,J) = (2I, 2J-1) for I <= nc, J <= nc+1
-// collapses along x.
+// lumped stencil along y (west, east); y-edge Y(I,J) = (2I, 2J-1) for I <= nc,
+// J <= nc+1 collapses along x (south, north).  An edge that does not exist has
+// the weights zero.
+struct EdgeWeights {
+    double lo, hi;   // LL, LR or LB, LA
+    bool there;
+};
 template <bool NINE>
-static __global__ void k_weights_edges(Lev<double> F, Wts<double> C, int nc, int *__restrict__ flags)
+__device__ __forceinline__ EdgeWeights x_edge(const Lev<double> &F, int nc, int I, int J, int &bad)
 {
-    const int I = blockIdx.x * blockDim.x + threadIdx.x + 1;
-    const int J = blockIdx.y * blockDim.y + threadIdx.y + 1;
-    if (I > nc + 1 || J > nc + 1) return;
-    const size_t c = (size_t)J * C.ld + I;
-    const size_t ld = F.ld;
-    int bad = 0;
+    const bool there = J >= 1 && J <= nc;
     double a[9];
-    if (J <= nc) {
-        row_of<NINE>(F, (size_t)(2 * J) * ld + (2 * I - 1), a);
-        lump_row(a);
-        const double D = (a[4] + a[7]) + a[1];
-        if (!(D > 0.0)) bad = F_BREAK_INTERP;
-        C.p[LL * C.ps + c] = -((a[3] + a[6]) + a[0]) / D;
-        C.p[LR * C.ps + c] = -((a[5] + a[8]) + a[2]) / D;
-    }
-    if (I <= nc) {
-        row_of<NINE>(F, (size_t)(2 * J - 1) * ld + (2 * I), a);
-        lump_row(a);
-        const double D = (a[4] + a[3]) + a[5];
-        if (!(D > 0.0)) bad = F_BREAK_INTERP;
-        C.p[LB * C.ps + c] = -((a[1] + a[0]) + a[2]) / D;
-        C.p[LA * C.ps + c] = -((a[7] + a[6]) + a[8]) / D;
-    }
-    if (bad) atomicOr(flags, bad);
+    row_of<NINE>(F, (size_t)(2 * min(max(J, 1), nc)) * F.ld + (2 * I - 1), a);
+    lump_row(a);
+    const double D = (a[4] + a[7]) + a[1];
+    if (there && !(D > 0.0)) bad = F_BREAK_INTERP;
+    const double lo = -((a[3] + a[6]) + a[0]) / D, hi = -((a[5] + a[8]) + a[2]) / D;
+    return {there ? lo : 0.0, there ? hi : 0.0, there};
+}
+template <bool NINE>
+__device__ __forceinline__ EdgeWeights y_edge(const Lev<double> &F, int nc, int I, int J, int &bad)
+{
+    const bool there = I >= 1 && I <= nc;
+    double a[9];
+    row_of<NINE>(F, (size_t)(2 * J - 1) * F.ld + 2 * min(max(I, 1), nc), a);
+    lump_row(a);
+    const double D = (a[4] + a[3]) + a[5];
+    if (there && !(D > 0.0)) bad = F_BREAK_INTERP;
+    const double lo = -((a[1] + a[0]) + a[2]) / D, hi = -((a[7] + a[6]) + a[8]) / D;
+    return {there ? lo : 0.0, there ? hi : 0.0, there};
 }
 
-// Cell-centre weights at Z(I,J) = (2I-1, 2J-1), I, J <= nc+1, from the lumped
-// stencil and the neighbouring edge weights.
+// All weights of coarse point (I, J), I, J <= nc+1: its two edges and its
+// cell centre Z(I,J) = (2I-1, 2J-1), which takes the weights of the edges
+// around it, the lumped stencil's couplings to them and to the four corners.
+// The two edges of the south and west neighbours are formed again here: their
+// rows are in the cache, and one pass over the level takes 188 us (4095^2,
+// five-point) where edges and then centres took 137 + 126.
 template <bool NINE>
-static __global__ void k_weights_corners(Lev<double> F, Wts<double> C, int nc, int *__restrict__ flags)
+static __global__ void k_weights(Lev<double> F, Wts<double> C, int nc, int *__restrict__ flags)
 {
     const int I = blockIdx.x * blockDim.x + threadIdx.x + 1;
     const int J = blockIdx.y * blockDim.y + threadIdx.y + 1;
     if (I > nc + 1 || J > nc + 1) return;
     const size_t c = (size_t)J * C.ld + I;
-    const size_t cs = c - C.ld, cw = c - 1;
+    int bad = 0;
+    const EdgeWeights n = x_edge<NINE>(F, nc, I, J, bad), s = x_edge<NINE>(F, nc, I, J - 1, bad);
+    const EdgeWeights e = y_edge<NINE>(F, nc, I, J, bad), w = y_edge<NINE>(F, nc, I - 1, J, bad);
     double a[9];
     row_of<NINE>(F, (size_t)(2 * J - 1) * F.ld + (2 * I - 1), a);
     lump_row(a);
-    if (!(a[4] > 0.0)) atomicOr(flags, F_BREAK_INTERP);
-    const double lr = C.at(LR, c), ll = C.at(LL, c), la = C.at(LA, c), lb = C.at(LB, c);
-    const double lr_s = C.at(LR, cs), ll_s = C.at(LL, cs);
-    const double la_w = C.at(LA, cw), lb_w = C.at(LB, cw);
-    C.p[LNE * C.ps + c] = -((a[8] + a[7] * lr) + a[5] * la) / a[4];
-    C.p[LNW * C.ps + c] = -((a[6] + a[7] * ll) + a[3] * la_w) / a[4];
-    C.p[LSE * C.ps + c] = -((a[2] + a[1] * lr_s) + a[5] * lb) / a[4];
-    C.p[LSW * C.ps + c] = -((a[0] + a[1] * ll_s) + a[3] * lb_w) / a[4];
+    if (!(a[4] > 0.0)) bad = F_BREAK_INTERP;
+    if (n.there) {
+        C.p[LL * C.ps + c] = n.lo;
+        C.p[LR * C.ps + c] = n.hi;
+    }
+    if (e.there) {
+        C.p[LB * C.ps + c] = e.lo;
+        C.p[LA * C.ps + c] = e.hi;
+    }
+    C.p[LNE * C.ps + c] = -((a[8] + a[7] * n.hi) + a[5] * e.hi) / a[4];
+    C.p[LNW * C.ps + c] = -((a[6] + a[7] * n.lo) + a[3] * w.hi) / a[4];
+    C.p[LSE * C.ps + c] = -((a[2] + a[1] * s.hi) + a[5] * e.lo) / a[4];
+    C.p[LSW * C.ps + c] = -((a[0] + a[1] * s.lo) + a[3] * w.lo) / a[4];
+    if (bad) atomicOr(flags, bad);
 }
 
 // --------------------------------------------------------- Galerkin RAP
@@ -303,13 +316,8 @@ static __global__ __launch_bounds__(128) void k_rap(Lev<double> F, Wts<double> C
 static inline void launch_weights(const Lev<double> &F, const Wts<double> &C, int nc, int *flags, dim3 grid,
                                   dim3 blk, hipStream_t st)
 {
-    if (F.SW) {
-        hipLaunchKernelGGL(k_weights_edges<true>, grid, blk, 0, st, F, C, nc, flags);
-        hipLaunchKernelGGL(k_weights_corners<true>, grid, blk, 0, st, F, C, nc, flags);
-    } else {
-        hipLaunchKernelGGL(k_weights_edges<false>, grid, blk, 0, st, F, C, nc, flags);
-        hipLaunchKernelGGL(k_weights_corners<false>, grid, blk, 0, st, F, C, nc, flags);
-    }
+    if (F.SW) hipLaunchKernelGGL(k_weights<true>, grid, blk, 0, st, F, C, nc, flags);
+    else hipLaunchKernelGGL(k_weights<false>, grid, blk, 0, st, F, C, nc, flags);
 }
 
 static inline void launch_rap(const Lev<double> &F, const Wts<double> &C, const Lev<double> &Cl, hipStream_t st)
