@@ -504,19 +504,19 @@ TileGeo level_tiles(const bmg_solver *h, int l, int hx)
     return g;
 }
 
-// FP64 pre passes compute the restriction weights (1) or read them (0).
-#ifndef BMG_PRE_WEIGHTS_IN_PASS
-#define BMG_PRE_WEIGHTS_IN_PASS 1
-#endif
-
+// Does the pre pass of level l not need the stored restriction weights?  Those
+// of an FP64 five-point level with operator-induced weights follow from the
+// stencil that the pass reads.  Not FP32 levels (their weights are the rounded
+// FP64 ones), not learned weights (no formula), not nine-point levels (the
+// divisions cost more than the loads); with several right-hand sides the weight
+// rows are shared through L2, while computing them would repeat the divisions
+// for each.
 template <typename T>
 static bool pre_weights_in_pass(const bmg_solver *h, int l, bool nine)
 {
     const bool learned = h->opt.interp == BMG_INTERP_LEARNED &&
                          (h->opt.learned_levels == 0 || l < h->opt.learned_levels);
-    // with several right-hand sides the weight rows are shared through L2,
-    // while computing them would repeat the divisions for each
-    return BMG_PRE_WEIGHTS_IN_PASS && std::is_same<T, double>::value && !nine && !learned && h->nrhs == 1;
+    return std::is_same<T, double>::value && !nine && !learned && h->nrhs == 1;
 }
 
 // Tiles of a wave-stream pass on level l of every right-hand side.
@@ -553,11 +553,6 @@ bmg_status fused_pre(bmg_solver *h, int l, int nu, const int *stop, bool zero_u 
     const dim3 grid = tile_grid(g), blk(FW);
 #define PRE(NINE, NU) hipLaunchKernelGGL((k_pre<T, NINE, NU>), grid, blk, 0, h->st, F, out, C, Cl, g, stop)
 #define PREW(NINE, NU) hipLaunchKernelGGL((k_pre<T, NINE, NU, true>), grid, blk, 0, h->st, F, out, C, Cl, g, stop)
-    // Five-point FP64 levels with operator-induced weights compute them in the
-    // pass instead of reading the 8 planes (16 of 68 bytes per fine point).
-    // Not FP32 levels (their weights are the rounded FP64 ones), not learned
-    // weights (no formula), and not nine-point levels, whose divisions cost
-    // more time than the loads they replace.
     const bool wrec = pre_weights_in_pass<T>(h, l, nine);
     // small nine-point levels: every sweep inside one square tile's LDS copy
     // (511^2: 23 us against 26 as waves, whose few rows per tile start with a
@@ -566,12 +561,17 @@ bmg_status fused_pre(bmg_solver *h, int l, int nu, const int *stop, bool zero_u 
     const bool sq = square_tiles(h, l) && nu <= 2;
     // stencil once and b, u read, u written for each right-hand side on the
     // fine level; b and u (zero) written for each on the coarse level, and the
-    // 8 weight planes read once unless computed
+    // 8 weight planes read once unless they follow from the stencil (the bytes
+    // that the step needs: the waves read them all the same)
     const double K = h->nrhs;
     trace_begin(h, BMG_TRACE_PRE, l,
                 sizeof(T) * ((stencil_planes(nine) + 3.0 * K) * (double)F.n * F.n +
                              (2.0 * K + (wrec ? 0.0 : 8.0)) * (double)Cl.n * Cl.n));
-    if (nu <= 2 && !sq && !wrec) {
+    // Up to two sweeps run as waves, also where the workgroup pass would compute
+    // the weights it does not need to read: an FP64 five-point level, two
+    // sweeps, 127^2 12 us against 26, 1023^2 25 / 61, 2047^2 62 / 126, 4095^2
+    // 274 / 296.
+    if (nu <= 2 && !sq) {
         const TileGeo gw = wave_tiles(h, l, nine ? 4 * nu + 2 : 2 * nu + 2);
         const dim3 wg = tile_grid(gw), wb(64);
 #define PREWAVE(NINE, NU)                                                                                      \
@@ -589,11 +589,9 @@ bmg_status fused_pre(bmg_solver *h, int l, int nu, const int *stop, bool zero_u 
         else
             hipLaunchKernelGGL((k_pre2d<T, 2>), g2, dim3(T2D_THREADS), 0, h->st, F, out, C, Cl, stop);
     } else if (wrec) {
-        if constexpr (std::is_same<T, double>::value) {
-            if (nu == 1) PREW(false, 1); else if (nu == 2) PREW(false, 2); else PREW(false, 3);
-        }
+        if constexpr (std::is_same<T, double>::value) PREW(false, 3);
     } else if (nine) {
-        PRE(true, 3);   // (one and two sweeps run as waves, above)
+        PRE(true, 3);
     } else {
         PRE(false, 3);
     }
@@ -1443,13 +1441,22 @@ static bmg_status cycle_pair_graph(bmg_solver *h, double tol, int maxc, double r
     return BMG_OK;
 }
 
-// One FP64 refinement step: L0.b holds r, L0.u = 0; V-cycle, (XH, XL) += u
-// (inside the fine post pass where the cycle allows).
+// r = B0 - A (XH + XL) -> L0.b for an FP64 refinement step (mode 2 of
+// resnorm_dd, which also clears L0.u; without that store, a mode 1 into L0.b,
+// where the step's pre pass takes u = 0 as known).
+static bmg_status refine_residual64(bmg_solver *h, int slot, bool record, double tol, int maxc)
+{
+    const bool known = post_update_fusable(h) && h->opt.nu1 >= 1 && h->opt.nu1 <= 2;
+    return resnorm_dd(h, h->B0, h->XH, h->XL, known ? 1 : 2, h->L[0].b, slot, record, tol, maxc, 0.0);
+}
+
+// One FP64 refinement step: L0.b holds r, the iterate is zero; V-cycle,
+// (XH, XL) += u (inside the fine post pass where the cycle allows).
 static bmg_status refine_step64(bmg_solver *h, const int *stop)
 {
     const Lev<double> &L = h->L[0];
     if (post_update_fusable(h)) {
-        TRY(fused_pre<double>(h, 0, h->opt.nu1, stop));
+        TRY(fused_pre<double>(h, 0, h->opt.nu1, stop, true));
         TRY(fused_cycle_from<double>(h, 1, stop, false));
         const IrArgs ir{nullptr, nullptr, nullptr, h->XH, h->XL};
         return post_update<double>(h, stop, ir);
@@ -1557,7 +1564,7 @@ bmg_status bmg_solve(bmg_solver *h, const double *rhs, double *x, double tol, bm
                     }
                 } else {
                     TRY(refine_step64(h, h->stop));
-                    TRY(resnorm_dd(h, h->B0, h->XH, h->XL, 2, nullptr, S_SUMSQ, true, tol, maxc, 0.0));
+                    TRY(refine_residual64(h, S_SUMSQ, true, tol, maxc));
                 }
             }
             TRY(poll(h, cs));
@@ -1568,7 +1575,7 @@ bmg_status bmg_solve(bmg_solver *h, const double *rhs, double *x, double tol, bm
                 refining = true;
                 HIPCHK(hipMemcpyAsync(h->XH, L.u, pl0, hipMemcpyDeviceToDevice, h->st));
                 HIPCHK(hipMemsetAsync(h->XL, 0, pl0, h->st));
-                TRY(resnorm_dd(h, h->B0, h->XH, h->XL, 2, nullptr, S_TMP, false, 0.0, 0, 0.0));
+                TRY(refine_residual64(h, S_TMP, false, 0.0, 0));
                 HIPCHK(hipMemsetAsync(h->stop, 0, sizeof(int), h->st));
                 continue;
             }

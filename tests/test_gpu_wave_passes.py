@@ -1,7 +1,5 @@
 """The fused passes as streams of single waves (the fine five-point level and the
-nine-point level below it; FP64 fine pre passes form their weights and stay in
-workgroups), against the
-oracle's separate steps: one and two sweeps, tiles of two rows, ragged last
+nine-point level below it), against the oracle's separate steps: one and two sweeps, tiles of two rows, ragged last
 tiles and strips (levels of 7 to 255 points: less than a strip, a strip and a
 few columns more, several), tiles streamed upward and downward, FP64 and FP32."""
 import numpy as np
