@@ -95,7 +95,8 @@ typedef struct {
     int persistent_below_n; /* coarse levels of at most this many points per
                         side (below the fine level) run as one persistent
                         one-workgroup launch per cycle: 2^k - 1 <= 63, or 1 for
-                        none; 0: 31 where coarsest_n <= 7, else none */
+                        none; 0: chosen by the coarsest size, the sweep
+                        counts and the call */
     int square_tiles_below_n; /* nine-point levels of at most this many points
                         per side run their fused pre pass with one workgroup
                         per 32 x 32 square tile, every sweep of the pass inside

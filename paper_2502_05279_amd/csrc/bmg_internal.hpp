@@ -75,6 +75,7 @@ struct bmg_solver {
     double *ualt[MAXL];         // second iterate buffer of each level (fused passes)
     float *ualt32[MAXL];
     int norm_parts = 0;         // partial sums left by the last fused norm
+    int small_n = 1;            // levels up to here run in one workgroup (small_from), set by each entry point
     // several right-hand sides on this hierarchy (a block solve's view; 1
     // otherwise): right-hand side k's level-l arrays start k*ks[l] elements
     // after the first's, its stop flag k*kstop ints and its norm partials

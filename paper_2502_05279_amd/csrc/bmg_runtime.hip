@@ -107,21 +107,29 @@ double ms_since(std::chrono::steady_clock::time_point t0)
 {
     return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
 }
-// Levels whose whole sub-cycle runs in one workgroup: by default from 31 points
-// down, and none where the coarsest level has 15 or more.  One workgroup saves
-// the launches of the smallest levels but runs a 63^2 level on one CU and the
-// coarsest solve without the loader waves that a larger factor needs.  A cycle
-// of 127^2, FP64, from 63 down / from 31 down / apart: coarsest 3 134 / 124 /
-// 146 us, 7 129 / 122 / 134, 15 138 / 131 / 125, 31 207 / - / 141; 1023^2 with
-// coarsest 31: 364 / - / 266.  Solves to 1e-8: 127^2, 7 1.93 / 1.88 / 2.24 ms,
-// 15 1.98 / 1.87 / 1.79; 1023^2, 7 6.9 / 6.6 / 7.1, 15 7.3 / 7.0 / 6.6, 31 7.9 /
-// - / 5.3.  (The other way round, by 3%, only where a 127^2 solve takes a few
-// cycles and the launches of a batch that the stop leaves empty count.)
-constexpr int SMALL_FROM_N = 31, SMALL_COARSEST = 7;
-int persistent_of(const bmg_options &o)
+// Levels of at most this many points per side run their whole sub-cycle in one
+// workgroup (1: none).  It saves launches, but runs a 63^2 level on one CU and the
+// coarsest solve without the loader waves that a larger factor needs.
+// - Coarsest levels of 31 points or more: none.  A cycle of 127^2, FP64, from 63
+//   down / apart 151 / 90 us; 1023^2 364 / 266.
+// - A solve enqueues cycles past its stop, and every launch of those counts: from
+//   63 down.  127^2 Poisson to 1e-6, coarsest 3, from 63 / from 31 / apart 647 /
+//   702 / 1027 us, coarsest 15 685 / 744 / 790 (a jumping field with its three
+//   times as many cycles, 3: 1653 / 1568 / 2031, 15: 1528 / 1474 / 1448).
+// - A cycle alone and the inner solves of the two-grid objective (some 25 cycles):
+//   from 31 down, apart above a coarsest level of 15 (127^2, 3: 85 / 82 / 104 us,
+//   7: 83 / 82 / 94, 15: 92 / 88 / 85; 255^2, 15: 121 / 113 / 108).
+// - Sweep counts beyond those of the streaming waves and square tiles, whose
+//   passes are slower apart: from 63 down (three sweeps before, 127^2, 3: 114 /
+//   146 / 248 us).
+int small_from(const bmg_solver *h, bool solve)
 {
+    const bmg_options &o = h->opt;
+    const int nc = coarsest_of(o);
     if (o.persistent_below_n > 0) return o.persistent_below_n;
-    return coarsest_of(o) <= SMALL_COARSEST ? SMALL_FROM_N : 1;
+    if (nc >= 31) return 1;
+    if (solve || o.nu1 < 1 || o.nu1 > 2 || o.nu2 < 1 || o.nu2 > 2) return SMALL_MAX_N;
+    return nc >= 15 && h->n > 63 ? 1 : 31;
 }
 // Fused pre pass of level l in square tiles (k_pre2d)?
 static bool square_tiles(const bmg_solver *h, int l)
@@ -693,7 +701,7 @@ template <typename T>
 bmg_status fused_cycle_from(bmg_solver *h, int l, const int *stop, bool norm)
 {
     if (l == h->nlev - 1) return coarse<T>(h, lev<T>(h, l), stop);
-    if (l >= 1 && lev<T>(h, l).n <= persistent_of(h->opt)) return small_cycle<T>(h, l, stop);
+    if (l >= 1 && lev<T>(h, l).n <= h->small_n) return small_cycle<T>(h, l, stop);
     TRY(fused_pre<T>(h, l, h->opt.nu1, stop, l >= 1));   // below the fine level a cycle starts from zero
     TRY(fused_cycle_from<T>(h, l + 1, stop, false));
     return fused_post<T>(h, l, h->opt.nu2, stop, norm && l == 0);
@@ -908,6 +916,7 @@ bmg_status solve_level(bmg_solver *h, int l, double tol, int maxc, int *cycles)
 {
     const Lev<double> &L = h->L[l];
     *cycles = 0;
+    h->small_n = small_from(h, false);
     const int np = std::min(NPART_ROWS, L.n);
     // (with sweep counts that both passes take, a cycle moves the iterate twice,
     // so cycles enqueued past the stop leave L.u where it was)
@@ -1471,6 +1480,7 @@ static bmg_status refine_step64(bmg_solver *h, const int *stop)
 bmg_status bmg_vcycle(bmg_solver *h, const double *rhs, double *x, double *rel_res)
 {
     if (!h || !rhs || !x) return fail(BMG_EINVAL, "NULL argument");
+    h->small_n = small_from(h, false);
     const Lev<double> &L = h->L[0];
     if (h->f32) {
         TRY(pack_in(h, rhs, h->B0));
@@ -1506,6 +1516,7 @@ bmg_status bmg_solve(bmg_solver *h, const double *rhs, double *x, double tol, bm
     const auto t0 = std::chrono::steady_clock::now();
     if (!h || !rhs || !x) return fail(BMG_EINVAL, "NULL argument");
     if (!(tol >= 0.0)) return fail(BMG_EINVAL, "tol must be >= 0");
+    h->small_n = small_from(h, true);
     const Lev<double> &L = h->L[0];
     const size_t pl0 = (size_t)(L.n + 2) * L.ld * sizeof(double);
     // a new solve: no history, no stop code left from the last one
@@ -2150,6 +2161,7 @@ bmg_status bmg_block_solve(bmg_block *B, const double *rhs, double *x, double to
     if (!B || !rhs || !x) return fail(BMG_EINVAL, "NULL argument");
     if (!(tol >= 0.0)) return fail(BMG_EINVAL, "tol must be >= 0");
     bmg_solver *hb = &B->hb;
+    hb->small_n = small_from(B->parent, true);
     const int K = B->k;
     const Lev<double> &L = hb->L[0];
     const size_t n2 = (size_t)L.n * L.n;
