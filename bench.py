@@ -34,12 +34,13 @@ HBM_PEAK_GBS = 8000.0
 # counts each array a launch needs once (read or written) for the variant that
 # ran: a five-point FP64 pre pass reads A_O, A_W, A_S, b, u and writes u (48 B
 # per fine point) and writes b_c, u_c (16 B per coarse point: 4 per fine point),
-# 52 B per fine point, as it computes the interpolation weights itself; with
-# stored weights their 8 planes add 16 B per fine point.
+# 52 B per fine point; the 8 planes of the stored interpolation weights add 16 B
+# per fine point (not counted where they follow from the stencil).
 
 
 KERNEL_NAMES = {"postpre": "k_postpre_wave (fine post pass with the next cycle's fine pre pass)",
-                "pre": "k_pre (fine pre pass)", "resnorm": "k_resid_dd (FP64 outer residual)",
+                "pre": "k_pre_wave (fine pre pass)",
+                "post": "k_post_res_wave (FP32 fine post pass, iterate update, next FP64 residual)", "resnorm": "k_resid_dd (FP64 outer residual)",
                 "smooth": "k_gs_colour / line relaxation (fine level)"}
 
 
@@ -397,7 +398,8 @@ def bench_nonsym(args):
         "config": {"workload": f"cd_{n}", "n": n, "beta": beta, "flow": "rotating", "coarsest": coarsest,
                    "cycles": info["cycles"], "rho": info["rho"], "final_rel_res": info["rel_res"],
                    "converged": info["status"] == 0},
-        "roofline": {"bound": "hbm", "kernel": "k_ns_gs_pair (fine level, the two colours of one row parity)", "achieved": achieved,
+        "roofline": {"bound": "hbm", "kernel": "k_ns_gs_pair (fine level, the two colours of one row parity, as a step by "
+                     "itself: a solve runs the five-point fine level as k_pre_wave and k_post_wave)", "achieved": achieved,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": None,
                      "avg_launch_ms": launch_ms, "bytes_per_launch": bytes_per_launch},
     }
@@ -577,7 +579,9 @@ def main():
         opts["graph_mode"] = 1
     tclass = "pre" if args.kernels == "fused" and not line else "smooth"
     if prec == boxmg.BMG_FP32_IR:
-        tclass = "resnorm"     # the FP64 outer residual (accurate, 64 B per point)
+        # the fine post pass of a refinement step with the next step's residual;
+        # with separate kernels the FP64 outer residual (64 B per point)
+        tclass = "post" if tclass == "pre" else "resnorm"
     elif tclass == "pre":
         # FP64 V(2,1) on the five-point fine level: the fine post pass of each
         # plain cycle runs with the next cycle's fine pre pass (k_postpre_wave)
@@ -614,7 +618,7 @@ def main():
     # stop flag is set); the fine pre pass runs once per cycle, so its working
     # launches are the cycles, and their average includes those few microseconds
     working = launches
-    if tclass == "pre":
+    if tclass in ("pre", "post"):
         working = min(launches, sum(i["cycles"] for i in infos))
     if tclass == "postpre":
         # one per plain cycle: up to the first residual at or below 16 tol,

@@ -706,7 +706,7 @@ bmg_status ns_coarse(bmg_ns *h)
 // the sweeps, the residual and the restriction; the interpolation, the sweeps
 // and the norm of the result.  The zero corner couplings are not read, and the
 // iterate moves to the level's r and back, whose residual is never stored.
-// 4095^2, V(2,1): 305 us and 285 us, 4.2 and 4.4 TB/s, where the steps apart took
+// 4095^2, V(2,1): 305 us and 285 us, 4.6 and 4.8 TB/s, where the steps apart took
 // 6 x 231 for the colours, 309 for the residual, 100 and 127 for restriction
 // and interpolation and 277 for the norm.
 bool ns_fused(const bmg_ns *h)
