@@ -333,7 +333,7 @@ def bench_learned(args):
     tflops = flop / (fwd_ms * 1e-3) / 1e12
     S0.close()
     net.close()
-    out["roofline"] = {"bound": "mfma", "kernel": "network forward (k_net_features, k_conv x 3)",
+    out["roofline"] = {"bound": "mfma", "kernel": "network forward (k_net_conv12, k_net_out)",
                        "achieved": tflops, "peak": 2500.0, "unit": "TFLOP/s", "frac": tflops / 2500.0,
                        "traffic": None, "flop_per_launch": flop, "avg_launch_ms": fwd_ms,
                        "dtype": "bf16 (fp32 accumulate)"}

@@ -841,8 +841,8 @@ bmg_status wgrad(bmg_net *h, const bf16_t *in, int in_side, const bf16_t *d, int
     WgArgs a{in, in_side, d, d_side, lo, width, h->part};
     hipLaunchKernelGGL((k_conv_wgrad<CINP, COUTP, STRIDE>), dim3(waves / 4), dim3(256), 0, h->st, a);
     const int nred = 9 * CINP * COUTP + cout;
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3((nred + WR_THREADS - 1) / WR_THREADS), dim3(WR_THREADS), 0, h->st, (const float *)h->part, waves,
-                       CINP, COUTP, cin, cout, h->G, woff, boff);
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3((nred + WR_THREADS - 1) / WR_THREADS), dim3(WR_THREADS), 0, h->st,
+                       (const float *)h->part, waves, CINP, COUTP, cin, cout, h->G, woff, boff);
     LAUNCHCHK();
     return BMG_OK;
 }
