@@ -163,13 +163,15 @@ enum { MODE_INIT = 1, MODE_STEPS = 2, MODE_FINISH = 3 };
 // after it (through this CU's L1 and this XCD's L2) sees what other workgroups
 // wrote before it.  A device-scope fence writes back or invalidates the whole
 // L2, under the loads of every other workgroup of the XCD, so there is one of
-// each per workgroup (its waves share one L1) and none in the wait: the
-// workgroups count themselves in by groups, the last of a group at the root,
-// the last there raises the generation, and one thread per workgroup polls that
-// with plain loads.  (With the cooperative-groups barrier, and fences by every
-// wave around it, the batch of 60 problems took 5.4 ms per step, its early
-// finishers' polling slowing the rest; with this one and the arrays' addresses
-// in scalar registers 1.7 ms.)
+// each per workgroup and none in the wait.  The release by one wave covers the
+// stores of all: every wave first waits until its own have reached the L2 (the
+// workgroup barrier alone does not wait for them).  The acquire covers all, as
+// the waves share one L1.  The workgroups count themselves in by groups, the
+// last of a group at the root, the last there raises the generation, and one
+// thread per workgroup polls that with plain loads.  (With the
+// cooperative-groups barrier, and fences by every wave around it, the batch of
+// 60 problems took 5.4 ms per step, its early finishers' polling slowing the
+// rest; with this one and the arrays' addresses in scalar registers 1.7 ms.)
 struct PhaseBarrier {
     GridBar *bar;
     unsigned gen;
@@ -192,6 +194,7 @@ struct PhaseBarrier {
     }
     __device__ __forceinline__ void wait()
     {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         ++gen;
         if (threadIdx.x == 0) {
