@@ -1719,6 +1719,7 @@ bmg_status bmg_solve_noalloc(const double *stencil, int n, int kind, const bmg_o
 // guess makes easy; the iterate goes to xout (tight).
 static bmg_status probe(bmg_solver *h, const double *rhs, const double *x, double *xout, int cycles, double *rho)
 {
+    h->small_n = small_from(h, false);
     const Lev<double> &L = h->L[0];
     TRY(pack_in(h, rhs, L.b));
     TRY(pack_in(h, x, L.u));
