@@ -1318,8 +1318,12 @@ static bmg_status cycle_and_norm(bmg_solver *h, double tol, int maxc, double ref
 }
 
 // Tiles of k_postpre_wave on the fine level: halo for the interpolation edge,
-// the sweeps, the residual and the restriction.
-static TileGeo postpre_geo(const bmg_solver *h) { return wave_tiles(h, 0, 2 * (h->opt.nu1 + 1) + 4); }
+// the sweeps, the residual and the restriction.  The table's heights, found for
+// other passes and for batches, do not apply to it.
+static TileGeo postpre_geo(const bmg_solver *h)
+{
+    return wave_geo(h->L[0].n, 2 * (h->opt.nu1 + 1) + 4, h->opt.tile_rows, 1);
+}
 
 // Plain FP64 cycles where the fine post pass of each cycle runs together with
 // the fine pre pass of the next (k_postpre_wave): an FP64 five-point fine level
