@@ -71,8 +71,8 @@ typedef struct {
                         and each cycle is one refinement step with an accurate
                         residual, which converges below the residual floor of
                         FP64 vectors; 0 = never (default 16) */
-    int tile_rows;   /* grid rows per workgroup tile of the fused passes
-                        (even, 0 = a measured default for each level size) */
+    int tile_rows;   /* grid rows per tile of the fused passes (even, 0 =
+                        chosen for each pass and level size) */
     int interp;      /* BMG_INTERP_BOXMG (default): operator-induced weights on
                         every level; BMG_INTERP_LEARNED: the weights of levels
                         l < learned_levels come from the network `net` */
@@ -345,8 +345,12 @@ bmg_status bmg_trace_read(bmg_solver *h, int *launches, double *total_ms, double
 
 /* ------------------------------------------------------------------------
  * Tile shapes of the fused passes.  A process-wide table of rows per tile for
- * each level size n = 2^m - 1, written by the autotuner; 0 restores the
- * built-in default.  bmg_options.tile_rows, when set, overrides the table.
+ * each level size n = 2^m - 1, written by the autotuner.  Without an entry each
+ * pass, and a batch, chooses its own height; get then returns that of the FP64
+ * five-point pre pass of two sweeps.  set with 0, or with the value that get
+ * returns without an entry, removes the entry.  bmg_options.tile_rows, when
+ * set, overrides the table; the fine level's pass across cycles
+ * (BMG_TRACE_POSTPRE) takes that option but not the table.
  * ---------------------------------------------------------------------- */
 bmg_status bmg_tile_rows_set(int n, int rows);
 bmg_status bmg_tile_rows_get(int n, int *rows);

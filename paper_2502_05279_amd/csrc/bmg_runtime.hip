@@ -80,20 +80,25 @@ TileGeo tile_geo(int n, int hx, int ht)
 
 }  // namespace bmgi
 
+// The height that a level of size n has without an entry: that of its pre pass
+// of two sweeps (FP64, five-point).  Other passes, and batches, then have
+// heights of their own, so writing this value restores all of them.
+static int builtin_tile_rows(int n) { return wave_geo(n, 2 * 2 + 2, 0, 1).ht; }
+
 extern "C" bmg_status bmg_tile_rows_set(int n, int rows)
 {
     if (!valid_n(n)) return fail(BMG_EINVAL, "n=%d is not 2^m-1", n);
     if (rows < 0 || (rows & 1) || rows > 65536) return fail(BMG_EINVAL, "rows=%d must be even, 0 = default", rows);
     int m = 0;
     while ((1 << m) < n + 1) ++m;
-    g_tile_rows[m] = rows;
+    g_tile_rows[m] = rows == builtin_tile_rows(n) ? 0 : rows;
     return BMG_OK;
 }
 
 extern "C" bmg_status bmg_tile_rows_get(int n, int *rows)
 {
     if (!valid_n(n) || !rows) return fail(BMG_EINVAL, "bad arguments");
-    *rows = tile_rows_for(nullptr, n, false);
+    *rows = tuned_tile_rows(n) > 0 ? tuned_tile_rows(n) : builtin_tile_rows(n);
     return BMG_OK;
 }
 

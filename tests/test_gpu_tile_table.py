@@ -1,5 +1,6 @@
-"""What the process-wide table of tile heights may not change: results, and the
-pass that runs a cycle's fine level together with the next cycle's."""
+"""The process-wide table of tile heights: what it may not change (results, the
+pass that runs a cycle's fine level together with the next cycle's) and that
+writing back what was read changes nothing."""
 import numpy as np
 import pytest
 import torch
@@ -39,3 +40,19 @@ def test_cross_cycle_pass_keeps_its_own_height(gpu, table):
         table(n, 2)
     got = solve(st, rhs)
     assert got[2] == want[2] > 0 and np.array_equal(got[0], want[0])
+
+
+@pytest.mark.parametrize("prec", [boxmg.BMG_FP64, boxmg.BMG_FP32_IR])
+def test_writing_back_what_was_read_changes_nothing(gpu, table, prec):
+    """The history's sums follow the tiles of the fine post pass (two sweeps: a
+    pass of its own), so equal histories to the bit are equal tiles."""
+    st, rhs = problem(1023)
+    want = solve(st, rhs, nu2=2, precision=prec)
+    for n in SIZES:
+        table(n, boxmg.tile_rows_get(n))
+    got = solve(st, rhs, nu2=2, precision=prec)
+    assert got[1] == want[1] and np.array_equal(got[0], want[0])
+    for n in SIZES:
+        table(n, 6)
+    got = solve(st, rhs, nu2=2, precision=prec)
+    assert np.array_equal(got[0], want[0])
