@@ -5,7 +5,7 @@ candidate tile heights (rows per workgroup tile) with the library's HIP-event
 trace, on a five-point level (the fine level of an n x n problem) and on a
 nine-point level (level 1 of a (2n+1) x (2n+1) problem), picks the fastest
 and installs it with ``bmg_tile_rows_set``.  Results are cached in a JSON
-file keyed by architecture, precision and n.
+file keyed by architecture, the kernels that were timed, precision and n.
 """
 from __future__ import annotations
 
@@ -17,6 +17,9 @@ import torch
 from . import boxmg, inputs
 
 DEFAULT_CANDIDATES = (2, 4, 8, 16, 32, 64, 128)
+
+# the kernels the cached heights were timed on; renamed with them
+KERNELS = "wave"
 
 # timings (ms per pre+post pass pair, by tile height) of the last tune() call
 LAST: dict = {}
@@ -63,7 +66,7 @@ def tune(sizes=(127, 255, 511, 1023, 2047), precision: int = boxmg.BMG_FP64,
     dev = torch.device("cuda:0")
     out = {}
     for n in sizes:
-        key = f"{_arch()}:{'fp32' if precision == boxmg.BMG_FP32_IR else 'fp64'}:{n}"
+        key = f"{_arch()}:{KERNELS}:{'fp32' if precision == boxmg.BMG_FP32_IR else 'fp64'}:{n}"
         if key in cache:
             out[n] = int(cache[key]["rows"])
             LAST[n] = cache[key]["ms"]
