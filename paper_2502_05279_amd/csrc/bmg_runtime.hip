@@ -333,6 +333,18 @@ static inline double stencil_planes(bool nine) { return nine ? 5.0 : 3.0; }
 // -------------------------------------------------------- cycle steps
 const dim3 B2(64, 4);
 
+// The LDS that the column half-sweeps of the longest lines take (rows, one line
+// a workgroup, stay below the 64 KB that need no asking), allowed once by a
+// set-up: the kernels are shared by levels and handles of all sizes.
+bmg_status line_half_setup()
+{
+    const int most = (int)line_lds(LINE_FUSED_N, LINE_COLS);
+    for (const void *f : {(const void *)k_line_sweep<false, false, LINE_COLS>,
+                          (const void *)k_line_sweep<false, true, LINE_COLS>})
+        HIPCHK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, most));
+    return BMG_OK;
+}
+
 // Half-sweep of the lines of parity par of level l in one launch.
 template <bool X, int G>
 bmg_status line_half(bmg_solver *h, const Lev<double> &L, bool nine, int par, const int *stop, int l)
@@ -340,8 +352,6 @@ bmg_status line_half(bmg_solver *h, const Lev<double> &L, bool nine, int par, co
     const int nl = par ? (L.n + 1) / 2 : (L.n - 1) / 2;
     const dim3 grid((nl + G - 1) / G), blk(LINE_THREADS);
     const size_t lds = line_lds(L.n, G);
-    const void *f = nine ? (const void *)k_line_sweep<X, true, G> : (const void *)k_line_sweep<X, false, G>;
-    if (lds > 64 * 1024) HIPCHK(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     const double *lf = X ? h->lfx[l] : h->lfy[l], *rf = X ? h->rfx[l] : h->rfy[l];
     if (nine) hipLaunchKernelGGL((k_line_sweep<X, true, G>), grid, blk, lds, h->st, L, par, lf, rf, stop);
     else hipLaunchKernelGGL((k_line_sweep<X, false, G>), grid, blk, lds, h->st, L, par, lf, rf, stop);
@@ -1094,6 +1104,7 @@ static bmg_status setup_into(bmg_solver *h, const double *stencil, int n, int ki
     hipLaunchKernelGGL(k_band_expand, dim3(h->band.M / 4), dim3(256), 0, h->st, h->band.nc, (const double *)h->Lb,
                        (const double *)h->Dd, (double *)h->band.CF, (double *)h->band.CG, (double *)h->band.Dp);
     if (op.smoother == BMG_SMOOTH_LINE) {
+        SCHK(line_half_setup());
         // y-lines in the grid's frame; x-lines on the transposed O (in the
         // scratch plane) and W
         for (int l = 0; l < h->nlev; ++l) {
