@@ -250,7 +250,8 @@ bmg_status bmg_block_workspace_bytes(const bmg_solver *h, int k, size_t *bytes);
 /* A block of k right-hand sides on the hierarchy of h (which must outlive it;
  * the block runs on h's stream and only reads h's operators, weights and
  * coarsest factor).  workspace: device, >= bmg_block_workspace_bytes, owned
- * by the caller, outliving the block.  Errors: BMG_EINVAL, BMG_EWORKSPACE. */
+ * by the caller, outliving the block, cleared on h's stream.  Errors:
+ * BMG_EINVAL, BMG_EWORKSPACE. */
 bmg_status bmg_block_create(bmg_block **out, bmg_solver *h, int k, void *workspace, size_t bytes);
 
 /* bmg_solve for the k right-hand sides at once.

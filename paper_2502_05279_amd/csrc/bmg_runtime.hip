@@ -2148,6 +2148,8 @@ bmg_status bmg_block_create(bmg_block **out, bmg_solver *h, int k, void *workspa
     if ((uintptr_t)workspace % ALIGN) return fail(BMG_EINVAL, "workspace not %zu-byte aligned", ALIGN);
     const size_t need = block_plan(h, k, nullptr, nullptr);
     if (bytes < need) return fail(BMG_EWORKSPACE, "block workspace %zu < %zu bytes", bytes, need);
+    // the passes take the planes' rings as zero
+    HIPCHK(hipMemsetAsync(workspace, 0, need, h->st));
     bmg_block *B = new bmg_block;
     B->parent = h;
     B->k = k;
