@@ -344,12 +344,8 @@ def bench_nonsym(args):
     """Nonsymmetric BoxMG (restriction from the transposed operator, coarse
     operators R A P) on a convection-diffusion operator: unit diffusion plus
     the upwind part of a recirculating flow of speed 300 on the 4095^2 grid,
-    coarsest level 63^2.  One step = set-up + solve to the tolerance.  The
-    roofline is that of the fine level's Gauss-Seidel sweep (two launches, each
-    the two colours of the rows of one parity), timed with HIP events on the
-    library's stream after the timed steps: per launch the stencil rows,
-    right-hand side and new values of its half of the points (88 B each) and
-    the iterate read once (8 B per point), 52 B per grid point."""
+    coarsest level 63^2.  One step = set-up + solve to the tolerance.  No
+    roofline: the library has no trace of this solver's passes."""
     import torch
     from paper_2502_05279_amd import boxmg, inputs
 
@@ -378,18 +374,7 @@ def bench_nonsym(args):
             S.close()
     torch.cuda.synchronize()
     dt = (time.perf_counter() - t0) / args.steps
-    # the fine level's sweep, timed on the library's stream
-    ev0, ev1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    reps = 20
-    ev0.record()
-    for _ in range(reps):
-        S.step(0, "smooth", 1)
-    ev1.record()
-    torch.cuda.synchronize()
-    launch_ms = ev0.elapsed_time(ev1) / (2 * reps)
     S.close()
-    bytes_per_launch = 52.0 * n * n
-    achieved = bytes_per_launch / (launch_ms * 1e-3) / 1e9
     out = {
         "metric": f"fine DOF/s solved to {args.tol:g} rel. residual ({n}^2 convection-diffusion, nonsymmetric BoxMG)",
         "value": n * n / dt, "unit": "DOF/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -398,10 +383,7 @@ def bench_nonsym(args):
         "config": {"workload": f"cd_{n}", "n": n, "beta": beta, "flow": "rotating", "coarsest": coarsest,
                    "cycles": info["cycles"], "rho": info["rho"], "final_rel_res": info["rel_res"],
                    "converged": info["status"] == 0},
-        "roofline": {"bound": "hbm", "kernel": "k_ns_gs_pair (fine level, the two colours of one row parity, as a step by "
-                     "itself: a solve runs the five-point fine level as k_pre_wave and k_post_wave)", "achieved": achieved,
-                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                     "avg_launch_ms": launch_ms, "bytes_per_launch": bytes_per_launch},
+        "roofline": None,
     }
     print(json.dumps(out))
 

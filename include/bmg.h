@@ -297,7 +297,9 @@ const char *bmg_last_error(void);
  * The *32 fields are the FP32 hierarchy (precision BMG_FP32_IR only) and
  * transfer float data.  A solve or V-cycle leaves the level-0 u32 unspecified:
  * the fused fine-level pass of a refinement step adds each FP32 correction to
- * the double-FP64 iterate in place of storing it. */
+ * the double-FP64 iterate in place of storing it.  A solve that ended in
+ * refinement steps, or with FP32_IR, leaves the level-0 u unspecified too, and
+ * any solve the level-0 r: the fused passes use them as second buffers. */
 enum {
     BMG_F_U = 0, BMG_F_B = 1, BMG_F_R = 2,
     BMG_F_AO = 3, BMG_F_AW = 4, BMG_F_AS = 5, BMG_F_ASW = 6, BMG_F_ANW = 7,
@@ -337,7 +339,8 @@ bmg_status bmg_step(bmg_solver *h, int level, int step, int arg, int fp32);
  * stream and returns the number of launches timed, their total duration in
  * milliseconds and (bytes, may be NULL) their algorithmic HBM bytes: each
  * array the launch needs counted once, read or written, for the variant that
- * ran (a fused pre pass that computes its weights does not count them).  It
+ * ran.  (The weights of an FP64 five-point pre pass of one right-hand side
+ * follow from the stencil and are not counted, unless they are learned.)  It
  * then clears the record.  Classes: */
 enum { BMG_TRACE_SMOOTH = 0, BMG_TRACE_PRE = 1, BMG_TRACE_POST = 2, BMG_TRACE_RESNORM = 3,
        BMG_TRACE_POSTPRE = 4 /* fine post pass fused with the next cycle's fine pre pass */ };
@@ -510,11 +513,13 @@ bmg_status bmg_solve_select(bmg_solver *learned, bmg_solver *boxmg, const double
  * interpolation the same formulas induce from A^T, applied with the term
  * order of Fig. restrict_kernel; the coarse operators are R A P in all nine
  * directions; every level stores all nine entries of each row; relaxation is
- * four-colour Gauss-Seidel (one launch per colour); the coarsest level (size
- * coarsest_n, 3 by default, at most 63) is factored as a band L D U (unit
- * triangular L and U) and solved by the one-wave band substitutions, each
- * update one fused multiply-add.  Options used: nu1, nu2, max_cycles,
- * coarsest_n; precision, smoother and interpolation must be the defaults.
+ * four-colour Gauss-Seidel (two colours a launch; on a five-point fine level
+ * inside two fused passes a cycle, with BMG_KERNELS_FUSED, nu1 and nu2 of 1 or
+ * 2); the coarsest level (size coarsest_n, 3 by default, at most 63) is factored
+ * as a band L D U (unit triangular L and U) and solved by the one-wave band
+ * substitutions, each update one fused multiply-add.  Options used: nu1, nu2,
+ * max_cycles, coarsest_n, kernels; precision, smoother and interpolation must be
+ * the defaults.
  * ---------------------------------------------------------------------- */
 typedef struct bmg_ns bmg_ns;
 
@@ -541,10 +546,10 @@ bmg_status bmg_ns_destroy(bmg_ns *h);
 /* Level access for tests: fields 0..8 the stencil planes (SW..NE), 9 P's and
  * 10 R's weights (8 planes of the coarse level's (nc+2)^2 shape), 11 u, 12 b,
  * 13 r (padded (n+2)^2, tight on output), 14 the coarsest factor (L band
- * m x w, U band m x w with U_ik at i w + (k - i - 1), D m).  Import takes u, b,
- * r.  Steps: 0 = arg sweeps, 1 = residual, 2 = restriction of r into the next
- * level's b (its u zeroed), 3 = u += P u_next, 4 = the coarsest solve.  All
- * synchronous on the handle's stream. */
+ * m x w, U band m x w with U_ik at i w + (k - i - 1), D m).  A solve leaves r
+ * unspecified.  Import takes u, b, r.  Steps: 0 = arg sweeps, 1 = residual,
+ * 2 = restriction of r into the next level's b (its u zeroed), 3 = u += P u_next,
+ * 4 = the coarsest solve.  All synchronous on the handle's stream. */
 bmg_status bmg_ns_num_levels(const bmg_ns *h, int *nlev);
 bmg_status bmg_ns_level_n(const bmg_ns *h, int level, int *n);
 bmg_status bmg_ns_export(bmg_ns *h, int level, int field, double *dst);

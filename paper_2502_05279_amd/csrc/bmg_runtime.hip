@@ -47,20 +47,14 @@ int tile_rows_for(const bmg_solver *h, int n, bool nine)
 {
     if (h && h->opt.tile_rows > 0) return h->opt.tile_rows;
     if (tuned_tile_rows(n) > 0) return tuned_tile_rows(n);
-    // measured defaults (FP64, V(2,1)): the fewest warm-up rows re-read while
-    // the tiles still fill the chip in whole rounds (at 4095^2, 96 rows give
-    // 731 tiles, one round of three 48 KiB pre-pass or four 40 KiB post-pass
-    // workgroups per CU, where 64 rows give 1088 and a second round of 64, and
-    // a second round costs more than the rows it saves); on the levels below 1023 the
-    // shortest tiles win, their passes being bound by the latency of the row
-    // pipeline rather than by bandwidth
-    // at 8191^2 (the FP32 refinement's fine level, five 20 KiB workgroups
-    // per CU) 224 rows give 1258 tiles, one round of 1280
+    // the passes that still run as workgroups (three sweeps before, and a
+    // refinement step's post pass by itself): few warm-up rows re-read while the
+    // tiles fill the chip in a whole round of workgroups, a second round costing
+    // more than the rows it saves (the heights of passes of two sweeps, for which
+    // they were measured); below 1023 the shortest tiles, these passes being
+    // bound by the latency of the row pipeline rather than by bandwidth
     if (n >= 8191) return 224;
     if (n >= 4095) return 96;
-    // nine-point tiles take 72 KiB of LDS, two per CU: 40 rows give 468
-    // tiles at 2047^2 and 12 rows 430 at 1023^2, each one round of 512 (36
-    // and 10 rows give 513 and 515)
     if (n >= 2047) return nine ? 40 : 48;
     if (n >= 1023) return nine ? 12 : 16;
     if (n >= 511) return 4;
@@ -119,8 +113,9 @@ double ms_since(std::chrono::steady_clock::time_point t0)
 //   down / apart 151 / 90 us; 1023^2 364 / 266.
 // - A solve enqueues cycles past its stop, and every launch of those counts: from
 //   63 down.  127^2 Poisson to 1e-6, coarsest 3, from 63 / from 31 / apart 647 /
-//   702 / 1027 us, coarsest 15 685 / 744 / 790 (a jumping field with its three
-//   times as many cycles, 3: 1653 / 1568 / 2031, 15: 1528 / 1474 / 1448).
+//   702 / 1027 us, coarsest 15 685 / 744 / 790.  Longer solves, in which they
+//   weigh less, pay for that: a jumping field with three times as many cycles 3:
+//   1653 / 1568 / 2031, 15: 1528 / 1474 / 1448.
 // - A cycle alone and the inner solves of the two-grid objective (some 25 cycles):
 //   from 31 down, apart above a coarsest level of 15 (127^2, 3: 85 / 82 / 104 us,
 //   7: 83 / 82 / 94, 15: 92 / 88 / 85; 255^2, 15: 121 / 113 / 108).

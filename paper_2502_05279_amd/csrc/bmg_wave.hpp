@@ -41,9 +41,11 @@ enum : int { FIVE = 0, NINE = 1, FIVE_NS = 2 };
 // Tiles of a wave-stream pass over n^2 points for nrhs right-hand sides, hx halo
 // columns on each side of a strip, of `rows` rows (0: chosen).  An FP64 pre pass
 // takes more than 256 registers, one wave per SIMD: the height is the least that
-// leaves all tiles in one round of 1024.  Half-height tiles (a round of 2048,
-// which FP32 and the post passes could hold) re-read more rows for no more
-// speed: 2047^2 pre 138 against 132 us, post 134 against 121.
+// leaves all tiles in one round of 1024.  Tiles of half that height (a round of
+// 2048, which FP32 and the post passes could hold) re-read more rows: nine-point
+// FP64, two sweeps before and one after, 2047^2 79 + 69 us against 87 + 78, 1023^2
+// 29 + 18 against 40 + 24, the cross-cycle pass of 4095^2 299 against 324; in FP32
+// 2047^2 42 + 29 either way, 1023^2 20.6 + 11.8 against 20.8 + 10.8.
 constexpr int WAVE_SLOTS = 1024;
 inline TileGeo wave_geo(int n, int hx, int rows, int nrhs)
 {
