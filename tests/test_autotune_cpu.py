@@ -1,6 +1,9 @@
 """The tuner's cache of tile heights: an entry is installed only if it was
 measured on the kernels that the heights would be used for."""
 import json
+from types import SimpleNamespace
+
+import torch
 
 from paper_2502_05279_amd import autotune, boxmg
 
@@ -11,7 +14,7 @@ def test_heights_of_other_kernels_are_measured_again(tmp_path, monkeypatch):
     monkeypatch.setenv("BMG_TUNE_CACHE", str(path))
     monkeypatch.setattr(autotune, "_arch", lambda: "gfx950")
     monkeypatch.setattr(boxmg, "discretize", lambda k, f: (k, f))
-    monkeypatch.setattr(autotune.torch, "device", lambda name, make=autotune.torch.device: make("cpu"))
+    monkeypatch.setattr(autotune, "torch", SimpleNamespace(device=lambda name: "cpu", from_numpy=torch.from_numpy))
     timed, installed = [], {}
     monkeypatch.setattr(autotune, "_time_level", lambda st, rhs, level, rows, *a: timed.append(rows) or 1.0 / rows)
     monkeypatch.setattr(boxmg, "tile_rows_set", installed.__setitem__)
